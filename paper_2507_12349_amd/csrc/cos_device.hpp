@@ -8,6 +8,7 @@ namespace libcos {
 #define COS_RF(x) __builtin_amdgcn_readfirstlane(x)
 
 typedef __attribute__((address_space(3))) double lds_double;
+typedef __attribute__((address_space(3))) int lds_int;
 // read-only tables read at wave-uniform addresses: through the constant
 // address space they are fetched with scalar loads
 typedef const __attribute__((address_space(4))) int32_t cint32;
@@ -49,6 +50,53 @@ __device__ __forceinline__ void lane_st(double *base, uint32_t lane8, double x) 
     global_char *p = (global_char *)base;
     asm volatile("" : "+s"(p));
     *(__attribute__((address_space(1))) double *)(p + lane8) = x;
+}
+
+// accesses of the tile kernels: a buffer descriptor over a plane of states
+// (scalar registers), a byte offset per lane (one vector register) and a
+// wave-uniform byte offset (one scalar register): no address arithmetic beyond
+// one scalar add per slot.  Offsets inside a plane stay below 2^32.
+typedef __amdgpu_buffer_rsrc_t plane_t;
+typedef unsigned int __attribute__((ext_vector_type(2))) u32x2;
+constexpr int kPlaneFlags = 0x00020000, kNt = 2;   // raw buffer; the nontemporal hint
+__device__ __forceinline__ plane_t make_plane(const double *base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0xffffffffu, kPlaneFlags);
+}
+__device__ __forceinline__ double slot_ld(plane_t p, uint32_t lane_off, uint32_t off) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(p, (int)lane_off, (int)off, 0));
+}
+__device__ __forceinline__ void slot_st(plane_t p, uint32_t lane_off, uint32_t off, double x) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), p, (int)lane_off, (int)off, 0);
+}
+// STREAM: with the nontemporal hint (states far larger than the caches, read
+// and written once)
+template <bool STREAM>
+__device__ __forceinline__ double state_ld(plane_t p, uint32_t lane_off, uint32_t off) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(p, (int)lane_off, (int)off, STREAM ? kNt : 0));
+}
+template <bool STREAM>
+__device__ __forceinline__ void state_st(plane_t p, uint32_t lane_off, uint32_t off, double x) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), p, (int)lane_off, (int)off, STREAM ? kNt : 0);
+}
+
+// Copies `slots` slots of 64 doubles from global memory to LDS by the whole
+// workgroup, without passing through registers: every wavefront issues all of
+// its 1 KB loads (two slots each, 16 bytes per lane) back to back, so the copy
+// costs one memory latency instead of one per iteration of a load-and-write
+// loop.  Returns when the caller's wavefront's part has arrived; the caller
+// still needs a barrier.  src and dst are 16-byte aligned (slots are 512 bytes).
+__device__ __forceinline__ void stage_slots(double *dst, const double *src, int slots) {
+    typedef __attribute__((address_space(1))) const void gvoid;
+    typedef __attribute__((address_space(3))) void lvoid;
+    const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    for (int p = wave; 2 * p + 1 < slots; p += waves)
+        __builtin_amdgcn_global_load_lds((gvoid *)(src + p * 128 + lane * 2), (lvoid *)(dst + p * 128), 16, 0, 0);
+    if ((slots & 1) && wave == waves - 1) {   // an odd last slot: 4 bytes per lane, twice
+        const int o = (slots - 1) * 64;
+        __builtin_amdgcn_global_load_lds((gvoid *)((const int *)(src + o) + lane), (lvoid *)(dst + o), 4, 0, 0);
+        __builtin_amdgcn_global_load_lds((gvoid *)((const int *)(src + o) + 64 + lane), (lvoid *)(dst + o + 32), 4, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 }  // namespace libcos

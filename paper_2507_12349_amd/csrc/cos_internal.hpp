@@ -28,18 +28,24 @@ namespace libcos {
 //   when no vertex below h is half visited (the cycle is still at its head).
 // ---------------------------------------------------------------------------
 
-// Per-level mask records (one 64-byte record per mask, level by level): what a
-// wavefront needs to process a mask, fetched with one scalar load.
+// Mask records (one 64-byte record per mask, level by level).  The plain state
+// tables (counts, and the integer counting mode):
 //   [0] mask code (base 3)     [1] ones | (twos << 16)
 //   [2] level-relative row of (m, 0)
 //   [3 + w] level-relative row of (m + e_w, 0) for each vertex w with m_w < 2
 //           (-1 otherwise)
+// The level kernels' tables (n >= 2): masks, levels and rows of the tile
+// scheme of cos_level.hip, over the first n - 1 vertices; in every level the
+// special masks (m_0 = 2, no vertex visited once) come last.  A row has n - 1
+// slots; what a wavefront needs is fetched with one scalar load:
+//   [0] ones | (twos << 16)    [1] first row (bytes from the level's first row)
+//   [2 + w] first row of m + e_w (bytes, in the next level), m_w < 2
 constexpr int kRecInts = 16;
 static_assert(3 + COS_NMAX <= kRecInts, "mask record too small");
 
 struct DevPlan {
     const int32_t *mrec;      // [total_masks][kRecInts]
-    const int4 *levels;       // [2n + 2] .x = first row, .y = #rows, .z = first mask, .w = #masks
+    const int4 *levels;       // [levels + 2] .x = first row, .y = #rows, .z = first mask, .w = #masks
     int32_t n;
     int32_t max_rows;         // largest #rows of a level
     int32_t max_masks;        // largest #masks of a level
@@ -130,9 +136,15 @@ struct LvlArgs {
     int64_t F_gstride, F_frows;
     int32_t F_row0;
     int32_t level, group0, nfs, stubs, mpb;
+    // unlabelled levels: the level's first mask, its masks that are not special
+    // (in nblocks blocks of mpb masks per wavefront; split, and the reverse with
+    // row_items: of mpb masks) and its special masks, which take further workgroups
+    int32_t mask0, nmasks, nspecial, nblocks;
+    int32_t split;            // forward: blocks of mpb masks whose heads go to different wavefronts
+    int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)
     int32_t det_groups;       // deterministic reverse: groups of the order (stride of the partial sums)
-    int32_t row_items;        // reverse: the work items are (mask, row) pairs, not masks (levels of few masks)
+    int32_t row_items;        // reverse: the work items are (mask, row) pairs (unlabelled: (mask, head)), not masks
     double W;                 // factor of one closed cycle: w * nflav (uniform) or w
     double *out;              // forward, last level: S per configuration (may be null)
     const double *out_bar;    // reverse: dL/dS per configuration
@@ -147,23 +159,28 @@ hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
 // sublattice forward level (cos_sub.hip): `a.plan` is a sublattice plan, rows
 // hold 2n slots, GT holds 2n x 2n matrices; wpb <= 16
 hipError_t launch_sub_level(const LvlArgs &a, int nblocks, int ngroups, int wpb, hipStream_t s);
-// sublattice reverse level: adj_waves_per_block() wavefronts per workgroup
+// sublattice reverse level: kSubAdjWaves wavefronts per workgroup
 hipError_t launch_sub_adj_level(const LvlArgs &a, int nblocks, int ngroups, hipStream_t s);
-// nblocks = blocks of `a.mpb` masks (reverse with row_items: of (mask, row)
-// items); `wpb` wavefronts per workgroup (forward: at most 16; reverse:
-// adj_waves_per_block())
-hipError_t launch_level(const LvlArgs &a, bool reverse, int nblocks, int ngroups, int wpb, hipStream_t s);
-int adj_waves_per_block();
+// unlabelled levels of orders n >= 2: forward with `wpb` wavefronts per
+// workgroup (at most 16), reverse with kAdjWaves
+hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s);
+hipError_t launch_level_adj(LvlArgs a, int ngroups, hipStream_t s);
+// order 1, every group (forward; with a.Gbar_T also the gradients)
+hipError_t launch_order1(const LvlArgs &a, int ngroups, hipStream_t s);
+// wavefronts per workgroup of the reverse sweeps
+constexpr int kAdjWaves = 8, kSubAdjWaves = 16;
+// most masks of a split forward block, and of a reverse block with row_items
+constexpr int kSplitMasks = 8, kAdjListMasks = 64;
+size_t fwd_lds_bytes(int n, int split_masks, int nspecial);
 // deterministic reverse sweep: every level's masks in kDetParts fixed parts;
 // Gbar_T / sbar_T of the LvlArgs point to the partial sums
-// [part][group][flavour][v][w][64] and [part][group][flavour][v][64]
+// [part][group][flavour][v][w][64] and [part][group][flavour][64]
 constexpr int kDetParts = 32;
 hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s);
-// GbT = sum of the gsize-element parts in order; sbT (ssize elements,
-// [group][flavour][64]) = sum over parts and slots v < n
-hipError_t launch_det_reduce(const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize, int n,
-                             double *GbT, double *sbT, hipStream_t s);
-// most masks per wavefront of the forward kernel when there are several flavours
+// GbT and sbT = the sums of the parts (gsize and ssize elements each) in order
+hipError_t launch_det_reduce(const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize, double *GbT,
+                             double *sbT, hipStream_t s);
+// most masks per wavefront of the labelled forward kernel when there are several flavours
 constexpr int kMultiMasks = 4;
 // launchers (cos_kernels.hip)
 hipError_t launch_g0(int nconf, const int32_t *n, const int64_t *voff, const int32_t *sites,
@@ -196,16 +213,17 @@ hipError_t launch_iota(int32_t *p, int n, hipStream_t s);
 cos_status report(cos_status s, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 // gfx950 check and compute-unit count of the current device
 cos_status current_device(int *dev, int *ncu);
-// host state tables of order n (built once, cached for the process)
+// host state tables of order n (built once, cached for the process): the plain
+// ones, or the level kernels' (`tiles`)
 struct PlanTables {
     const int32_t *mrec;      // [masks][kRecInts]
     size_t mrec_ints;
-    const int4 *levels;       // [2n + 2]
+    const int4 *levels;
     size_t nlevels;
     int32_t max_rows, max_masks;
     int64_t total_rows;
 };
-cos_status plan_tables(int n, PlanTables *out);
+cos_status plan_tables(int n, bool tiles, PlanTables *out);
 // workspace of one forward call: every pointer inside device memory the
 // caller owns; the level windows hold `chunk` groups of 64 configurations
 struct FixedWorkspace {

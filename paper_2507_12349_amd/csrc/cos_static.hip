@@ -53,7 +53,7 @@ cos_status setup_device(int dev, StaticDevice *sd) {
     size_t off = 0;
     for (int n = 1; n <= COS_STATIC_NMAX; ++n) {
         PlanTables t;
-        if (cos_status st = plan_tables(n, &t)) return st;
+        if (cos_status st = plan_tables(n, true, &t)) return st;
         const size_t mb = t.mrec_ints * sizeof(int32_t), lb = t.nlevels * sizeof(int4);
         if (off + up256(mb) + up256(lb) > (size_t)COS_STATIC_SCRATCH_BYTES)
             return report(COS_ENOMEM, "the state tables do not fit the static scratch");

@@ -462,7 +462,7 @@ hipError_t launch_sub_level(const LvlArgs &a, int nblocks, int ngroups, int wpb,
 
 hipError_t launch_sub_adj_level(const LvlArgs &a, int nblocks, int ngroups, hipStream_t s) {
     const int n = a.plan.n;
-    const int wpa = adj_waves_per_block();
+    const int wpa = kSubAdjWaves;
     const size_t side = 2 * (size_t)n, mat = side * side * 64 * sizeof(double);
     const bool split = 2 * mat > 160 * 1024;   // as SubAdjShape: two workgroups per block of masks
     const size_t shm = split ? mat : 2 * mat;   // owned rows of G and of the accumulator

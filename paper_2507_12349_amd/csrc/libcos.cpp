@@ -66,12 +66,16 @@ hipError_t dev_malloc(void **p, size_t bytes) {
     return hipMalloc(p, bytes);
 }
 
-// a kernel launch of the library; an injected failure skips the launch
-#define LAUNCH_TRY(expr)                                                                       \
+// a kernel launch of the library that does `steps` steps (levels of the
+// dynamic programme); an injected failure of one of them skips the launch
+#define LAUNCH_STEPS(steps, expr)                                                              \
     do {                                                                                       \
-        if (injected(1)) return fail(COS_EDEVICE, "%s failed: injected launch failure", #expr); \
+        bool bad_ = false;                                                                     \
+        for (int i_ = 0; i_ < (steps) && !bad_; ++i_) bad_ = injected(1);                      \
+        if (bad_) return fail(COS_EDEVICE, "%s failed: injected launch failure", #expr);       \
         HIP_TRY(expr);                                                                         \
     } while (0)
+#define LAUNCH_TRY(expr) LAUNCH_STEPS(1, expr)
 
 // ---------------------------------------------------------------------------
 // Host plan: the state tables for one order n (identical for every
@@ -84,9 +88,12 @@ struct HostPlan {
     std::vector<uint32_t> minfo;    // [3^n]
     std::vector<int2> rows;
     std::vector<int32_t> masks;
-    std::vector<int4> levels;       // [2n + 2]
+    std::vector<int4> levels;       // [nlev + 2]
     std::vector<int32_t> mrec;      // [masks][rec_ints]
-    bool sub = false;               // sublattice-labelled state space
+    std::vector<int32_t> special;   // level kernels' tables: special masks per level (the last ones of it)
+    int nlev = 0;                   // levels (launches of a sweep)
+    int slots = 0;                  // slots per row
+    int64_t total_rows = 0;
     int rec_ints = kRecInts;
     int32_t max_rows = 0, max_masks = 0;
     int64_t states = 0, ext = 0, closes = 0, shift_edges = 0;
@@ -94,7 +101,8 @@ struct HostPlan {
 
 void build_host_plan(int n, HostPlan &P) {
     const int N3 = pow3(n);
-    P.n = n;
+    P.n = P.slots = n;
+    P.nlev = 2 * n;
     P.rowbase.assign(N3, -1);
     P.minfo.assign(N3, 0);
     std::vector<std::vector<int32_t>> bylevel(2 * n + 2);
@@ -149,6 +157,7 @@ void build_host_plan(int n, HostPlan &P) {
         P.max_masks = std::max(P.max_masks, mi);
     }
     P.closes = P.states;
+    P.total_rows = (int64_t)P.rows.size();
     P.levels[2 * n + 1] = make_int4((int)P.rows.size(), 0, (int)P.masks.size(), 0);
     P.mrec.assign(P.masks.size() * kRecInts, -1);
     for (size_t i = 0; i < P.masks.size(); ++i) {
@@ -164,10 +173,75 @@ void build_host_plan(int n, HostPlan &P) {
     }
 }
 
+// The level kernels' tables (tiles of three rows over the first n - 1 vertices;
+// see cos_internal.hpp and cos_level.hip).  Order 1 has no levels (it runs in
+// closed form) and keeps one row, so that its workspaces are not empty.
+void build_host_plan_tiles(int n, HostPlan &P) {
+    const int nb = n - 1, N3 = pow3(nb);
+    P.n = n;
+    P.slots = std::max(nb, 1);
+    P.nlev = 2 * nb;
+    P.levels.assign(P.nlev + 2, make_int4(0, 0, 0, 0));
+    P.special.assign(P.nlev + 2, 0);
+    if (nb == 0) {
+        P.max_rows = 1;
+        P.total_rows = 1;
+        return;
+    }
+    P.rowbase.assign(N3, -1);
+    P.minfo.assign(N3, 0);
+    std::vector<std::vector<int32_t>> plain(P.nlev + 2), special(P.nlev + 2);
+    for (int code = 0; code < N3; ++code) {
+        uint32_t ones = 0, twos = 0;
+        int c = code, lvl = 0;
+        for (int k = 0; k < nb; ++k) {
+            const int d = c % 3;
+            c /= 3;
+            if (d == 1) ones |= 1u << k;
+            if (d == 2) twos |= 1u << k;
+            lvl += d;
+        }
+        P.minfo[code] = ones | (twos << 16);
+        if (!((ones | twos) & 1u)) continue;   // vertex 0 is always visited
+        ((twos & 1u) && !ones ? special : plain)[lvl].push_back(code);
+    }
+    for (int l = 1; l <= P.nlev; ++l) {
+        int r = 0;
+        const int mask0 = (int)P.masks.size();
+        for (auto *list : {&plain[l], &special[l]})
+            for (int code : *list) {
+                const uint32_t twos = P.minfo[code] >> 16;
+                P.rowbase[code] = r;
+                P.masks.push_back(code);
+                // three rows per head, and the one row of head n - 1 once vertex 0 is full
+                r += (twos & 1u) ? 3 * (1 + __builtin_popcount(twos & ~1u)) + 1 : 3;
+            }
+        const int nm = (int)P.masks.size() - mask0;
+        P.levels[l] = make_int4((int)P.total_rows, r, mask0, nm);
+        P.special[l] = (int32_t)special[l].size();
+        P.total_rows += r;
+        P.max_rows = std::max(P.max_rows, r);
+        P.max_masks = std::max(P.max_masks, nm);
+    }
+    P.levels[P.nlev + 1] = make_int4((int)P.total_rows, 0, (int)P.masks.size(), 0);
+    P.mrec.assign(P.masks.size() * kRecInts, 0);
+    const uint32_t row_bytes = (uint32_t)nb * 512u;   // 832 MB per level and flavour at n = 12
+    for (size_t i = 0; i < P.masks.size(); ++i) {
+        const int code = P.masks[i];
+        const uint32_t twos = P.minfo[code] >> 16;
+        int32_t *r = &P.mrec[i * kRecInts];
+        r[0] = (int32_t)P.minfo[code];
+        r[1] = (int32_t)((uint32_t)P.rowbase[code] * row_bytes);
+        for (int w = 0; w < nb; ++w)
+            if (!((twos >> w) & 1u)) r[2 + w] = (int32_t)((uint32_t)P.rowbase[code + pow3(w)] * row_bytes);
+    }
+}
+
 // The sublattice-labelled plan (mask digits base 4; see cos_internal.hpp).
 void build_host_plan_sub(int n, HostPlan &P) {
     P.n = n;
-    P.sub = true;
+    P.slots = 2 * n;
+    P.nlev = 2 * n;
     P.rec_ints = kSubRecInts;
     int N4 = 1;
     for (int k = 0; k < n; ++k) N4 *= 4;
@@ -232,6 +306,7 @@ void build_host_plan_sub(int n, HostPlan &P) {
         P.max_masks = std::max(P.max_masks, mi);
     }
     P.closes = P.states;
+    P.total_rows = (int64_t)P.rows.size();
     P.levels[2 * n + 1] = make_int4((int)P.rows.size(), 0, (int)P.masks.size(), 0);
     P.mrec.assign(P.masks.size() * kSubRecInts, -1);
     int p4[kSubNmax + 1];
@@ -262,16 +337,19 @@ struct DevTables {
 };
 
 std::mutex g_mu;
-std::map<std::pair<int, int>, std::shared_ptr<HostPlan>> g_host;   // (n, sublattice)
-std::map<std::tuple<int, int, int>, DevTables> g_dev;              // (device, n, sublattice)
+// the plain state tables (counts), the labelled ones, the level kernels' tiles
+enum PlanKind { kPlain = 0, kSub = 1, kTiles = 2 };
+std::map<std::pair<int, int>, std::shared_ptr<HostPlan>> g_host;   // (n, kind)
+std::map<std::tuple<int, int, int>, DevTables> g_dev;              // (device, n, kind)
 int64_t g_live = 0;   // batch handles alive: they hold pointers into g_dev's tables
 
-std::shared_ptr<HostPlan> host_plan(int n, bool sub = false) {
-    auto key = std::make_pair(n, sub ? 1 : 0);
+std::shared_ptr<HostPlan> host_plan(int n, PlanKind kind) {
+    auto key = std::make_pair(n, (int)kind);
     auto it = g_host.find(key);
     if (it != g_host.end()) return it->second;
     auto p = std::make_shared<HostPlan>();
-    if (sub) build_host_plan_sub(n, *p);
+    if (kind == kSub) build_host_plan_sub(n, *p);
+    else if (kind == kTiles) build_host_plan_tiles(n, *p);
     else build_host_plan(n, *p);
     g_host[key] = p;
     return p;
@@ -312,15 +390,15 @@ cos_status alloc_chunked(double **out, std::vector<int> &chunks, const std::vect
     }
 }
 
-cos_status device_plan(int dev, int n, bool sub, DevPlan *out) {
+cos_status device_plan(int dev, int n, PlanKind kind, DevPlan *out) {
     std::lock_guard<std::mutex> lk(g_mu);
-    auto key = std::make_tuple(dev, n, sub ? 1 : 0);
+    auto key = std::make_tuple(dev, n, (int)kind);
     auto it = g_dev.find(key);
     if (it != g_dev.end()) {
         *out = it->second.dp;
         return COS_OK;
     }
-    auto hp = host_plan(n, sub);
+    auto hp = host_plan(n, kind);
     const size_t s1 = align_up(hp->mrec.size() * 4), s2 = align_up(hp->levels.size() * sizeof(int4));
     char *mem = nullptr;
     if (dev_malloc((void **)&mem, s1 + s2) != hipSuccess)
@@ -338,7 +416,7 @@ cos_status device_plan(int dev, int n, bool sub, DevPlan *out) {
     t.dp.n = n;
     t.dp.max_rows = hp->max_rows;
     t.dp.max_masks = hp->max_masks;
-    t.dp.total_rows = (int64_t)hp->rows.size();
+    t.dp.total_rows = hp->total_rows;
     g_dev[key] = t;
     *out = t.dp;
     return COS_OK;
@@ -407,7 +485,8 @@ struct OrderGroup {
     bool sub = false;                  // sublattice-labelled states (2n slots per row)
     bool side = false;                 // forward on the batch's side stream, in the side windows
     std::shared_ptr<HostPlan> hp;
-    int slots() const { return sub ? 2 * n : n; }
+    int mat_side() const { return sub ? 2 * n : n; }     // of a matrix
+    int slots() const { return hp->slots; }          // per row of states
 };
 
 struct cos_batch_s {
@@ -487,7 +566,7 @@ cos_status cos_plan_counts(int32_t n, int64_t *states, int64_t *extensions, int6
     std::shared_ptr<HostPlan> p;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        p = host_plan(n);
+        p = host_plan(n, kPlain);
     }
     if (states) *states = p->states;
     if (extensions) *extensions = p->ext;
@@ -505,7 +584,7 @@ cos_status cos_plan_counts_sublattice(int32_t n, int64_t *states, int64_t *exten
     std::shared_ptr<HostPlan> p;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        p = host_plan(n, true);
+        p = host_plan(n, kSub);
     }
     if (states) *states = p->states;
     if (extensions) *extensions = p->ext;
@@ -608,7 +687,7 @@ cos_status cos_batch_create(int32_t nconf, const int32_t *n, int32_t nflav, int3
     for (int c = 0; c < nconf; ++c) seen[n[c]] = true;
     for (int k = 1; k <= COS_NMAX; ++k)
         if (seen[k]) {
-            if ((st = device_plan(dev, k, sub, &b->plans[k]))) return st;
+            if ((st = device_plan(dev, k, sub ? kSub : kTiles, &b->plans[k]))) return st;
         }
     b->uniform_n = std::all_of(n, n + nconf, [&](int32_t x) { return x == n[0]; });
 
@@ -632,9 +711,9 @@ cos_status cos_batch_create(int32_t nconf, const int32_t *n, int32_t nflav, int3
         if (sub) o.shape.fwd_wpb = 16;   // (2n)^2 matrices in LDS: one workgroup per CU, make it wide
         {
             std::lock_guard<std::mutex> lk(g_mu);
-            o.hp = host_plan(o.n, sub);
+            o.hp = host_plan(o.n, sub ? kSub : kTiles);
         }
-        gt += (int64_t)o.ngroups * b->nfs * o.slots() * o.slots() * 64;
+        gt += (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
         sg += (int64_t)o.ngroups * b->nfs * 64;
         ln += (int64_t)o.ngroups * 64;
         b->orders.push_back(o);
@@ -759,7 +838,7 @@ static PackArgs pack_args(cos_batch_t b, const OrderGroup &o, const double *d_G,
     p.GT = b->d_GT + o.gt_off;
     p.sigT = b->d_sigT + o.sig_off;
     p.lane_cfg = b->d_lane + o.lane_off;
-    p.n = o.slots();   // matrix side: n, or 2n with sublattice labels
+    p.n = o.mat_side();    // n, or 2n with sublattice labels
     p.nfs = b->nfs;
     p.nmat = b->nmat;
     p.nstub = b->nstub;
@@ -786,9 +865,15 @@ static LvlArgs level_args(cos_batch_t b, const OrderGroup &o, double cycle_weigh
 // masks per wavefront of a forward level launch with `nm` masks and `ng`
 // groups: up to the shape's cap (to amortise loading G into LDS), fewer when
 // the level is small so that its rows spread over enough wavefronts
-static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu) {
-    int cap = sh.fwd_cap ? sh.fwd_cap : (nfs <= 1 ? 8 : kMultiMasks);
-    if (nfs > 1) cap = std::min(cap, kMultiMasks);   // close sums of several flavours in registers
+static int fwd_cap(const LaunchShape &sh, int nfs, bool sub) {
+    // unlabelled: 2 (n = 10, 2048 configurations: 3.58 ms at 1 or 2, 3.67 at 4,
+    // 3.84 at 8: small blocks keep the masks in work close together in memory)
+    if (!sub) return sh.fwd_cap ? sh.fwd_cap : 2;
+    const int cap = sh.fwd_cap ? sh.fwd_cap : (nfs <= 1 ? 8 : kMultiMasks);
+    return nfs > 1 ? std::min(cap, kMultiMasks) : cap;   // close sums of several flavours in registers
+}
+static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu, bool sub) {
+    const int cap = fwd_cap(sh, nfs, sub);
     const int64_t per = ((int64_t)nm * ng) / std::max<int64_t>(1, (int64_t)ncu * 16);
     return (int)std::max<int64_t>(1, std::min<int64_t>(cap, per));
 }
@@ -799,11 +884,76 @@ static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu) {
 // share the block's masks dynamically, so workgroups take equal time, and the
 // level is cut into as few rounds of one workgroup per CU as the cap allows,
 // with the masks spread evenly over them
-static int adj_masks(const LaunchShape &sh, int nm, int ng, int ncu) {
-    const int64_t slots = (int64_t)std::max(1, ncu) * 16;                 // wavefronts of one round (16 per CU)
+static int adj_masks(const LaunchShape &sh, int nm, int ng, int ncu, int per_cu) {
+    const int64_t slots = (int64_t)std::max(1, ncu) * per_cu;             // wavefronts of one round
     const int64_t work = (int64_t)nm * ng;
     const int64_t rounds = std::max<int64_t>(1, (work + slots * sh.adj_cap - 1) / (slots * sh.adj_cap));
     return (int)std::max<int64_t>(1, std::min<int64_t>(sh.adj_cap, (work + slots * rounds - 1) / (slots * rounds)));
+}
+
+// wavefronts of the reverse that a CU holds: workgroups of kAdjWaves as their
+// LDS (G and the dS/dG accumulator) and registers (at most 16 wavefronts of up
+// to 128 each fit) allow; the labelled reverse always has 16
+static int adj_waves_per_cu(const OrderGroup &o) {
+    if (o.sub) return kSubAdjWaves;
+    return 2 * o.n * o.n * 512 * 2 <= 160 * 1024 ? 2 * kAdjWaves : kAdjWaves;
+}
+
+// rows of levels a..c (inclusive) of a plan
+static int64_t level_rows(const HostPlan &p, int a, int c) { return (int64_t)p.levels[c + 1].x - p.levels[a].x; }
+
+// the masks of an unlabelled level
+static void level_masks(const OrderGroup &o, int l, LvlArgs *a) {
+    a->mask0 = o.hp->levels[l].z;
+    a->nspecial = o.hp->special[l];
+    a->nmasks = o.hp->levels[l].w - a->nspecial;
+}
+
+// steps of the dynamic programme that the launch of level l does: a labelled
+// level is one; of the unlabelled ones the last counts the two visits of the
+// vertex that the tiles keep out of the levels
+static int level_steps(const OrderGroup &o, int l) { return !o.sub && l == o.hp->nlev ? 3 : 1; }
+
+// one forward level of `cg` groups, its masks filled in here
+static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, int l, int cg, hipStream_t s) {
+    a.level = l;
+    if (o.sub) {
+        const int nm = o.hp->levels[l].w;
+        a.mpb = fwd_masks(o.shape, b->nfs, nm, cg, b->ncu, true);
+        LAUNCH_TRY(launch_sub_level(a, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
+        return COS_OK;
+    }
+    level_masks(o, l, &a);
+    const int wpb = o.shape.fwd_wpb;
+    // the heads of a mask go to different wavefronts on the upper levels (at
+    // least n / 3 heads a mask on average), while the masks are fewer than half
+    // the wavefronts that fit the chip: at n = 10, 2048 configurations, the last
+    // two levels with masks of this kind took 28 + 18 us and take 13 + 8; with
+    // three flavours 79 + 46 and 29 + 20.  On the lower levels, and with more
+    // masks than that, loading G for fewer masks costs more than it gains (n = 10,
+    // three flavours, level 4: 54 -> 107 us)
+    const int heads = (int)std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)o.hp->levels[l].w));
+    a.split = a.nmasks > 0 && 3 * heads >= o.n && (int64_t)a.nmasks * cg <= (int64_t)b->ncu * 8;
+    if (a.split) {
+        // about one head per wavefront of a workgroup, in 80 KB of LDS so that
+        // two workgroups fit a CU
+        a.mpb = std::max(1, std::min({kSplitMasks, (wpb + heads - 1) / heads, a.nmasks}));
+        while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb, a.nspecial) > 80 * 1024) --a.mpb;
+        a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
+    } else {
+        a.mpb = fwd_masks(o.shape, b->nfs, a.nmasks, cg, b->ncu, false);
+        a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
+    }
+    if (a.nblocks && a.nspecial && 2 * fwd_lds_bytes(o.n, 0, 0) <= 160 * 1024 &&
+        2 * fwd_lds_bytes(o.n, a.split ? a.mpb : 0, a.nspecial) > 160 * 1024) {
+        // n = 12: the special masks' close sums would leave one workgroup per CU
+        LvlArgs p = a;
+        p.nspecial = 0;
+        HIP_TRY(launch_level_fwd(p, cg, wpb, s));
+        a.nblocks = a.split = 0;
+    }
+    LAUNCH_STEPS(level_steps(o, l), launch_level_fwd(a, cg, wpb, s));
+    return COS_OK;
 }
 
 // forward levels of one order, all groups, chunk by chunk (two level windows:
@@ -814,25 +964,27 @@ static cos_status forward_order(cos_batch_t b, const OrderGroup &o, const double
     if (mark) HIP_TRY(tmark(b, COS_PHASE_PACK, s));
     LAUNCH_TRY(launch_pack(pack_args(b, o, d_G, d_Goff, d_stub), s));
     if (mark) HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
+    if (o.hp->nlev == 0) {   // order 1: closed form
+        LvlArgs a = level_args(b, o, cycle_weight);
+        a.out = d_out;
+        LAUNCH_STEPS(2, launch_order1(a, o.ngroups, s));
+        return COS_OK;
+    }
     const int64_t rs = (int64_t)b->nfs * o.slots() * 64;
     const int64_t gstride = (int64_t)o.hp->max_rows * rs;
     double *const base = o.side ? b->d_win2 : b->d_win;
     for (int c0 = 0; c0 < o.ngroups; c0 += o.chunk_fwd) {
         const int cg = std::min(o.chunk_fwd, o.ngroups - c0);
         double *win0 = base, *win1 = base + gstride * cg;
-        for (int l = 1; l <= 2 * o.n; ++l) {
+        for (int l = 1; l <= o.hp->nlev; ++l) {
             LvlArgs a = level_args(b, o, cycle_weight);
-            a.level = l;
             a.group0 = c0;
             a.cur = (l & 1) ? win1 : win0;
             a.nxt = (l & 1) ? win0 : win1;
             a.cur_gstride = a.nxt_gstride = gstride;
             a.cur_frows = a.nxt_frows = o.hp->max_rows;
-            const int nm = o.hp->levels[l].w;
-            a.mpb = fwd_masks(o.shape, b->nfs, nm, cg, b->ncu);
             a.out = d_out;
-            if (o.sub) LAUNCH_TRY(launch_sub_level(a, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
-            else LAUNCH_TRY(launch_level(a, false, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
+            if (cos_status st = forward_level(b, o, a, l, cg, s)) return st;
         }
     }
     return COS_OK;
@@ -870,24 +1022,25 @@ cos_status cos_connected_sum_batched(cos_batch_t b, const double *d_G, const int
     return COS_OK;
 }
 
-// rows of levels a..c (inclusive) of a plan
-static int64_t level_rows(const HostPlan &p, int a, int c) { return (int64_t)p.levels[c + 1].x - p.levels[a].x; }
-
 // the split level h of a two-segment reverse sweep that minimises the larger
 // segment (levels 1..h, recomputed, or h+1..2n, stored by the first forward)
-static int best_split(const HostPlan &p, int n) {
+// (a level with special masks cannot be h: their head-b rows get the value
+// their cycle opens with when their own level is processed, and level h is not
+// processed again)
+static int best_split(const HostPlan &p) {
     int best = 0;
     int64_t bv = INT64_MAX;
-    for (int h = 1; h < 2 * n; ++h) {
-        const int64_t v = std::max(level_rows(p, 1, h), level_rows(p, h + 1, 2 * n));
+    for (int h = 1; h < p.nlev; ++h) {
+        if (!p.special.empty() && p.special[h]) continue;
+        const int64_t v = std::max(level_rows(p, 1, h), level_rows(p, h + 1, p.nlev));
         if (v < bv) bv = v, best = h;
     }
     return best;
 }
 
 // forward-state rows the reverse sweep of one group keeps
-static int64_t adj_store_rows(const HostPlan &p, int n, int h) {
-    return h ? std::max(level_rows(p, 1, h), level_rows(p, h + 1, 2 * n)) : (int64_t)p.rows.size();
+static int64_t adj_store_rows(const HostPlan &p, int h) {
+    return h ? std::max(level_rows(p, 1, h), level_rows(p, h + 1, p.nlev)) : p.total_rows;
 }
 
 static cos_status prepare_adjoint(cos_batch_t b) {
@@ -897,9 +1050,9 @@ static cos_status prepare_adjoint(cos_batch_t b) {
         o.gb_off = gb;
         o.sb_off = sb;
         o.sp_off = sp;
-        gb += (int64_t)o.ngroups * b->nfs * o.slots() * o.slots() * 64;
+        gb += (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
         sb += (int64_t)o.ngroups * b->nfs * 64;
-        sp += (int64_t)kDetParts * o.ngroups * b->nfs * o.slots() * 64;
+        sp += (int64_t)kDetParts * o.ngroups * b->nfs * 64;
     }
     const bool det = (b->flags & COS_F_DETERMINISTIC) != 0;
     if (dev_malloc((void **)&b->d_GbT, sizeof(double) * gb) != hipSuccess ||
@@ -920,16 +1073,16 @@ static cos_status prepare_adjoint(cos_batch_t b) {
     // when asked for, or when storing every level would split the groups
     for (OrderGroup &o : b->orders) {
         const int64_t rs = (int64_t)b->nfs * o.slots() * 64;
-        const int64_t all = ((int64_t)o.hp->rows.size() + 2 * (int64_t)o.hp->max_rows) * rs;
+        const int64_t all = (o.hp->total_rows + 2 * (int64_t)o.hp->max_rows) * rs;
         const bool seg = o.n >= 3 && (b->adj_segments == 2 ||
                                       (b->adj_segments == 0 && cap / (8 * all) < o.ngroups));
-        o.adj_split = seg ? best_split(*o.hp, o.n) : 0;
+        o.adj_split = seg ? best_split(*o.hp) : 0;
     }
     std::vector<int> chunks(b->orders.size()), ng(b->orders.size());
     for (size_t i = 0; i < b->orders.size(); ++i) ng[i] = b->orders[i].ngroups;
     auto per_group = [&](size_t i) {
         const OrderGroup &o = b->orders[i];
-        return (adj_store_rows(*o.hp, o.n, o.adj_split) + 2 * (int64_t)o.hp->max_rows) * b->nfs * o.slots() * 64;
+        return (adj_store_rows(*o.hp, o.adj_split) + 2 * (int64_t)o.hp->max_rows) * b->nfs * o.slots() * 64;
     };
     auto total = [&]() {
         int64_t w = 0;
@@ -949,7 +1102,6 @@ static cos_status prepare_adjoint(cos_batch_t b) {
     return COS_OK;
 }
 
-// forward (every level kept) and reverse levels of one order
 // forward (levels kept) and reverse levels of one order.  Every forward level
 // is stored, or with a split level h only levels h+1..2n: their reverse runs
 // first, then levels 1..h are computed again into the same store and
@@ -961,12 +1113,12 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
     HIP_TRY(tmark(b, COS_PHASE_PACK, s));
     LAUNCH_TRY(launch_pack(pa, s));
     double *GbT = b->d_GbT + o.gb_off, *sbT = b->d_sbT + o.sb_off;
-    const int64_t ngb = (int64_t)o.ngroups * b->nfs * o.slots() * o.slots() * 64;
+    const int64_t ngb = (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
     const int64_t nsb = (int64_t)o.ngroups * b->nfs * 64;
     const bool det = (b->flags & COS_F_DETERMINISTIC) != 0;
     double *Gp = det ? b->d_Gpart + (int64_t)kDetParts * o.gb_off : nullptr;
     double *Sp = det ? b->d_Spart + o.sp_off : nullptr;
-    const int64_t nsp = (int64_t)kDetParts * o.ngroups * b->nfs * o.slots() * 64;
+    const int64_t nsp = (int64_t)kDetParts * nsb;
     if (det) {
         LAUNCH_TRY(launch_zero(Gp, (int64_t)kDetParts * ngb, s));
         LAUNCH_TRY(launch_zero(Sp, nsp, s));
@@ -974,9 +1126,22 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
         LAUNCH_TRY(launch_zero(GbT, ngb, s));
         LAUNCH_TRY(launch_zero(sbT, nsb, s));
     }
-    const int n2 = 2 * o.n, h = o.adj_split;
+    if (o.hp->nlev == 0) {   // order 1: closed form, forward and gradients in one launch
+        LvlArgs a = level_args(b, o, cycle_weight);
+        a.out = d_out;
+        a.out_bar = d_out_bar;
+        a.Gbar_T = GbT;
+        a.sbar_T = sbT;
+        HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
+        HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
+        LAUNCH_STEPS(4, launch_order1(a, o.ngroups, s));
+        HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
+        LAUNCH_TRY(launch_unpack(pa, GbT, sbT, d_G_bar, (b->flags & COS_F_STUBS) ? d_stub_bar : nullptr, s));
+        return COS_OK;
+    }
+    const int n2 = o.hp->nlev, h = o.adj_split;
     const int64_t rs = (int64_t)b->nfs * o.slots() * 64;
-    const int64_t srows = adj_store_rows(*o.hp, o.n, h), mrows = o.hp->max_rows;
+    const int64_t srows = adj_store_rows(*o.hp, h), mrows = o.hp->max_rows;
     const int64_t fstride = srows * rs, bstride = mrows * rs;
     // store row of level l: levels are stored from level 1 (all, or the lower
     // segment) or from level h + 1 (the upper segment)
@@ -991,7 +1156,6 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
         auto forward = [&](int from, int to, bool first_pass) -> cos_status {
             for (int l = from; l <= to; ++l) {
                 LvlArgs a = level_args(b, o, cycle_weight);
-                a.level = l;
                 a.group0 = c0;
                 const bool in_store = !first_pass || !h || l > h;      // level l
                 const bool out_store = !first_pass || !h || l + 1 > h; // level l + 1
@@ -1004,11 +1168,8 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 a.nxt_gstride = out_store ? fstride : bstride;
                 a.nxt_frows = out_store ? srows : mrows;
                 a.nxt_row0 = out_store ? (int32_t)srow(std::min(l + 1, n2 + 1), up) : 0;
-                const int nm = o.hp->levels[l].w;
-                a.mpb = fwd_masks(o.shape, b->nfs, nm, cg, b->ncu);
                 a.out = d_out;
-                if (o.sub) LAUNCH_TRY(launch_sub_level(a, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
-                else LAUNCH_TRY(launch_level(a, false, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
+                if (cos_status st = forward_level(b, o, a, l, cg, s)) return st;
             }
             return COS_OK;
         };
@@ -1025,30 +1186,46 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 a.F_gstride = fstride;
                 a.F_frows = srows;
                 a.F_row0 = (int32_t)srow(l, upper);
-                const int nm = o.hp->levels[l].w;
-                // a level whose masks fill at most half the wavefronts of one
-                // round (labelled: an eighth; its rows are split over two
-                // workgroups at n = 7, 8 and each row reloads its mask's close
-                // adjoints in every flavour), and whose masks hold at least
-                // half the most rows a mask can have (n, labelled 2n) on
-                // average (the upper levels), gives every row a wavefront of its own
-                const int64_t fill = o.sub ? 8 : 2;
-                a.row_items = ((int64_t)nm * cg * fill <= (int64_t)b->ncu * 16 &&
-                               2 * level_rows(*o.hp, l, l) >= (int64_t)nm * o.slots()) ? 1 : 0;
-                const int items = a.row_items ? nm * o.slots() : nm;
-                a.mpb = adj_masks(o.shape, items, cg, b->ncu);
+                const int nm = o.hp->levels[l].w, per_cu = adj_waves_per_cu(o);
                 a.out_bar = d_out_bar;
                 a.Gbar_T = GbT;
                 a.sbar_T = sbT;
+                if (o.sub) {
+                    // a level whose masks fill at most an eighth of one round
+                    // (its rows are split over two workgroups at n = 7, 8 and
+                    // each row reloads its mask's close adjoints in every
+                    // flavour), and whose masks hold at least half the most
+                    // rows a mask can have (2n) on average (the upper levels),
+                    // gives every row a wavefront of its own
+                    a.row_items = ((int64_t)nm * cg * 8 <= (int64_t)b->ncu * 16 &&
+                                   2 * level_rows(*o.hp, l, l) >= (int64_t)nm * o.slots()) ? 1 : 0;
+                    const int items = a.row_items ? nm * o.slots() : nm;
+                    a.mpb = adj_masks(o.shape, items, cg, b->ncu, per_cu);
+                    LAUNCH_TRY(launch_sub_adj_level(a, (items + a.mpb - 1) / a.mpb, cg, s));
+                    continue;
+                }
+                level_masks(o, l, &a);
                 if (det) {
                     a.Gbar_T = Gp;
                     a.sbar_T = Sp;
                     a.det_groups = o.ngroups;
-                    LAUNCH_TRY(launch_level_det(a, cg, s));
+                    LAUNCH_STEPS(level_steps(o, l), launch_level_det(a, cg, s));
                     continue;
                 }
-                if (o.sub) LAUNCH_TRY(launch_sub_adj_level(a, (items + a.mpb - 1) / a.mpb, cg, s));
-                else LAUNCH_TRY(launch_level(a, true, (items + a.mpb - 1) / a.mpb, cg, adj_waves_per_block(), s));
+                // a level with fewer masks than the wavefronts of one round
+                // spreads the heads of its masks over wavefronts, in blocks of
+                // about one (mask, head) item per wavefront (n = 8, 1000
+                // configurations: reverse levels 440 -> 385 us)
+                a.row_items = (int64_t)nm * cg <= (int64_t)b->ncu * per_cu ? 1 : 0;
+                if (a.row_items) {
+                    const int64_t tiles = std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)nm));
+                    a.mpb = (int)std::max<int64_t>(1, std::min<int64_t>(kAdjListMasks, (kAdjWaves + tiles - 1) / tiles));
+                    a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
+                } else {
+                    a.mpb = adj_masks(o.shape, a.nmasks, cg, b->ncu, per_cu);
+                    a.nblocks = (a.nmasks + kAdjWaves * a.mpb - 1) / (kAdjWaves * a.mpb);
+                }
+                LAUNCH_STEPS(level_steps(o, l), launch_level_adj(a, cg, s));
             }
             return COS_OK;
         };
@@ -1066,7 +1243,7 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
     }
     HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
     if (det)
-        LAUNCH_TRY(launch_det_reduce(Gp, (b->flags & COS_F_STUBS) ? Sp : nullptr, ngb, nsb, o.slots(), GbT, sbT, s));
+        LAUNCH_TRY(launch_det_reduce(Gp, (b->flags & COS_F_STUBS) ? Sp : nullptr, ngb, nsb, GbT, sbT, s));
     LAUNCH_TRY(launch_unpack(pa, GbT, sbT, d_G_bar, (b->flags & COS_F_STUBS) ? d_stub_bar : nullptr, s));
     return COS_OK;
 }
@@ -1185,9 +1362,7 @@ cos_status cos_batch_launch_shape(cos_batch_t b, int32_t n, int32_t *fwd_waves, 
     for (const OrderGroup &o : b->orders)
         if (o.n == n) {
             *fwd_waves = o.shape.fwd_wpb;
-            int cap = o.shape.fwd_cap ? o.shape.fwd_cap : (b->nfs <= 1 ? 8 : kMultiMasks);
-            if (b->nfs > 1) cap = std::min(cap, kMultiMasks);
-            *fwd_masks_cap = cap;
+            *fwd_masks_cap = fwd_cap(o.shape, b->nfs, o.sub);
             *adj_masks_cap = o.shape.adj_cap;
             return COS_OK;
         }
@@ -1452,7 +1627,7 @@ cos_status cos_batch_adjoint_plan(cos_batch_t b, int32_t n, int32_t *split_level
             if (split_level) *split_level = o.adj_split;
             if (groups_per_chunk) *groups_per_chunk = o.chunk_adj;
             if (bytes_per_group)
-                *bytes_per_group = 8 * (adj_store_rows(*o.hp, o.n, o.adj_split) + 2 * (int64_t)o.hp->max_rows) *
+                *bytes_per_group = 8 * (adj_store_rows(*o.hp, o.adj_split) + 2 * (int64_t)o.hp->max_rows) *
                                    b->nfs * o.slots() * 64;
             return COS_OK;
         }
@@ -1508,12 +1683,12 @@ cos_status libcos::report(cos_status s, const char *fmt, ...) {
 
 cos_status libcos::current_device(int *dev, int *ncu) { return check_device(dev, ncu); }
 
-cos_status libcos::plan_tables(int n, PlanTables *out) {
+cos_status libcos::plan_tables(int n, bool tiles, PlanTables *out) {
     if (n < 1 || n > COS_NMAX) return fail(COS_ERANGE, "n must be in [1, %d], got %d", COS_NMAX, n);
     std::shared_ptr<HostPlan> p;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        p = host_plan(n);
+        p = host_plan(n, tiles ? kTiles : kPlain);
     }
     // the plan stays in the process-wide cache, which only cos_release clears
     out->mrec = p->mrec.data();
@@ -1522,7 +1697,7 @@ cos_status libcos::plan_tables(int n, PlanTables *out) {
     out->nlevels = p->levels.size();
     out->max_rows = p->max_rows;
     out->max_masks = p->max_masks;
-    out->total_rows = (int64_t)p->rows.size();
+    out->total_rows = p->total_rows;
     return COS_OK;
 }
 
@@ -1533,7 +1708,7 @@ FixedSizes libcos::fixed_sizes(int nconf, int n, int nfs, int32_t max_rows) {
     z.gt_doubles = ngroups * nfs * n * n * 64;
     z.sig_doubles = ngroups * nfs * 64;
     z.lane_ints = ngroups * 64;
-    z.win_doubles_per_group = 2 * (int64_t)max_rows * nfs * n * 64;
+    z.win_doubles_per_group = 2 * (int64_t)max_rows * nfs * std::max(n - 1, 1) * 64;
     return z;
 }
 
@@ -1563,7 +1738,7 @@ cos_status libcos::forward_fixed(int dev, int ncu, const FixedWorkspace &ws, int
     o.chunk_fwd = std::max(1, std::min(ws.chunk, o.ngroups));
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        o.hp = host_plan(n);
+        o.hp = host_plan(n, kTiles);
     }
     LAUNCH_TRY(launch_iota(ws.order, nconf, s));
     return forward_order(&b, o, d_G, nullptr, d_stub, cycle_weight, d_out, s);
