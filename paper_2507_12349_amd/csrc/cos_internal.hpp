@@ -51,7 +51,20 @@ struct DevPlan {
     int32_t max_masks;        // largest #masks of a level
     int32_t pad;
     int64_t total_rows;
+    const int32_t *script;    // small orders: rounds and items of the one-launch sweeps, else null
 };
+
+// One-launch sweeps of small orders (cos_level.hip): tables of (mask, head)
+// items and of the rounds of the forward.  The script is
+//   [0] rounds R   [1] items I
+//   R records of kSmallRoundInts: level, first item, items, first close, closes,
+//     1 if it closes the full mask's head-b row
+//   I words: items (mask << 8 | head slot << 4 | head, kSmallBrow for a head-b
+//     row) and closes (mask << 8 | first item of the round << 4 | items)
+//   3 ints per level 0..2(n - 1): first item, items, head-b rows of special
+//     masks (they follow the items)
+constexpr int kSmallMax = 5, kSmallWaves = 16, kSmallItems = 16, kSmallBrow = 15;
+constexpr int kSmallHeader = 2, kSmallRoundInts = 6;
 
 __host__ __device__ inline constexpr int pow3(int k) { return k <= 0 ? 1 : 3 * pow3(k - 1); }
 
@@ -151,7 +164,26 @@ struct LvlArgs {
     double *Gbar_T, *sbar_T;  // reverse: packed gradient accumulators
 };
 
+// a one-launch sweep (forward; with G_bar forward and reverse)
+struct SmallArgs {
+    DevPlan plan;
+    const double *G;          // caller matrices, offsets (may be null), shift weights (null: none)
+    const int64_t *Goff;
+    const double *stub;
+    const int32_t *order;     // configurations of this order, in lane order
+    double *win;              // two level windows per group (reverse: of adjoints)
+    double *F;                // reverse: every forward level of each group
+    int64_t win_gstride, F_gstride;   // doubles per group
+    double W;
+    double *out;              // may be null in the reverse
+    const double *out_bar;
+    double *G_bar, *stub_bar; // caller layout
+    int32_t nfs, count, group0, mask_only;
+};
+
 // launchers (cos_level.hip)
+hipError_t launch_small(const SmallArgs &a, bool reverse, int ngroups, hipStream_t s);
+size_t small_lds_bytes(int n, int nfs, bool reverse);   // of a workgroup
 hipError_t launch_pack(const PackArgs &a, hipStream_t s);
 hipError_t launch_unpack(const PackArgs &a, const double *GbT, const double *sbT, double *Gb, double *sb,
                          hipStream_t s);
@@ -222,6 +254,8 @@ struct PlanTables {
     size_t nlevels;
     int32_t max_rows, max_masks;
     int64_t total_rows;
+    const int32_t *script;    // small orders, else empty
+    size_t script_ints;
 };
 cos_status plan_tables(int n, bool tiles, PlanTables *out);
 // workspace of one forward call: every pointer inside device memory the

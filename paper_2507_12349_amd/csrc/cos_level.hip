@@ -1230,4 +1230,266 @@ hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s) {
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// small orders (2 <= n <= kSmallMax): a whole sweep in one launch
+//
+// At these orders a level of one group is at most a few dozen tiles, a launch
+// per level costs more than the level's work (at n = 4 each launch ran 3-4 us
+// for well under 1 us of work), and one group's states (0.25 MB for two levels
+// at n = 5) stay in the caches.  So one workgroup of kSmallWaves wavefronts takes
+// one group of 64 configurations through every level, with barriers instead of
+// launches between them; it reads the caller's matrices and writes the
+// caller's gradients itself, so that the packing, zeroing and unpacking
+// launches go too.  G of every flavour stays in LDS, and in the reverse sweep
+// the dS/dG accumulators beside it.
+//
+// The heads of a mask run side by side on different wavefronts: the forward
+// works in rounds of at most kSmallItems (mask, head) items per flavour, whose
+// close sums wait in LDS; after a barrier one wavefront per mask adds them up
+// (heads in order, flavours in order, as the level kernels do, so that the sums
+// agree bit for bit) and opens the next cycle.  The rounds come from a table
+// made with the state tables (kSmallHeader and following).
+//
+// Measured, one flavour, 300 and 8192 configurations, against the level kernels:
+// forward n = 4 26 / 28 -> 16 / 17 us, n = 5 43 / 54 -> 34 / 36 us; with the
+// reverse n = 4 69 / 74 -> 32 / 34 us, n = 5 121 / 165 -> 79 / 95 us.  At n = 6
+// one CU per group is too little (65 -> 96 us at 300 configurations, with the
+// reverse 179 -> 334 us): the line lies at n = 5.
+// ---------------------------------------------------------------------------
+template <int N>
+struct SmallCtx {
+    const SmallArgs &A;
+    cint32 *script;
+    int nrounds, lane, wave, nfs, gl;
+    double *Gs, *Ts, *sig;   // LDS: G [nfs][N * N][64], close sums, shift weights [nfs][64]
+    int cfg;
+    uint32_t lane8;
+    uint32_t off[3];
+};
+
+// states of level l: all levels kept (reverse sweep) or two windows
+template <int N>
+__device__ __forceinline__ double *small_level(const SmallCtx<N> &C, bool keep, int l, int64_t *plane) {
+    constexpr int NB = N - 1;
+    if (keep) {
+        *plane = C.A.plan.total_rows * NB * 64;
+        const cint32 *p = (const cint32 *)(C.A.plan.levels + l);
+        return C.A.F + C.gl * C.A.F_gstride + (int64_t)p[0] * NB * 64;
+    }
+    *plane = (int64_t)C.A.plan.max_rows * NB * 64;
+    return C.A.win + C.gl * C.A.win_gstride + (l & 1) * (*plane) * C.nfs;
+}
+
+// the workgroup's G (and shift weights) into LDS, straight from the caller's
+// layout: the lanes of a wavefront read their own configurations' entries, and
+// the lines they touch are used up within 16 entries
+template <int N>
+__device__ __forceinline__ void small_stage(const SmallCtx<N> &C) {
+    const SmallArgs &A = C.A;
+    const int n2 = C.nfs * N * N;
+    const double *src = nullptr;
+    if (C.cfg >= 0) src = A.G + (A.Goff ? A.Goff[C.cfg] : (int64_t)C.cfg * n2);
+    const int wpb = blockDim.x >> 6;
+    for (int e = C.wave; e < n2; e += wpb) C.Gs[e * 64 + C.lane] = src ? src[e] : 0.0;
+    for (int l = C.wave; l < C.nfs; l += wpb)
+        C.sig[l * 64 + C.lane] = (src && A.stub) ? A.stub[(int64_t)C.cfg * C.nfs + l] : 0.0;
+}
+
+// every forward level; writes S
+template <int N, bool MASK>
+__device__ __forceinline__ void small_forward(const SmallCtx<N> &C, bool keep) {
+    constexpr int NB = N - 1;
+    const SmallArgs &A = C.A;
+    const int wpb = blockDim.x >> 6, nfs = C.nfs, lane = C.lane;
+    const cint32 *rounds = C.script + kSmallHeader, *items = rounds + C.nrounds * kSmallRoundInts;
+    double tfull = 0.0;   // close sum of the full mask (the wavefront that owns it)
+    for (int r = 0; r < C.nrounds; ++r) {
+        const cint32 *R = rounds + r * kSmallRoundInts;
+        const int level = R[0], item0 = R[1], ni = R[2], close0 = R[3], nc = R[4];
+        int64_t cpl, npl;
+        double *cur = small_level<N>(C, keep, level, &cpl), *nxt = small_level<N>(C, keep, level + 1, &npl);
+        const bool start = level == 1;
+        for (int q = C.wave; q < ni * nfs; q += wpb) {
+            const int lam = q / ni, i = q - lam * ni;
+            const uint32_t word = (uint32_t)items[item0 + i];
+            const int k = (word >> 4) & 15, u = word & 15;
+            const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
+            const plane_t curL = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
+            const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
+            const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
+            double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
+            if (u == kSmallBrow) {
+                const bool special = special_mask(M.ones, M.twos);
+                const double inj = special ? slot_ld(make_plane(cur), C.lane8, M.rb + k * kTileB<N>) : 0.0;
+                fwd_brow<N, MASK, false>(M, gaddr, curL, nxtL, C.lane8, k * kTileB<N>, inj, sg, T[2]);
+            } else if (!(MASK && empty_plane(u, lam, M.twos))) {
+                fwd_tile<N, MASK, false>(M, gaddr, curL, nxtL, C.off, u, k * kTileB<N>, start, sg, T, dext);
+            }
+            // m_0 = 1: vertex 0's second visit, on the slot the next cycle opens on
+            if (!MASK && !(M.twos & 1u)) {
+                const uint32_t dst = M.crb[0];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) slot_st(nxtL, C.off[j], dst, dext[j]);
+            }
+            double *t = C.Ts + (lam * kSmallItems + i) * 192 + lane;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) t[j * 64] = T[j];
+        }
+        __syncthreads();
+        // one wavefront per mask: t_m = W sum over heads and flavours
+        for (int c = C.wave; c < nc; c += wpb) {
+            const uint32_t word = (uint32_t)items[close0 + c];
+            const int first = (word >> 4) & 15, cnt = word & 15;
+            const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
+            const bool full = M.twos == (1u << NB) - 1u;
+            double T[3] = {0.0, 0.0, 0.0};
+            for (int lam = 0; lam < nfs; ++lam) {
+                double s[3] = {0.0, 0.0, 0.0};
+                for (int i = first; i < first + cnt; ++i) {
+                    const double *t = C.Ts + (lam * kSmallItems + i) * 192 + lane;
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) s[j] += t[j * 64];
+                }
+#pragma unroll
+                for (int j = 0; j < 3; ++j) T[j] += s[j];
+                if (R[5]) tfull += s[2];   // the full mask's head-b row, after its tiles
+            }
+            if (R[5]) continue;
+            if (special_mask(M.ones, M.twos)) {
+                const uint32_t brow = (1u + (uint32_t)__builtin_popcount(M.twos & ~1u)) * kTileB<N>;
+                slot_st(make_plane(cur), C.lane8, M.rb + brow, A.W * T[1]);
+                if (full) tfull = T[2];
+                continue;
+            }
+            const int h = __builtin_ctz(M.ones);
+            const uint32_t dst = child_rows<N>(M, h) + open_slot<N>(h, M.twos);
+            for (int k = 0; k < nfs; ++k) {
+                if (MASK && h == 0 && k == 0) continue;
+                const plane_t d = make_plane(nxt + k * npl);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const double x = (!MASK && h == 0) ? slot_ld(d, C.off[j], dst) : 0.0;
+                    slot_st(d, C.off[j], dst, __builtin_fma(A.W, T[j], x));
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // the last two rounds close the full mask, each with one mask: wavefront 0
+    if (C.wave == 0 && C.cfg >= 0 && A.out) A.out[C.cfg] = A.W * tfull;
+}
+
+template <int N>
+__device__ __forceinline__ SmallCtx<N> small_ctx(const SmallArgs &A, double *lds, uint32_t tail_doubles) {
+    const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6), g = A.group0 + (int)blockIdx.x;
+    cint32 *script = (cint32 *)A.plan.script;
+    const int slot = g * 64 + lane;
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    double *Ts = lds + (int64_t)A.nfs * N * N * 64;
+    return SmallCtx<N>{A,    script, (int)script[0], lane, wave, A.nfs, (int)blockIdx.x, lds, Ts, Ts + tail_doubles,
+                       slot < A.count ? A.order[slot] : -1, lane8, {lane8, lane8 + 512u, lane8 + 1024u}};
+}
+
+template <int N, bool MASK>
+__global__ void __launch_bounds__(64 * kSmallWaves) small_fwd_kernel(const SmallArgs A) {
+    extern __shared__ double lds[];
+    const SmallCtx<N> C = small_ctx<N>(A, lds, (uint32_t)A.nfs * kSmallItems * 192u);
+    small_stage<N>(C);
+    __syncthreads();
+    small_forward<N, MASK>(C, false);
+}
+
+// forward (every level kept) and reverse; writes S, dS/dG and dS/dsigma.  The
+// accumulators take the place of the forward's close sums in LDS.
+template <int N, bool MASK>
+__global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const SmallArgs A) {
+    constexpr int NB = N - 1;
+    extern __shared__ double lds[];
+    const uint32_t tail = (uint32_t)A.nfs * 64u * (N * N > 3 * kSmallItems ? N * N : 3 * kSmallItems);
+    const SmallCtx<N> C = small_ctx<N>(A, lds, tail);
+    const int wpb = blockDim.x >> 6, nfs = C.nfs, lane = C.lane;
+    double *Gb = C.Ts, *sb = C.sig + nfs * 64;
+    small_stage<N>(C);
+    __syncthreads();
+    small_forward<N, MASK>(C, true);
+    const int n2 = nfs * N * N;
+    for (int e = C.wave; e < n2; e += wpb) Gb[e * 64 + lane] = 0.0;
+    for (int l = C.wave; l < nfs; l += wpb) sb[l * 64 + lane] = 0.0;
+    __syncthreads();
+    const double obar = C.cfg >= 0 ? A.out_bar[C.cfg] : 0.0;
+    const cint32 *items = C.script + kSmallHeader + C.nrounds * kSmallRoundInts, *lev = items + C.script[1];
+    for (int l = 2 * NB; l >= 1; --l) {
+        int64_t fpl, cpl, npl;
+        const double *F = small_level<N>(C, true, l, &fpl);
+        const double *Bn = small_level<N>(C, false, l + 1, &cpl);
+        double *Bc = small_level<N>(C, false, l, &npl);
+        const int item0 = lev[3 * l], ni = lev[3 * l + 1], nsb = lev[3 * l + 2];
+        const bool start = l == 1;
+        // the special masks' head-b rows, then everything else
+        for (int part = nsb ? 0 : 1; part < 2; ++part) {
+            const int i0 = part ? item0 : item0 + ni, n = part ? ni : nsb;
+            for (int q = C.wave; q < n * nfs; q += wpb) {
+                const int lam = q / n;
+                const uint32_t word = (uint32_t)items[i0 + (q - lam * n)];
+                const int k = (word >> 4) & 15, u = word & 15;
+                const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
+                const plane_t FL = make_plane(F + lam * fpl), BnL = make_plane(Bn + lam * cpl),
+                              BcL = make_plane(Bc + lam * npl);
+                const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
+                const uint32_t gbaddr = lds_addr(Gb + lam * N * N * 64) + C.lane8;
+                const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
+                const uint32_t hb = k * kTileB<N>;
+                double sacc = 0.0;
+                if (part == 0) {
+                    const double fi = slot_ld(make_plane(F), C.lane8, M.rb + hb);
+                    const double bi = adj_brow<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.lane8, hb, fi,
+                                                        M.twos == (1u << NB) - 1u ? A.W * obar : 0.0, sg, sacc, {});
+                    slot_st(BcL, C.lane8, M.rb + hb, bi);
+                } else {
+                    double tb[3];
+                    close_adjoint<N, MASK>(M, Bn, Bc, cpl, npl, C.off, nfs, A.W, obar, tb);
+                    if (u == kSmallBrow)
+                        adj_brow<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.lane8, hb, 0.0, tb[2], sg, sacc, {});
+                    else if (!(MASK && empty_plane(u, lam, M.twos)))
+                        adj_tile<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.off, u, hb, start, tb, sg, sacc, {});
+                }
+                if (A.stub) atomicAdd(sb + lam * 64 + lane, sacc);
+            }
+            __syncthreads();
+        }
+    }
+    if (C.cfg < 0) return;
+    double *out = A.G_bar + (A.Goff ? A.Goff[C.cfg] : (int64_t)C.cfg * n2);
+    for (int e = C.wave; e < n2; e += wpb) out[e] = Gb[e * 64 + lane];
+    if (A.stub)
+        for (int l = C.wave; l < nfs; l += wpb) A.stub_bar[(int64_t)C.cfg * nfs + l] = sb[l * 64 + lane];
+}
+
+size_t small_lds_bytes(int n, int nfs, bool reverse) {
+    const size_t tail = reverse && n * n > 3 * kSmallItems ? (size_t)n * n : (size_t)3 * kSmallItems;
+    return (size_t)nfs * 512 * (n * n + tail + (reverse ? 2 : 1));
+}
+
+hipError_t launch_small(const SmallArgs &a, bool reverse, int ngroups, hipStream_t s) {
+    const size_t shm = small_lds_bytes(a.plan.n, a.nfs, reverse);
+    const dim3 grid((unsigned)ngroups), block(64 * kSmallWaves);
+    const void *fn = nullptr;
+    switch (a.plan.n) {
+#define COS_SMALL_CASE(K)                                                                            \
+    case K:                                                                                          \
+        fn = reverse ? (a.mask_only ? (const void *)small_adj_kernel<K, true>                        \
+                                    : (const void *)small_adj_kernel<K, false>)                      \
+                     : (a.mask_only ? (const void *)small_fwd_kernel<K, true>                        \
+                                    : (const void *)small_fwd_kernel<K, false>);                     \
+        break;
+        COS_SMALL_CASE(2) COS_SMALL_CASE(3) COS_SMALL_CASE(4) COS_SMALL_CASE(5)
+#undef COS_SMALL_CASE
+        default: return hipErrorInvalidValue;
+    }
+    hipError_t e = allow_lds(fn, shm);
+    if (e != hipSuccess) return e;
+    void *args[] = {(void *)&a};
+    return hipLaunchKernel(fn, grid, block, args, shm, s);
+}
+
 }  // namespace libcos

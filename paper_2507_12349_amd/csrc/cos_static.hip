@@ -55,10 +55,13 @@ cos_status setup_device(int dev, StaticDevice *sd) {
         PlanTables t;
         if (cos_status st = plan_tables(n, true, &t)) return st;
         const size_t mb = t.mrec_ints * sizeof(int32_t), lb = t.nlevels * sizeof(int4);
-        if (off + up256(mb) + up256(lb) > (size_t)COS_STATIC_SCRATCH_BYTES)
+        const size_t sb = t.script_ints * sizeof(int32_t);
+        if (off + up256(mb) + up256(lb) + up256(sb) > (size_t)COS_STATIC_SCRATCH_BYTES)
             return report(COS_ENOMEM, "the state tables do not fit the static scratch");
         e = hipMemcpy(base + off, t.mrec, mb, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(base + off + up256(mb), t.levels, lb, hipMemcpyHostToDevice);
+        if (e == hipSuccess && sb)
+            e = hipMemcpy(base + off + up256(mb) + up256(lb), t.script, sb, hipMemcpyHostToDevice);
         if (e != hipSuccess)
             return report(COS_EDEVICE, "upload of the state tables into the static scratch failed: %s",
                           hipGetErrorString(e));
@@ -69,7 +72,8 @@ cos_status setup_device(int dev, StaticDevice *sd) {
         p.max_rows = t.max_rows;
         p.max_masks = t.max_masks;
         p.total_rows = t.total_rows;
-        off += up256(mb) + up256(lb);
+        p.script = sb ? (const int32_t *)(base + off + up256(mb) + up256(lb)) : nullptr;
+        off += up256(mb) + up256(lb) + up256(sb);
     }
     sd->base = base;
     sd->ncu = ncu;

@@ -91,6 +91,7 @@ struct HostPlan {
     std::vector<int4> levels;       // [nlev + 2]
     std::vector<int32_t> mrec;      // [masks][rec_ints]
     std::vector<int32_t> special;   // level kernels' tables: special masks per level (the last ones of it)
+    std::vector<int32_t> script;    // small orders: the one-launch sweeps' table
     int nlev = 0;                   // levels (launches of a sweep)
     int slots = 0;                  // slots per row
     int64_t total_rows = 0;
@@ -173,6 +174,8 @@ void build_host_plan(int n, HostPlan &P) {
     }
 }
 
+void build_script(HostPlan &P);
+
 // The level kernels' tables (tiles of three rows over the first n - 1 vertices;
 // see cos_internal.hpp and cos_level.hip).  Order 1 has no levels (it runs in
 // closed form) and keeps one row, so that its workspaces are not empty.
@@ -235,6 +238,60 @@ void build_host_plan_tiles(int n, HostPlan &P) {
         for (int w = 0; w < nb; ++w)
             if (!((twos >> w) & 1u)) r[2 + w] = (int32_t)((uint32_t)P.rowbase[code + pow3(w)] * row_bytes);
     }
+    if (n <= kSmallMax) build_script(P);
+}
+
+// The table of the one-launch sweeps (see cos_internal.hpp).
+void build_script(HostPlan &P) {
+    const int nb = P.n - 1;
+    std::vector<int32_t> rounds, words, levels(3 * (P.nlev + 1), 0);
+    for (int l = 1; l <= P.nlev; ++l) {
+        const int m0 = P.levels[l].z, nm = P.levels[l].w, nsp = P.special[l];
+        struct Close { int mask, items; };
+        std::vector<int32_t> items, brows;
+        std::vector<Close> closes;
+        for (int i = 0; i < nm; ++i) {
+            const uint32_t twos = P.minfo[P.masks[m0 + i]] >> 16;
+            const uint32_t heads = (twos & 1u) ? (twos & ~1u) : 0u;
+            const size_t before = items.size();
+            int k = 0;
+            items.push_back((m0 + i) << 8 | k++ << 4);
+            for (int h = 1; h < nb; ++h)
+                if ((heads >> h) & 1u) items.push_back((m0 + i) << 8 | k++ << 4 | h);
+            if (twos & 1u) (i < nm - nsp ? items : brows).push_back((m0 + i) << 8 | k << 4 | kSmallBrow);
+            closes.push_back({m0 + i, (int)(items.size() - before)});
+        }
+        const int item0 = (int)words.size();
+        words.insert(words.end(), items.begin(), items.end());
+        words.insert(words.end(), brows.begin(), brows.end());
+        levels[3 * l] = item0;
+        levels[3 * l + 1] = (int32_t)items.size();
+        levels[3 * l + 2] = (int32_t)brows.size();
+        // rounds of whole masks
+        for (size_t c = 0, at = 0; c < closes.size();) {
+            int ni = 0, nc = 0;
+            const int close0 = (int)words.size();
+            while (c < closes.size() && ni + closes[c].items <= kSmallItems) {
+                words.push_back(closes[c].mask << 8 | ni << 4 | closes[c].items);
+                ni += closes[c].items;
+                ++nc, ++c;
+            }
+            for (int32_t x : {l, item0 + (int32_t)at, ni, close0, nc, 0}) rounds.push_back(x);
+            at += ni;
+        }
+        // head-b rows of the special masks; the full mask's closes the sum
+        for (size_t at = 0; at < brows.size(); at += kSmallItems) {
+            const int ni = (int)std::min<size_t>(kSmallItems, brows.size() - at), close0 = (int)words.size();
+            const bool last = l == P.nlev;
+            if (last) words.push_back(m0 << 8 | 0 << 4 | 1);
+            for (int32_t x : {l, item0 + (int32_t)(items.size() + at), ni, close0, last ? 1 : 0, last ? 1 : 0})
+                rounds.push_back(x);
+        }
+    }
+    P.script = {(int32_t)(rounds.size() / kSmallRoundInts), (int32_t)words.size()};
+    P.script.insert(P.script.end(), rounds.begin(), rounds.end());
+    P.script.insert(P.script.end(), words.begin(), words.end());
+    P.script.insert(P.script.end(), levels.begin(), levels.end());
 }
 
 // The sublattice-labelled plan (mask digits base 4; see cos_internal.hpp).
@@ -400,11 +457,13 @@ cos_status device_plan(int dev, int n, PlanKind kind, DevPlan *out) {
     }
     auto hp = host_plan(n, kind);
     const size_t s1 = align_up(hp->mrec.size() * 4), s2 = align_up(hp->levels.size() * sizeof(int4));
+    const size_t s3 = align_up(hp->script.size() * 4);
     char *mem = nullptr;
-    if (dev_malloc((void **)&mem, s1 + s2) != hipSuccess)
+    if (dev_malloc((void **)&mem, s1 + s2 + s3) != hipSuccess)
         return fail(COS_ENOMEM, "device allocation of the state tables for n=%d failed", n);
     hipError_t e = hipMemcpy(mem, hp->mrec.data(), hp->mrec.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(mem + s1, hp->levels.data(), hp->levels.size() * sizeof(int4), hipMemcpyHostToDevice);
+    if (e == hipSuccess && s3) e = hipMemcpy(mem + s1 + s2, hp->script.data(), hp->script.size() * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         return fail(COS_EDEVICE, "upload of the state tables failed: %s", hipGetErrorString(e));
@@ -417,6 +476,7 @@ cos_status device_plan(int dev, int n, PlanKind kind, DevPlan *out) {
     t.dp.max_rows = hp->max_rows;
     t.dp.max_masks = hp->max_masks;
     t.dp.total_rows = hp->total_rows;
+    t.dp.script = s3 ? (const int32_t *)(mem + s1 + s2) : nullptr;
     g_dev[key] = t;
     *out = t.dp;
     return COS_OK;
@@ -956,12 +1016,46 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
     return COS_OK;
 }
 
+// orders that run a whole sweep in one launch: their tables are there, and G
+// (and the dS/dG accumulators) of every flavour fit LDS
+static bool small_order(cos_batch_t b, const OrderGroup &o, bool reverse) {
+    return !o.sub && b->plans[o.n].script && small_lds_bytes(o.n, b->nfs, reverse) <= 160 * 1024;
+}
+
+static SmallArgs small_args(cos_batch_t b, const OrderGroup &o, const double *d_G, const int64_t *d_Goff,
+                            const double *d_stub, double cycle_weight, double *d_out) {
+    const PackArgs p = pack_args(b, o, d_G, d_Goff, d_stub);
+    SmallArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.plan = b->plans[o.n];
+    a.G = p.G;
+    a.Goff = p.Goff;
+    a.stub = p.stub;
+    a.order = p.order;
+    a.W = level_args(b, o, cycle_weight).W;
+    a.out = d_out;
+    a.nfs = b->nfs;
+    a.count = o.count;
+    a.mask_only = (b->flags & COS_F_MASK_ONLY) ? 1 : 0;
+    return a;
+}
+
 // forward levels of one order, all groups, chunk by chunk (two level windows:
 // the side windows for a side order); `mark`: record the phase marks on s
 static cos_status forward_order(cos_batch_t b, const OrderGroup &o, const double *d_G, const int64_t *d_Goff,
                                 const double *d_stub, double cycle_weight, double *d_out, hipStream_t s,
                                 bool mark = true) {
     if (mark) HIP_TRY(tmark(b, COS_PHASE_PACK, s));
+    if (small_order(b, o, false)) {
+        if (mark) HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
+        SmallArgs a = small_args(b, o, d_G, d_Goff, d_stub, cycle_weight, d_out);
+        a.win = o.side ? b->d_win2 : b->d_win;
+        a.win_gstride = 2 * (int64_t)o.hp->max_rows * b->nfs * o.slots() * 64;
+        for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_fwd)
+            // (counted as the packing and the 2n levels that it does)
+            LAUNCH_STEPS(1 + 2 * o.n, launch_small(a, false, std::min(o.chunk_fwd, o.ngroups - a.group0), s));
+        return COS_OK;
+    }
     LAUNCH_TRY(launch_pack(pack_args(b, o, d_G, d_Goff, d_stub), s));
     if (mark) HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
     if (o.hp->nlev == 0) {   // order 1: closed form
@@ -1111,6 +1205,23 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                                 double *d_out, double *d_G_bar, double *d_stub_bar, hipStream_t s) {
     const PackArgs pa = pack_args(b, o, d_G, d_Goff, d_stub);
     HIP_TRY(tmark(b, COS_PHASE_PACK, s));
+    if (small_order(b, o, true) && !(b->flags & COS_F_DETERMINISTIC) && !o.adj_split) {
+        HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
+        HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
+        SmallArgs a = small_args(b, o, d_G, d_Goff, d_stub, cycle_weight, d_out);
+        a.out_bar = d_out_bar;
+        a.G_bar = d_G_bar;
+        a.stub_bar = d_stub_bar;
+        a.F_gstride = o.hp->total_rows * b->nfs * o.slots() * 64;
+        a.win_gstride = 2 * (int64_t)o.hp->max_rows * b->nfs * o.slots() * 64;
+        a.F = b->d_Fall;
+        a.win = b->d_Fall + a.F_gstride * o.chunk_adj;
+        for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_adj)
+            // (counted as the packing, zeroing, unpacking and the 4n levels that it does)
+            LAUNCH_STEPS(4 + 4 * o.n, launch_small(a, true, std::min(o.chunk_adj, o.ngroups - a.group0), s));
+        HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
+        return COS_OK;
+    }
     LAUNCH_TRY(launch_pack(pa, s));
     double *GbT = b->d_GbT + o.gb_off, *sbT = b->d_sbT + o.sb_off;
     const int64_t ngb = (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
@@ -1319,6 +1430,8 @@ cos_status cos_batch_autotune(cos_batch_t b, const double *d_G, const int64_t *d
     static const int kCaps[] = {1, 2, 4, 8, 16};
     static const int kAdjCaps[] = {2, 4, 6, 8, 12, 16, 24, 32, 48, 64};
     for (OrderGroup &o : b->orders) {
+        // a one-launch sweep has one shape
+        if (small_order(b, o, false) && (!d_out_bar || (small_order(b, o, true) && !o.adj_split))) continue;
         // forward: waves per workgroup x masks per wavefront
         LaunchShape best = o.shape;
         float tbest = 1e30f;
@@ -1698,6 +1811,8 @@ cos_status libcos::plan_tables(int n, bool tiles, PlanTables *out) {
     out->max_rows = p->max_rows;
     out->max_masks = p->max_masks;
     out->total_rows = p->total_rows;
+    out->script = p->script.data();
+    out->script_ints = p->script.size();
     return COS_OK;
 }
 
