@@ -75,7 +75,7 @@ extern "C" cos_status cos_connected_count(int32_t n, int64_t cycle_weight, int64
     int dev = 0, ncu = 0;
     if (cos_status st = current_device(&dev, &ncu)) return st;
     PlanTables t;
-    if (cos_status st = plan_tables(n, false, &t)) return st;
+    if (cos_status st = plan_tables(n, false, false, &t)) return st;
     // one allocation: the state tables, two level windows and the result
     const size_t mb = up256(t.mrec_ints * 4), lb = up256(t.nlevels * sizeof(int4));
     const size_t win = (size_t)t.max_rows * n;

@@ -35,11 +35,12 @@ namespace libcos {
 //   [3 + w] level-relative row of (m + e_w, 0) for each vertex w with m_w < 2
 //           (-1 otherwise)
 // The level kernels' tables (n >= 2): masks, levels and rows of the tile
-// scheme of cos_level.hip, over the first n - 1 vertices; in every level the
-// special masks (m_0 = 2, no vertex visited once) come last.  A row has n - 1
-// slots; what a wavefront needs is fetched with one scalar load:
-//   [0] ones | (twos << 16)    [1] first row (bytes from the level's first row)
-//   [2 + w] first row of m + e_w (bytes, in the next level), m_w < 2
+// scheme of cos_level.hip, over the first n - 1 vertices; a row of the tables is
+// one slot (64 doubles).  Batches of several flavours have tables of their own,
+// with three more slots in front of each mask with m_0 = 2.  What a wavefront
+// needs is fetched with one scalar load:
+//   [0] ones | (twos << 16)    [1] head 0's tile (bytes from the level's first)
+//   [2 + w] head 0's tile of m + e_w (bytes, in the next level), m_w < 2
 constexpr int kRecInts = 16;
 static_assert(3 + COS_NMAX <= kRecInts, "mask record too small");
 
@@ -57,14 +58,12 @@ struct DevPlan {
 // One-launch sweeps of small orders (cos_level.hip): tables of (mask, head)
 // items and of the rounds of the forward.  The script is
 //   [0] rounds R   [1] items I
-//   R records of kSmallRoundInts: level, first item, items, first close, closes,
-//     1 if it closes the full mask's head-b row
+//   R records of kSmallRoundInts: level, first item, items, first close, closes
 //   I words: items (mask << 8 | head slot << 4 | head, kSmallBrow for a head-b
 //     row) and closes (mask << 8 | first item of the round << 4 | items)
-//   3 ints per level 0..2(n - 1): first item, items, head-b rows of special
-//     masks (they follow the items)
+//   2 ints per level 0..2(n - 1): first item, items
 constexpr int kSmallMax = 5, kSmallWaves = 16, kSmallItems = 16, kSmallBrow = 15;
-constexpr int kSmallHeader = 2, kSmallRoundInts = 6;
+constexpr int kSmallHeader = 2, kSmallRoundInts = 5;
 
 __host__ __device__ inline constexpr int pow3(int k) { return k <= 0 ? 1 : 3 * pow3(k - 1); }
 
@@ -149,10 +148,10 @@ struct LvlArgs {
     int64_t F_gstride, F_frows;
     int32_t F_row0;
     int32_t level, group0, nfs, stubs, mpb;
-    // unlabelled levels: the level's first mask, its masks that are not special
-    // (in nblocks blocks of mpb masks per wavefront; split, and the reverse with
-    // row_items: of mpb masks) and its special masks, which take further workgroups
-    int32_t mask0, nmasks, nspecial, nblocks;
+    // unlabelled levels: the level's first mask and its masks, in nblocks blocks
+    // of mpb masks per wavefront (split, and the reverse with row_items: of mpb
+    // masks)
+    int32_t mask0, nmasks, nblocks;
     int32_t split;            // forward: blocks of mpb masks whose heads go to different wavefronts
     int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)
@@ -203,7 +202,7 @@ hipError_t launch_order1(const LvlArgs &a, int ngroups, hipStream_t s);
 constexpr int kAdjWaves = 8, kSubAdjWaves = 16;
 // most masks of a split forward block, and of a reverse block with row_items
 constexpr int kSplitMasks = 8, kAdjListMasks = 64;
-size_t fwd_lds_bytes(int n, int split_masks, int nspecial);
+size_t fwd_lds_bytes(int n, int split_masks);
 // deterministic reverse sweep: every level's masks in kDetParts fixed parts;
 // Gbar_T / sbar_T of the LvlArgs point to the partial sums
 // [part][group][flavour][v][w][64] and [part][group][flavour][64]
@@ -257,7 +256,8 @@ struct PlanTables {
     const int32_t *script;    // small orders, else empty
     size_t script_ints;
 };
-cos_status plan_tables(int n, bool tiles, PlanTables *out);
+// (`tiles`: for one flavour, or with `multi` for several)
+cos_status plan_tables(int n, bool tiles, bool multi, PlanTables *out);
 // workspace of one forward call: every pointer inside device memory the
 // caller owns; the level windows hold `chunk` groups of 64 configurations
 struct FixedWorkspace {
@@ -272,7 +272,7 @@ struct FixedWorkspace {
 struct FixedSizes {
     int64_t order_ints, gt_doubles, sig_doubles, lane_ints, win_doubles_per_group;
 };
-FixedSizes fixed_sizes(int nconf, int n, int nfs, int32_t max_rows);
+FixedSizes fixed_sizes(int nconf, int n, int nfs, int32_t max_rows);   // max_rows: of the tile tables
 // forward sums of nconf configurations of order n stored back to back (layout
 // of cos_connected_sum_batched with d_Goff = NULL), asynchronous on s
 cos_status forward_fixed(int dev, int ncu, const FixedWorkspace &ws, int32_t nconf, int32_t n, int32_t nflav,

@@ -33,9 +33,19 @@
 //   state buffers [group][flavour][row][v < n - 1][64]
 // Rows of a mask m, in order: head 0 (three rows, m_b = 0, 1, 2), then when
 // m_0 = 2 each head h >= 1 visited twice (three rows each) and last the one
-// row of head b (m_b = 2).  Slot 0 of a head-b row is never a current slot; in
-// a "special" mask (m_0 = 2, no vertex visited once) it holds the value with
-// which the cycle of head b opens there.
+// row of head b (m_b = 2).  A tile is stored slot by slot ([v][j][64]).
+//
+// Flavours meet only in t_m, and every flavour has workgroups of its own: each
+// stores its own part W sum_u acc[u] of t_m in its own plane, and whoever reads
+// a slot on which a cycle opens adds up the parts of all planes.  For head
+// h >= 1 the part is the slot (h, h) itself; for head 0, whose slot also takes
+// vertex 0's extension, it is a slot of its own in front of the mask's rows
+// (batches of one flavour add both and have no such slot).  For head b, which
+// opens only in a "special" mask (m_0 = 2, no vertex but b visited once): the
+// part is kept in slot 0 of the mask's own head-b row (never a current slot) for
+// the reverse sweep, and in slot 0 of the head-b row of every child m + e_w,
+// which then adds the opened cycle's first step, 2 t G[b][w], to its slot w.  So
+// no part of a level waits for another.
 //
 // Forward rules per row (m, u) and flavour l (Results; Alg. 2/3):
 //   acc = f . G_l;  extension to w (m_w < 2): child (m + e_w, u)[w] = c_w acc[w]
@@ -43,9 +53,7 @@
 //   reached for the first time: + (-sigma_l) f[w] (doubled on the start row);
 //   close: t_m = W sum_{u,l} acc[u]; the next cycle opens at
 //   h = min{k : m_k = 1} with value t_m in every flavour, or S = t_m at the
-//   full mask.  h is b only in special masks with m_b = 1, whose t feeds the
-//   head-b row of the same mask: its tiles come first, its head-b row after
-//   them (after every flavour's).
+//   full mask.
 //
 // Mask-only rules (SU(2), w = -1; Results, the variant without cycle factors;
 // Alg. 1): the states are (head point, current point, mask) with points, not
@@ -97,6 +105,18 @@ __device__ __forceinline__ uint32_t child_rows(const MaskRec<N> &M, int h) {
 // bytes of a tile's slot (three rows of 64 lanes) and of a tile
 constexpr uint32_t kSlotB = 3u * 512u;
 template <int N> constexpr uint32_t kTileB = (N - 1) * kSlotB;
+
+// every flavour's plane of a level
+struct Planes {
+    const double *base;
+    int64_t stride;   // doubles
+    int n;
+    __device__ __forceinline__ double sum(uint32_t lane_off, uint32_t at) const {
+        double x = 0.0;
+        for (int k = 0; k < n; ++k) x += slot_ld(make_plane(base + k * stride), lane_off, at);
+        return x;
+    }
+};
 
 // vertex 0 visited twice and no other vertex (but b) visited once
 __device__ __forceinline__ bool special_mask(uint32_t ones, uint32_t twos) { return (twos & 1u) && ones == 0u; }
@@ -168,40 +188,94 @@ __device__ __forceinline__ int claim(int *next, int lane) {
 // ---------------------------------------------------------------------------
 // forward: level -> level + 1
 // ---------------------------------------------------------------------------
-// the slots of the three rows at one vertex, or zeros (wave-uniform choice)
-template <bool STREAM>
-__device__ __forceinline__ void load_slot(double &x0, double &x1, double &x2, bool c, plane_t src,
-                                          const uint32_t (&off)[3], uint32_t at) {
-    x0 = x1 = x2 = 0.0;
-    if (c) {
-        x0 = state_ld<STREAM>(src, off[0], at);
-        x1 = state_ld<STREAM>(src, off[1], at);
-        x2 = state_ld<STREAM>(src, off[2], at);
+// The states of a tile: rows (m, m_b = j), head u, j = 0, 1, 2, at byte offset
+// `row`; zeros where v is not current (wave-uniform).  MULTI: the slot that the
+// tile's cycle opens on is the sum of every plane's part (for head 0 the parts
+// lie in front of the mask's rows, and the slot holds this flavour's extension).
+template <int N, bool MULTI, bool MASK, bool STREAM>
+__device__ __forceinline__ void tile_states(double (&f)[3][N - 1], const MaskRec<N> &M, uint32_t cm, int u, uint32_t row,
+                                            bool start, plane_t own, const Planes &all, const uint32_t (&off)[3]) {
+    uint32_t ld = start ? 0u : cm;   // slots read from the own plane
+    double y[3] = {0.0, 0.0, 0.0}, z[3] = {0.0, 0.0, 0.0};
+    const bool open = MULTI && ((ld >> u) & 1u) && (u || (M.twos & 1u));
+    const uint32_t oat = u ? row + (uint32_t)u * kSlotB : M.rb - kSlotB;
+    if (open) {
+        // mask-only: the first cycle's parts lie in plane 0 alone, and vertex 0
+        // is not reached by an extension
+        if (u || MASK) ld &= ~(1u << u);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            y[j] = slot_ld(make_plane(all.base), off[j], oat);
+            if (!MASK || u) z[j] = slot_ld(make_plane(all.base + all.stride), off[j], oat);
+        }
     }
+#pragma unroll
+    for (int v = 0; v < N - 1; ++v) {
+        f[0][v] = f[1][v] = f[2][v] = 0.0;
+        if (!((ld >> v) & 1u)) continue;
+        const uint32_t at = row + v * kSlotB;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) f[j][v] = state_ld<STREAM>(own, off[j], at);
+    }
+    if (MULTI) {
+        if (open && !MASK) {
+            for (int k = 2; k < all.n; ++k) {
+                const plane_t p = make_plane(all.base + k * all.stride);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) y[j] += slot_ld(p, off[j], oat);
+            }
+        }
+        // (selects: branches here made the compiler spill)
+#pragma unroll
+        for (int v = 0; v < N - 1; ++v)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) f[j][v] += v == u ? y[j] + z[j] : 0.0;
+    }
+    if (start) f[0][0] = 1.0;   // mask-only: plane 0 only (plane 1 skipped)
 }
 
-// One tile: rows (m, m_b = j), head u, j = 0, 1, 2.  cur and nxt: this
-// flavour's planes; hb: byte offset of the tile in its mask's rows.  Adds the
-// close to T[j] and returns in dext[j] the extension of vertex 0 to its second
-// visit while m_0 = 1 (the next cycle opens on that same slot).
+// The states of the row of head b, at byte offset `row`: where exactly one
+// vertex w is visited once, the cycle opened in m - e_w adds its first step.
+// Returns G in LDS.
 template <int N, bool MASK, bool STREAM>
-__device__ __forceinline__ void fwd_tile(const MaskRec<N> &M, uint32_t gaddr, plane_t cur, plane_t nxt,
+__device__ __forceinline__ const lds_double *brow_states(double (&f)[N - 1], const MaskRec<N> &M, uint32_t row,
+                                                         uint32_t gaddr, plane_t own, const Planes &all, uint32_t off) {
+    constexpr int NB = N - 1;
+    const uint32_t cm = (M.ones | M.twos) & ~1u;
+    int w = 31;
+    double y = 0.0;
+    if (M.ones && (M.ones & (M.ones - 1u)) == 0u) {
+        w = __builtin_ctz(M.ones);
+        y = (MASK ? 1.0 : 2.0) * all.sum(off, row) * ((const lds_double *)(uintptr_t)gaddr)[(NB * N + w) * 64];
+    }
+    asm volatile("" : "+v"(y));
+#pragma unroll
+    for (int v = 0; v < NB; ++v) {
+        f[v] = v == w ? y : 0.0;   // wave-uniform
+        if ((cm >> v) & 1u) f[v] += state_ld<STREAM>(own, off, row + v * 512u);
+    }
+    asm volatile("" : "+v"(gaddr));   // as in fwd_tile
+    const lds_double *Gs = (const lds_double *)(uintptr_t)gaddr;
+    return Gs;
+}
+
+// One tile.  own, nxt: this flavour's planes; hb: byte offset of the tile in its
+// mask's rows.  Adds the close to T[j] and returns in dext[j] the extension of
+// vertex 0 to its second visit while m_0 = 1 (the next cycle opens on that same
+// slot).
+template <int N, bool MULTI, bool MASK, bool STREAM>
+__device__ __forceinline__ void fwd_tile(const MaskRec<N> &M, uint32_t gaddr, plane_t own, const Planes &all, plane_t nxt,
                                          const uint32_t (&off)[3], int u, uint32_t hb, bool start, double sg,
                                          double (&T)[3], double (&dext)[3]) {
     constexpr int NB = N - 1;
     const uint32_t ones = M.ones, twos = M.twos;
     const uint32_t cm = current_set(u, ones, twos);   // the same for the three rows (on the start row: j = 0 only)
-    const uint32_t row = M.rb + hb;
-    // G comes from LDS for every tile: an opaque base keeps the N^2 reads inside
-    // the tile instead of hoisted into N^2 registers for the whole loop
+    double f[3][NB];
+    tile_states<N, MULTI, MASK, STREAM>(f, M, cm, u, M.rb + hb, start, own, all, off);
+    // G comes from LDS for every tile: a base that is opaque from here on keeps
+    // the N^2 reads behind the loads of the states, instead of in N^2 registers
     asm volatile("" : "+v"(gaddr));
     const lds_double *Gs = (const lds_double *)(uintptr_t)gaddr;
-    double f[3][NB];
-#pragma unroll
-    for (int v = 0; v < NB; ++v) {
-        load_slot<STREAM>(f[0][v], f[1][v], f[2][v], ((cm >> v) & 1u) && !start, cur, off, row + v * kSlotB);
-    }
-    if (start) f[0][0] = 1.0;   // mask-only: plane 0 only (plane 1 skipped)
     // vertex b first: the slots with current b of rows j = 1, 2
     double fb1, fb2;
     {
@@ -259,23 +333,16 @@ __device__ __forceinline__ void fwd_tile(const MaskRec<N> &M, uint32_t gaddr, pl
     }
 }
 
-// the row of head b (m_b = 2) at byte offset hb of its mask's rows; inj: the
-// value its cycle opens with (special masks, else 0).  Adds the close to T2.
+// the row of head b (m_b = 2) at byte offset hb of its mask's rows; returns its
+// close
 template <int N, bool MASK, bool STREAM>
-__device__ __forceinline__ void fwd_brow(const MaskRec<N> &M, uint32_t gaddr, plane_t cur, plane_t nxt,
-                                         uint32_t off, uint32_t hb, double inj, double sg, double &T2) {
+__device__ __forceinline__ double fwd_brow(const MaskRec<N> &M, uint32_t gaddr, plane_t own, const Planes &all,
+                                           plane_t nxt, uint32_t off, uint32_t hb, double sg) {
     constexpr int NB = N - 1;
     const uint32_t ones = M.ones, twos = M.twos;
     const uint32_t cm = (ones | twos) & ~1u;
-    const uint32_t row = M.rb + hb;
-    asm volatile("" : "+v"(gaddr));
-    const lds_double *Gs = (const lds_double *)(uintptr_t)gaddr;
-    double f[NB];
-#pragma unroll
-    for (int v = 0; v < NB; ++v) {
-        f[v] = 0.0;
-        if ((cm >> v) & 1u) f[v] = state_ld<STREAM>(cur, off, row + v * 512u);
-    }
+    double f[NB], close = 0.0;
+    const lds_double *Gs = brow_states<N, MASK, STREAM>(f, M, M.rb + hb, gaddr, own, all, off);
 #pragma unroll
     for (int w = 0; w < N; ++w) {
         const uint32_t bit = 1u << w;
@@ -283,57 +350,46 @@ __device__ __forceinline__ void fwd_brow(const MaskRec<N> &M, uint32_t gaddr, pl
         double a = 0.0;
 #pragma unroll
         for (int v = 0; v < NB; ++v) a = __builtin_fma(f[v], Gs[(v * N + w) * 64], a);
-        a = __builtin_fma(inj, Gs[(NB * N + w) * 64], a);
         if (w == NB) {
-            T2 += a;
+            close = a;
             continue;
         }
         const bool first = !(ones & bit);
-        if (first) a = MASK ? a : 2.0 * a;
+        if (first) a *= MASK ? 1.0 : 2.0;
         else if (cm & bit) a = __builtin_fma(-sg, f[w < NB ? w : 0], a);
         state_st<STREAM>(nxt, off, M.crb[w < NB ? w : 0] + hb + (first ? 0u : kTileB<N>) + w * 512u, a);
     }
+    return close;
 }
 
-// The close of a mask that is not special, for flavour lam (T: sums over its
-// heads): adds to the sums of the earlier flavours, which wait in the slots the
-// next cycle opens on (last plane), and after the last flavour opens it there
-// in every flavour.
+// Opens the next cycle of a mask that is not full with this flavour's part of
+// t_m (T: sums over its heads).
 template <int N, bool MULTI, bool MASK>
-__device__ __forceinline__ void close_mask(const MaskRec<N> &M, const LvlArgs &A, double *nxt, int64_t npl, int nfs,
-                                           int lam, plane_t nxtL, const uint32_t (&off)[3], double (&T)[3],
-                                           const double (&dext)[3]) {
+__device__ __forceinline__ void close_mask(const MaskRec<N> &M, double W, plane_t own, plane_t nxt,
+                                           const uint32_t (&off)[3], const double (&T)[3], const double (&dext)[3]) {
+    constexpr int NB = N - 1;
+    if (special_mask(M.ones, M.twos)) {   // head b, m_b = 1
+        const uint32_t brow = (1u + (uint32_t)__builtin_popcount(M.twos & ~1u)) * kTileB<N>;
+        const double x = W * T[1];
+        slot_st(own, off[0], M.rb + brow, x);
+#pragma unroll
+        for (int w = 0; w < NB; ++w)
+            if (!((M.twos >> w) & 1u)) slot_st(nxt, off[0], M.crb[w] + brow, x);
+        return;
+    }
     const int h = __builtin_ctz(M.ones);   // some vertex but b is visited once
-    const uint32_t dst = child_rows<N>(M, h) + open_slot<N>(h, M.twos);
-    const plane_t nxtZ = MULTI ? make_plane(nxt + (nfs - 1) * npl) : nxtL;
-    if (MULTI) {
-        if (lam > 0) {
+    const uint32_t base = child_rows<N>(M, h), dst = base + open_slot<N>(h, M.twos);
+    if (!MULTI) {
 #pragma unroll
-            for (int j = 0; j < 3; ++j) T[j] += slot_ld(nxtZ, off[j], dst);
-        }
-        if (lam < nfs - 1) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) slot_st(nxtZ, off[j], dst, T[j]);
-            if (!MASK && h == 0) {
-#pragma unroll
-                for (int j = 0; j < 3; ++j) slot_st(nxtL, off[j], dst, dext[j]);
-            }
-            return;
-        }
-        // mask-only: the first cycle's successor opens on the down point of
-        // vertex 0 only; later ones on both ends of h
-        for (int k = 0; k < nfs - 1; ++k) {
-            if (MASK && h == 0) continue;
-            const plane_t d = make_plane(nxt + k * npl);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double x = (!MASK && h == 0) ? slot_ld(d, off[j], dst) : 0.0;
-                slot_st(d, off[j], dst, __builtin_fma(A.W, T[j], x));
-            }
-        }
+        for (int j = 0; j < 3; ++j) slot_st(nxt, off[j], dst, __builtin_fma(W, T[j], h == 0 ? dext[j] : 0.0));
+        return;
     }
 #pragma unroll
-    for (int j = 0; j < 3; ++j) slot_st(nxtZ, off[j], dst, __builtin_fma(A.W, T[j], h == 0 ? dext[j] : 0.0));
+    for (int j = 0; j < 3; ++j) slot_st(nxt, off[j], h ? dst : base - kSlotB, W * T[j]);
+    if (!MASK && h == 0) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) slot_st(nxt, off[j], dst, dext[j]);
+    }
 }
 
 // head of slot k of a mask with `heads` (the heads >= 1)
@@ -342,27 +398,93 @@ __device__ __forceinline__ int head_of(uint32_t heads, int k) {
     return k ? __builtin_ctz(heads) : 0;
 }
 
-// A workgroup serves one group of 64 configurations and a block of masks.
-// G_l of the 64 lanes sits in LDS ([v][w][lane], conflict-free: the lanes read
-// consecutive words), loaded once per flavour by the whole workgroup; with
-// several flavours the flavour loop is outermost.
+// head slots of a mask: its tiles, and the head-b row
+__device__ __forceinline__ int head_slots(uint32_t twos) {
+    return (twos & 1u) ? 2 + __builtin_popcount(twos & ~1u) : 1;
+}
+
+// lists the items (mask << 4 | head slot) of a block of `nm` <= 64 masks, mask
+// by mask, heads in order: lane m of one wavefront takes mask m.  Returns their
+// number in lane 63.
+__device__ __forceinline__ int list_items(uint16_t *list, const int32_t *mrec, int nm, int lane) {
+    const int cnt = lane < nm ? head_slots((uint32_t)mrec[(int64_t)lane * kRecInts] >> 16) : 0;
+    int end = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int x = __shfl_up(end, d);
+        if (lane >= d) end += x;
+    }
+    for (int k = 0; k < cnt; ++k) list[end - cnt + k] = (uint16_t)(lane << 4 | k);
+    return end;
+}
+
+// The last level: the full mask alone.  One workgroup per group, its heads
+// spread over the wavefronts, flavour after flavour; wavefront 0 adds up the
+// closes.  (A kernel of its own: inside level_fwd_kernel a further copy of the
+// tile made the compiler spill.)
+template <int N, bool MULTI, bool MASK>
+__global__ void __launch_bounds__(1024) level_last_kernel(const LvlArgs A) {
+    constexpr int NB = N - 1;
+    extern __shared__ double lds[];
+    double *Gs_all = lds, *Ts = lds + N * N * 64;   // G, close sums [head][3][64]
+    const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6), wpb = blockDim.x >> 6;
+    const int gl = blockIdx.x, g = A.group0 + gl, nfs = MULTI ? A.nfs : 1;
+    const Planes all{A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * 64, A.cur_frows * 64, nfs};
+    const plane_t nxt = make_plane(A.nxt);   // (nothing is open: never written)
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
+    const MaskRec<N> M = load_rec<N>(A.plan, A.mask0);
+    const uint32_t heads = M.twos & ~1u, brow = (uint32_t)NB * kTileB<N>;
+    const uint32_t gaddr = lds_addr(Gs_all) + lane8;
+    double T1 = 0.0, T2 = 0.0, gbb = 0.0;
+    for (int lam = 0; lam < nfs; ++lam) {
+        if (MULTI && lam) __syncthreads();
+        stage_slots(Gs_all, A.GT + (int64_t)(g * nfs + lam) * N * N * 64, N * N);
+        __syncthreads();
+        const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+        const plane_t own = make_plane(all.base + lam * all.stride);
+        for (int k = wave; k <= NB; k += wpb) {
+            double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
+            const int u = head_of(heads, min(k, NB - 1));
+            if (k == NB) T[2] = fwd_brow<N, MASK, true>(M, gaddr, own, all, nxt, lane8, brow, sg);
+            else if (!(MASK && empty_plane(u, lam, M.twos)))
+                fwd_tile<N, MULTI, MASK, true>(M, gaddr, own, all, nxt, off, u, (uint32_t)k * kTileB<N>, false, sg, T, dext);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) Ts[(k * 3 + j) * 64 + lane] = T[j];
+        }
+        __syncthreads();
+        if (wave) continue;
+        double s1 = 0.0, s2 = 0.0;
+        for (int k = 0; k <= NB; ++k) {
+            s1 += Ts[(k * 3 + 1) * 64 + lane];
+            s2 += Ts[(k * 3 + 2) * 64 + lane];
+        }
+        T1 += A.W * s1;   // the parts of the cycle of head b, as the other masks store them
+        T2 += s2;
+        gbb += Gs_all[(NB * N + NB) * 64 + lane];
+        slot_st(own, lane8, M.rb + brow, A.W * s1);
+    }
+    // the cycle of head b closes at once
+    const int cfg = A.lane_cfg[g * 64 + lane];
+    if (wave == 0 && cfg >= 0 && A.out) A.out[cfg] = A.W * __builtin_fma(T1, gbb, T2);
+}
+
+// A workgroup serves one group of 64 configurations, one flavour and a block of
+// masks.  G_l of the 64 lanes sits in LDS ([v][w][lane], conflict-free: the
+// lanes read consecutive words), loaded once by the whole workgroup.
 //   Levels of many masks: the wavefronts claim the block's masks one at a time
 // from an LDS counter (a wavefront that drew masks with few heads takes more)
 // and take a mask's heads in turn.
 //   Levels with fewer masks than wavefronts that fit the chip (A.split): the
 // heads of a mask go to different wavefronts, and the close sums of the heads
 // wait in LDS until one wavefront adds them up, in the same order.
-//   Special masks have workgroups of their own, one mask each, its heads spread
-// over the wavefronts, which pass over the flavours twice: the tiles, then the
-// head-b row.
 template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
-    constexpr int NB = N - 1;
     extern __shared__ double lds[];
     double *Gs_all = lds;                      // [N * N][64]
-    double *Ts = lds + N * N * 64;             // close sums of heads [item][3][64] (split, special)
+    double *Ts = lds + N * N * 64;             // close sums of heads [item][3][64] (split)
     __shared__ int next_mask, nitems;
-    __shared__ uint8_t item_list[kSplitMasks * N];
+    __shared__ uint16_t item_list[kSplitMasks * N];
     const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6);   // wave index: uniform
     const int wpb = blockDim.x >> 6;
     const DevPlan &P = A.plan;
@@ -371,149 +493,83 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
     const int gl = at.group, g = A.group0 + gl;
     const int nfs = MULTI ? A.nfs : 1;
     // wave-uniform bases; the lane's word is added at each access.  States are
-    // stored by flavour plane: [flavour][row][v][lane], planes of *_frows rows
-    const double *cur = A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * NB * 64;
-    double *nxt = A.nxt + gl * A.nxt_gstride + (int64_t)A.nxt_row0 * NB * 64;
-    const int64_t cpl = A.cur_frows * NB * 64, npl = A.nxt_frows * NB * 64;
+    // stored by flavour plane: [flavour][row][v][lane], planes of *_frows slots
+    const Planes all{A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * 64, A.cur_frows * 64, nfs};
+    double *nxt = A.nxt + gl * A.nxt_gstride + (int64_t)A.nxt_row0 * 64;
     const uint32_t lane8 = (uint32_t)lane * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
-    const uint32_t gaddr = lds_addr(Gs_all) + lane8, taddr = lds_addr(Ts) + lane8;
-    lds_double *const Tl = (lds_double *)(uintptr_t)taddr;
+    const uint32_t gaddr = lds_addr(Gs_all) + lane8;
     const bool start = A.level == 1;
-    const double *__restrict__ GT = A.GT + (int64_t)g * nfs * N * N * 64;
+    const double *GT = A.GT + (int64_t)g * nfs * N * N * 64, *sigT = A.stubs ? A.sigT + (int64_t)g * nfs * 64 : nullptr;
 
-    if (at.x < A.nblocks) {
-        const int bm = A.split ? A.mpb : wpb * A.mpb;   // masks of a block
-        const int mb0 = at.x * bm, mb1 = min(mb0 + bm, A.nmasks);
-        if (A.split && wave == 0) {
-            // the block's items, mask by mask, heads in order: lane m takes mask m
-            const int m = lane < mb1 - mb0 ? lane : -1;
-            const uint32_t twos =
-                m >= 0 ? (uint32_t)P.mrec[(int64_t)(A.mask0 + mb0 + m) * kRecInts] >> 16 : 0u;
-            const int cnt = m < 0 ? 0 : (twos & 1u) ? 2 + __builtin_popcount(twos & ~1u) : 1;
-            int end = cnt;
-#pragma unroll
-            for (int d = 1; d < kSplitMasks; d <<= 1) {
-                const int x = __shfl_up(end, d);
-                if (lane >= d) end += x;
+    const int blk = MULTI ? at.x / nfs : at.x, lam = MULTI ? at.x - blk * nfs : 0;
+    const int bm = A.split ? A.mpb : wpb * A.mpb;   // masks of a block
+    const int mb0 = blk * bm, mb1 = min(mb0 + bm, A.nmasks);
+    if (A.split && wave == 0) {
+        const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + mb0) * kRecInts, mb1 - mb0, lane);
+        if (lane == 63) nitems = n;
+    }
+    if (threadIdx.x == 0) next_mask = mb0 + wpb;   // the first wpb masks go to the waves in order
+    stage_slots(Gs_all, GT + (int64_t)lam * N * N * 64, N * N);
+    __syncthreads();
+    const double sg = sigT ? sigT[lam * 64 + lane] : 0.0;
+    const plane_t own = make_plane(all.base + lam * all.stride), nxtL = make_plane(nxt + lam * (A.nxt_frows * 64));
+    if (A.split) {
+        const int ni = COS_RF(nitems);
+        for (int i = wave; i < ni; i += wpb) {
+            const int word = COS_RF((int)item_list[i]), k = word & 15;
+            const MaskRec<N> M = load_rec<N>(P, A.mask0 + mb0 + (word >> 4));
+            const uint32_t heads = (M.twos & 1u) ? (M.twos & ~1u) : 0u, hb = (uint32_t)k * kTileB<N>;
+            double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
+            if (k == 1 + __builtin_popcount(heads)) {
+                T[2] = fwd_brow<N, MASK, true>(M, gaddr, own, all, nxtL, lane8, hb, sg);
+            } else {
+                const int u = head_of(heads, k);
+                if (!(MASK && empty_plane(u, lam, M.twos)))
+                    fwd_tile<N, MULTI, MASK, true>(M, gaddr, own, all, nxtL, off, u, hb, start, sg, T, dext);
             }
-            for (int k = 0; k < cnt; ++k) item_list[end - cnt + k] = (uint8_t)(m << 4 | k);
-            if (lane == kSplitMasks - 1) nitems = end;
+            if (!(M.twos & 1u)) {   // the mask's only head
+                close_mask<N, MULTI, MASK>(M, A.W, own, nxtL, off, T, dext);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 3; ++j) Ts[(i * 3 + j) * 64 + lane] = T[j];
+            }
         }
-        for (int lam = 0; lam < nfs; ++lam) {
-            if (MULTI && lam) __syncthreads();
-            if (threadIdx.x == 0) next_mask = mb0 + wpb;   // the first wpb masks go to the waves in order
-            stage_slots(Gs_all, GT + (int64_t)lam * N * N * 64, N * N);
-            __syncthreads();
-            const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
-            const plane_t curL = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
-            if (A.split) {
-                const int ni = COS_RF(nitems);
-                for (int i = wave; i < ni; i += wpb) {
-                    const int word = COS_RF((int)item_list[i]), k = word & 15;
-                    const MaskRec<N> M = load_rec<N>(P, A.mask0 + mb0 + (word >> 4));
-                    const uint32_t heads = (M.twos & 1u) ? (M.twos & ~1u) : 0u;
-                    double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
-                    if (k == 1 + __builtin_popcount(heads)) {
-                        fwd_brow<N, MASK, true>(M, gaddr, curL, nxtL, lane8, (uint32_t)k * kTileB<N>, 0.0, sg, T[2]);
-                    } else {
-                        const int u = head_of(heads, k);
-                        if (!(MASK && empty_plane(u, lam, M.twos)))
-                            fwd_tile<N, MASK, true>(M, gaddr, curL, nxtL, off, u, (uint32_t)k * kTileB<N>, start, sg, T,
-                                                    dext);
-                    }
-                    if (!(M.twos & 1u)) {   // the mask's only head
-                        close_mask<N, MULTI, MASK>(M, A, nxt, npl, nfs, lam, nxtL, off, T, dext);
-                    } else {
+        __syncthreads();
+        int i0 = 0;
+        for (int m = 0; m < mb1 - mb0; ++m) {
+            const MaskRec<N> M = load_rec<N>(P, A.mask0 + mb0 + m);
+            const int cnt = head_slots(M.twos);
+            if ((M.twos & 1u) && m % wpb == wave) {
+                double T[3] = {0.0, 0.0, 0.0};
+                const double dext[3] = {0.0, 0.0, 0.0};
+                for (int i = i0; i < i0 + cnt; ++i)
 #pragma unroll
-                        for (int j = 0; j < 3; ++j) Tl[(i * 3 + j) * 64] = T[j];
-                    }
-                }
-                __syncthreads();
-                int i0 = 0;
-                for (int m = 0; m < mb1 - mb0; ++m) {
-                    const MaskRec<N> M = load_rec<N>(P, A.mask0 + mb0 + m);
-                    const int cnt = (M.twos & 1u) ? 2 + __builtin_popcount(M.twos & ~1u) : 1;
-                    if ((M.twos & 1u) && m % wpb == wave) {
-                        double T[3] = {0.0, 0.0, 0.0};
-                        const double dext[3] = {0.0, 0.0, 0.0};
-                        for (int i = i0; i < i0 + cnt; ++i)
-#pragma unroll
-                            for (int j = 0; j < 3; ++j) T[j] += Tl[(i * 3 + j) * 64];
-                        close_mask<N, MULTI, MASK>(M, A, nxt, npl, nfs, lam, nxtL, off, T, dext);
-                    }
-                    i0 += cnt;
-                }
-                continue;
+                    for (int j = 0; j < 3; ++j) T[j] += Ts[(i * 3 + j) * 64 + lane];
+                close_mask<N, MULTI, MASK>(M, A.W, own, nxtL, off, T, dext);
             }
-            for (int mi = mb0 + wave; mi < mb1; mi = claim(&next_mask, lane)) {
-                const MaskRec<N> M = load_rec<N>(P, A.mask0 + mi);
-                const uint32_t twos = M.twos;
-                uint32_t hs = (twos & 1u) ? (twos & ~1u) : 0u;   // heads >= 1, ascending
-                int u = 0;
-                uint32_t hb = 0;
-                double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
-                while (true) {
-                    if (!(MASK && empty_plane(u, lam, twos)))
-                        fwd_tile<N, MASK, true>(M, gaddr, curL, nxtL, off, u, hb, start, sg, T, dext);
-                    hb += kTileB<N>;
-                    if (!hs) break;
-                    u = __builtin_ctz(hs);
-                    hs &= hs - 1u;
-                }
-                if (twos & 1u) fwd_brow<N, MASK, true>(M, gaddr, curL, nxtL, off[0], hb, 0.0, sg, T[2]);
-                close_mask<N, MULTI, MASK>(M, A, nxt, npl, nfs, lam, nxtL, off, T, dext);
-            }
+            i0 += cnt;
         }
         return;
     }
-
-    // a special mask: the tiles, then the row of head b
-    const MaskRec<N> M = load_rec<N>(P, A.mask0 + A.nmasks + (at.x - A.nblocks));
-    const uint32_t heads = M.twos & ~1u;
-    const int nh = 1 + __builtin_popcount(heads);
-    const uint32_t brow = (uint32_t)nh * kTileB<N>;
-    const int cfg = A.lane_cfg[g * 64 + lane];
-    double T1 = 0.0, T2 = 0.0;   // wavefront 0
-    for (int lam = 0; lam < nfs; ++lam) {
-        if (MULTI && lam) __syncthreads();
-        stage_slots(Gs_all, GT + (int64_t)lam * N * N * 64, N * N);
-        __syncthreads();
-        const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
-        const plane_t curL = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
-        for (int k = wave; k < nh; k += wpb) {
-            double T[3] = {0.0, 0.0, 0.0}, dext[3];
-            const int u = head_of(heads, k);
-            if (!(MASK && empty_plane(u, lam, M.twos)))
-                fwd_tile<N, MASK, true>(M, gaddr, curL, nxtL, off, u, (uint32_t)k * kTileB<N>, false, sg, T, dext);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) Tl[(k * 3 + j) * 64] = T[j];
+    for (int mi = mb0 + wave; mi < mb1; mi = claim(&next_mask, lane)) {
+        const MaskRec<N> M = load_rec<N>(P, A.mask0 + mi);
+        const uint32_t twos = M.twos;
+        uint32_t hs = (twos & 1u) ? (twos & ~1u) : 0u;   // heads >= 1, ascending
+        int u = 0;
+        uint32_t hb = 0;
+        double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
+        while (true) {
+            if (!(MASK && empty_plane(u, lam, twos)))
+                fwd_tile<N, MULTI, MASK, true>(M, gaddr, own, all, nxtL, off, u, hb, start, sg, T, dext);
+            hb += kTileB<N>;
+            if (!hs) break;
+            u = __builtin_ctz(hs);
+            hs &= hs - 1u;
         }
-        __syncthreads();
-        if (wave) continue;
-        double s1 = 0.0, s2 = 0.0;
-        for (int k = 0; k < nh; ++k) {
-            s1 += Tl[(k * 3 + 1) * 64];
-            s2 += Tl[(k * 3 + 2) * 64];
-        }
-        T1 += s1;
-        T2 += s2;
+        if (twos & 1u) T[2] += fwd_brow<N, MASK, true>(M, gaddr, own, all, nxtL, lane8, hb, sg);
+        close_mask<N, MULTI, MASK>(M, A.W, own, nxtL, off, T, dext);
     }
-    const double inj = A.W * T1;
-    // slot 0 of the head-b row, plane 0: the reverse sweep reads it
-    if (wave == 0) slot_st(make_plane(cur), lane8, M.rb + brow, inj);
-    for (int lam = 0; lam < nfs; ++lam) {
-        if (MULTI) {
-            __syncthreads();
-            stage_slots(Gs_all, GT + (int64_t)lam * N * N * 64, N * N);
-            __syncthreads();
-        }
-        if (wave) continue;
-        const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
-        fwd_brow<N, MASK, true>(M, gaddr, make_plane(cur + lam * cpl), make_plane(nxt + lam * npl), lane8, brow, inj, sg,
-                                T2);
-    }
-    if (wave == 0 && M.twos == (1u << NB) - 1u && cfg >= 0 && A.out) A.out[cfg] = A.W * T2;
 }
 
 // ---------------------------------------------------------------------------
@@ -560,10 +616,11 @@ __device__ __forceinline__ void lds_add(lds_double *p, double x) {
     __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-template <int N, bool MASK, bool STREAM, class Order>
-__device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F, plane_t Bn,
-                                         plane_t Bc, const uint32_t (&off)[3], int u, uint32_t hb, bool start,
-                                         const double (&tb)[3], double sg, double &sacc, const Order &order) {
+template <int N, bool MULTI, bool MASK, bool STREAM, class Order>
+__device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F,
+                                         const Planes &Fall, plane_t Bn, plane_t Bc, const uint32_t (&off)[3], int u,
+                                         uint32_t hb, bool start, const double (&tb)[3], double sg, double &sacc,
+                                         const Order &order) {
     constexpr int NB = N - 1;
     const uint32_t ones = M.ones, twos = M.twos;
     const uint32_t cm = current_set(u, ones, twos);
@@ -584,11 +641,7 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
             for (int j = 0; j < 3; ++j) a[j][w] = 0.0;
         }
     }
-#pragma unroll
-    for (int v = 0; v < NB; ++v) {
-        load_slot<STREAM>(f[0][v], f[1][v], f[2][v], ((cm >> v) & 1u) && !start, F, off, row + v * kSlotB);
-    }
-    if (start) f[0][0] = 1.0;
+    tile_states<N, MULTI, MASK, STREAM>(f, M, cm, u, row, start, F, Fall, off);
     const double sgx = start ? 2.0 * sg : sg, sc = start ? 2.0 : 1.0;
 #pragma unroll
     for (int w = 0; w < NB; ++w) {
@@ -606,10 +659,8 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
             for (int j = 0; j < 3; ++j) sacc = __builtin_fma(-sc * f[j][w], a[j][w], sacc);
         }
         // the close of this row feeds t_m: dS/dacc[u] gains W tbar
-        if (w == u) {
 #pragma unroll
-            for (int j = 0; j < 3; ++j) a[j][w] += tb[j];
-        }
+        for (int j = 0; j < 3; ++j) a[j][w] += w == u ? tb[j] : 0.0;   // (a branch here made the compiler spill)
     }
     const uint32_t need = (~twos | (1u << u)) & ((1u << NB) - 1u);   // w < b with a[w] != 0 possible
     asm volatile("" : "+v"(gaddr));
@@ -689,28 +740,30 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
     order.done();
 }
 
-// the row of head b; fi: the forward value its cycle opened with (special
-// masks, else 0).  Returns the adjoint of that value.
+// the row of head b; tb: W times the adjoint of its close.  In special masks
+// the cycle that opens there adds its own terms to dS/dG (its adjoint is formed
+// by close_adjoint).
 template <int N, bool MASK, bool STREAM, class Order>
-__device__ __forceinline__ double adj_brow(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F, plane_t Bn,
-                                           plane_t Bc, uint32_t off, uint32_t hb, double fi, double tb, double sg,
-                                           double &sacc, const Order &order) {
+__device__ __forceinline__ void adj_brow(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F,
+                                         const Planes &Fall, plane_t Bn, plane_t Bc, uint32_t off, uint32_t hb, double tb,
+                                         double sg, double &sacc, const Order &order) {
     constexpr int NB = N - 1;
     const uint32_t ones = M.ones, twos = M.twos;
     const uint32_t cm = (ones | twos) & ~1u;
     const uint32_t row = M.rb + hb;
     double a[N], f[NB];
+    double fi = 0.0;
+    if (special_mask(ones, twos)) fi = Fall.sum(off, row);
+    const lds_double *Gs = brow_states<N, MASK, STREAM>(f, M, row, gaddr, F, Fall, off);
 #pragma unroll
     for (int w = 0; w < NB; ++w) {
         const uint32_t bit = 1u << w;
         const bool first = !(ones & bit);
         a[w] = 0.0;
-        if (!(twos & bit)) {
-            a[w] = slot_ld(Bn, off, M.crb[w] + hb + (first ? 0u : kTileB<N>) + w * 512u);
-        }
-        f[w] = 0.0;
-        if ((cm >> w) & 1u) f[w] = state_ld<STREAM>(F, off, row + w * 512u);
+        if (!(twos & bit)) a[w] = slot_ld(Bn, off, M.crb[w] + hb + (first ? 0u : kTileB<N>) + w * 512u);
     }
+    asm volatile("" : "+v"(gbaddr));
+    lds_double *Gb = (lds_double *)(uintptr_t)gbaddr;
 #pragma unroll
     for (int w = 0; w < NB; ++w) {
         const uint32_t bit = 1u << w;
@@ -718,24 +771,17 @@ __device__ __forceinline__ double adj_brow(const MaskRec<N> &M, uint32_t gaddr, 
         if ((ones & bit) && (cm & bit)) sacc = __builtin_fma(-f[w], a[w], sacc);
     }
     a[NB] = tb;
-    asm volatile("" : "+v"(gaddr));
-    asm volatile("" : "+v"(gbaddr));
-    const lds_double *Gs = (const lds_double *)(uintptr_t)gaddr;
-    lds_double *Gb = (lds_double *)(uintptr_t)gbaddr;
-    double binj = 0.0;
     order.wait();   // (a head-b row is short: its turn covers all of the following)
 #pragma unroll
     for (int v = 0; v < N; ++v) {
         const uint32_t bit = 1u << v;
         if (v < NB ? !(cm & bit) : !special_mask(ones, twos)) continue;
-        double b = 0.0;
-#pragma unroll
-        for (int w = 0; w < N; ++w) b = __builtin_fma(Gs[(v * N + w) * 64], a[w], b);
         if (v < NB) {
+            double b = 0.0;
+#pragma unroll
+            for (int w = 0; w < N; ++w) b = __builtin_fma(Gs[(v * N + w) * 64], a[w], b);
             if (ones & bit) b = __builtin_fma(-sg, a[v < NB ? v : 0], b);
             state_st<STREAM>(Bc, off, row + v * 512u, b);
-        } else {
-            binj = b;
         }
         const double fv = v < NB ? f[v < NB ? v : 0] : fi;
 #pragma unroll
@@ -743,28 +789,37 @@ __device__ __forceinline__ double adj_brow(const MaskRec<N> &M, uint32_t gaddr, 
             if (w == NB || !((twos >> w) & 1u)) lds_add(Gb + (v * N + w) * 64, fv * a[w]);   // wave-uniform
     }
     order.done();
-    return binj;
 }
 
-// W tbar of a mask's three rows.  Special masks: row 1 feeds the head-b rows,
-// whose opening adjoints lie in slot 0 of those rows at this level; row 2 is
-// the result at the full mask.
-template <int N, bool MASK>
-__device__ __forceinline__ void close_adjoint(const MaskRec<N> &M, const double *Bn, const double *Bc,
-                                              int64_t cpl, int64_t npl, const uint32_t (&off)[3], int nfs, double W,
-                                              double obar, double (&tb)[3]) {
+// W tbar of a mask's three rows.  Special masks: row 1 opens the cycle of head
+// b, whose adjoint in flavour l is sum_w G_l[b][w] a_l[w] over the head-b row's
+// outputs (the children's slots, its close); row 2 is the result at the full
+// mask.  grow(l, w): G_l[b][w].
+template <int N, bool MASK, class RowB>
+__device__ __forceinline__ void close_adjoint(const MaskRec<N> &M, const Planes &Bn, const RowB &grow,
+                                              const uint32_t (&off)[3], double W, double obar, double (&tb)[3]) {
+    constexpr int NB = N - 1;
     const uint32_t ones = M.ones, twos = M.twos;
     tb[0] = tb[1] = tb[2] = 0.0;
     if (special_mask(ones, twos)) {
         const uint32_t brow = (1u + (uint32_t)__builtin_popcount(twos & ~1u)) * kTileB<N>;
-        for (int k = 0; k < nfs; ++k) tb[1] += slot_ld(make_plane(Bc + k * npl), off[0], M.rb + brow);
-        if (twos == (1u << (N - 1)) - 1u) tb[2] = obar;
+        const bool full = twos == (1u << NB) - 1u;
+        for (int k = 0; k < Bn.n; ++k) {
+            const plane_t p = make_plane(Bn.base + k * Bn.stride);
+#pragma unroll
+            for (int w = 0; w < NB; ++w)
+                if (!((twos >> w) & 1u))
+                    tb[1] = __builtin_fma((MASK ? 1.0 : 2.0) * slot_ld(p, off[0], M.crb[w] + brow + w * 512u),
+                                          grow(k, w), tb[1]);
+            if (full) tb[1] = __builtin_fma(W * obar, grow(k, NB), tb[1]);
+        }
+        if (full) tb[2] = obar;
     } else {
         const int h = __builtin_ctz(ones);
         const uint32_t at = child_rows<N>(M, h) + open_slot<N>(h, twos);
-        for (int k = 0; k < nfs; ++k) {
+        for (int k = 0; k < Bn.n; ++k) {
             if (MASK && h == 0 && k == 0) continue;
-            const plane_t p = make_plane(Bn + k * cpl);
+            const plane_t p = make_plane(Bn.base + k * Bn.stride);
 #pragma unroll
             for (int j = 0; j < 3; ++j) tb[j] += slot_ld(p, off[j], at);
         }
@@ -773,9 +828,42 @@ __device__ __forceinline__ void close_adjoint(const MaskRec<N> &M, const double 
     for (int j = 0; j < 3; ++j) tb[j] *= W;
 }
 
-template <int N, bool MASK>
+// the head slots [s0, s1) of a mask, backwards
+template <int N, bool MULTI, bool MASK, bool STREAM, class Order>
+__device__ __forceinline__ void adj_heads(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F,
+                                          const Planes &Fall, plane_t Bn, plane_t Bc, const uint32_t (&off)[3], int lam,
+                                          int s0, int s1, bool start, const double (&tb)[3], double sg, double &sacc,
+                                          const Order &order) {
+    const uint32_t twos = M.twos;
+    const int nh = (twos & 1u) ? 1 + __builtin_popcount(twos & ~1u) : 1;
+    uint32_t hs = (twos & 1u) ? (twos & ~1u) : 0u;   // heads >= 1, ascending
+    for (int k = 1; k < s0; ++k) hs &= hs - 1u;
+    for (int k = s0; k < s1 && k < nh; ++k) {
+        int u = 0;
+        if (k > 0) {
+            u = __builtin_ctz(hs);
+            hs &= hs - 1u;
+        }
+        if (!(MASK && empty_plane(u, lam, twos))) {
+            adj_tile<N, MULTI, MASK, STREAM, Order>(M, gaddr, gbaddr, F, Fall, Bn, Bc, off, u, (uint32_t)k * kTileB<N>, start, tb,
+                                             sg, sacc, order);
+        } else {
+            order.wait();
+            order.done();
+        }
+    }
+    if ((twos & 1u) && s1 > nh)   // the close of the head-b row feeds row 2
+        adj_brow<N, MASK, STREAM, Order>(M, gaddr, gbaddr, F, Fall, Bn, Bc, off[0], (uint32_t)nh * kTileB<N>, tb[2], sg,
+                                         sacc, order);
+}
+
+// A workgroup serves one group, one flavour and a block of masks.  Its
+// wavefronts claim masks one at a time from an LDS counter, so that a wavefront
+// that drew masks with few heads takes more.  On levels of few masks the items
+// are (mask, head) pairs instead (A.row_items: blocks of mpb masks, their items
+// listed in LDS), so that the heads of a mask run side by side.
+template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs A) {
-    constexpr int NB = N - 1;
     extern __shared__ double lds[];
     double *Gs_all = lds;                     // [N * N][64]  G of the flavour
     double *Gb_all = lds + N * N * 64;        // [N * N][64]  dS/dG of the flavour, this workgroup
@@ -786,123 +874,74 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
     const DevPlan &P = A.plan;
     BlockAt at;
     if (!xcd_block(A, at)) return;
-    // the workgroup's block of masks; its wavefronts claim masks one at a time
-    // from an LDS counter, so that a wavefront that drew masks with few heads
-    // takes more.  On levels of few masks the items are (mask, head) pairs
-    // instead (A.row_items: blocks of mpb masks, their items listed in LDS), so
-    // that the heads of a mask run side by side.
-    const bool special = at.x >= A.nblocks;
-    const int nm = special ? A.nspecial : A.nmasks, m0 = A.mask0 + (special ? A.nmasks : 0);
-    const int bm = A.row_items ? A.mpb : special ? wpb : wpb * A.mpb;   // masks of a block
-    const int blk0 = (at.x - (special ? A.nblocks : 0)) * bm, blk1 = min(blk0 + bm, nm);
+    const int nfs = MULTI ? A.nfs : 1, blk = at.x / nfs, lam = at.x - blk * nfs;
+    const int bm = A.row_items ? A.mpb : wpb * A.mpb;   // masks of a block
+    const int blk0 = blk * bm, nm = min(bm, A.nmasks - blk0);
     const int gl = at.group, g = A.group0 + gl;
-    const int nfs = A.nfs;
     // wave-uniform bases; the lane's word is added at each access; flavour planes
-    const double *F = A.F + gl * A.F_gstride + (int64_t)A.F_row0 * NB * 64;
-    const int64_t fpl = A.F_frows * NB * 64, cpl = A.cur_frows * NB * 64, npl = A.nxt_frows * NB * 64;
-    const double *Bn = A.cur + gl * A.cur_gstride;   // level + 1
-    double *Bc = A.nxt + gl * A.nxt_gstride;         // level
+    const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};
+    const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * 64, nfs};   // level + 1
+    double *Bc = A.nxt + gl * A.nxt_gstride;                               // level
     const uint32_t lane8 = (uint32_t)lane * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
     const int cfg = A.lane_cfg[g * 64 + lane];
     const double obar = cfg >= 0 ? A.out_bar[cfg] : 0.0;
     const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane8;
-    const bool start = A.level == 1;
+    const double *GT = A.GT + (int64_t)g * nfs * N * N * 64;
+    const auto grow = [&](int l, int w) {
+        return slot_ld(make_plane(GT + (l * N + N - 1) * N * 64), lane8, (uint32_t)w * 512u);
+    };
 
     if (A.row_items && wave == 0) {
-        // the block's items: lane m takes mask m; its tiles, and the head-b row
-        // unless the mask is special (those rows go before, mask by mask)
-        const int m = lane < blk1 - blk0 ? lane : -1;
-        const uint32_t twos = m >= 0 ? (uint32_t)P.mrec[(int64_t)(m0 + blk0 + m) * kRecInts] >> 16 : 0u;
-        const int cnt = m < 0 ? 0 : (twos & 1u) ? (special ? 1 : 2) + __builtin_popcount(twos & ~1u) : 1;
-        int end = cnt;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int x = __shfl_up(end, d);
-            if (lane >= d) end += x;
-        }
-        for (int k = 0; k < cnt; ++k) item_list[end - cnt + k] = (uint16_t)(m << 4 | k);
-        if (lane == 63) nlist = end;
+        const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + blk0) * kRecInts, nm, lane);
+        if (lane == 63) nlist = n;
     }
-    // special masks: the head-b rows first (every flavour), whose opening
-    // adjoints the tiles' closes of m_b = 1 need
-    for (int pass = special ? 0 : 1; pass < 2; ++pass) {
-        for (int lam = 0; lam < nfs; ++lam) {
-            __syncthreads();   // the previous flavour's accumulator has been flushed
-            for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
-            if (threadIdx.x == 0) next_item = wpb;   // the first wpb items go to the waves in order
-            stage_slots(Gs_all, A.GT + (int64_t)(g * nfs + lam) * N * N * 64, N * N);
-            __syncthreads();
-            const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
-            const plane_t FL = make_plane(F + lam * fpl), BnL = make_plane(Bn + lam * cpl),
-                          BcL = make_plane(Bc + lam * npl);
-            const bool listed = A.row_items && pass;
-            const int nitems = listed ? COS_RF(nlist) : blk1 - blk0;
-            double sacc = 0.0;
-            bool any = false;
-            for (int it = wave; it < nitems; it = claim(&next_item, lane)) {
-                any = true;
-                const int word = listed ? COS_RF((int)item_list[it]) : it << 4, k = word & 15;
-                const MaskRec<N> M = load_rec<N>(P, m0 + blk0 + (word >> 4));
-                const uint32_t twos = M.twos;
-                const uint32_t heads = (twos & 1u) ? (twos & ~1u) : 0u;   // heads >= 1, ascending
-                const int nh = 1 + __builtin_popcount(heads);
-                const uint32_t brow = (uint32_t)nh * kTileB<N>;
-                if (special && pass == 0) {
-                    const double fi = slot_ld(make_plane(F), lane8, M.rb + brow);
-                    const double bi = adj_brow<N, MASK, true, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, lane8, brow, fi,
-                                                              twos == (1u << NB) - 1u ? A.W * obar : 0.0, sg, sacc, {});
-                    slot_st(BcL, lane8, M.rb + brow, bi);
-                    continue;
-                }
-                double tb[3];
-                close_adjoint<N, MASK>(M, Bn, Bc, cpl, npl, off, nfs, A.W, obar, tb);
-                // this item's head slots: all of the mask's, or slot k alone
-                const int s0 = listed ? k : 0, s1 = listed ? k + 1 : nh + 1;
-                uint32_t hs = heads;
-                for (int s = 1; s < s0; ++s) hs &= hs - 1u;
-                for (int s = s0; s < s1 && s < nh; ++s) {
-                    int u = 0;
-                    if (s > 0) {
-                        u = __builtin_ctz(hs);
-                        hs &= hs - 1u;
-                    }
-                    if (!(MASK && empty_plane(u, lam, twos)))
-                        adj_tile<N, MASK, true, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, off, u, (uint32_t)s * kTileB<N>, start, tb,
-                                                sg, sacc, {});
-                }
-                if (!special && (twos & 1u) && s1 > nh)
-                    adj_brow<N, MASK, true, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, lane8, brow, 0.0, tb[2], sg, sacc, {});
-            }
-            if (A.stubs && any) atomicAdd(A.sbar_T + (int64_t)(g * nfs + lam) * 64 + lane, sacc);
-            __syncthreads();
-            double *__restrict__ gb = A.Gbar_T + (int64_t)(g * nfs + lam) * N * N * 64;
-            for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) {
-                const double x = Gb_all[i];
-                if (x != 0.0) atomicAdd(gb + i, x);
-            }
-        }
+    if (threadIdx.x == 0) next_item = wpb;   // the first wpb items go to the waves in order
+    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
+    stage_slots(Gs_all, GT + lam * N * N * 64, N * N);
+    __syncthreads();
+    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+    const plane_t FL = make_plane(Fall.base + lam * Fall.stride), BnL = make_plane(Bn.base + lam * Bn.stride),
+                  BcL = make_plane(Bc + lam * (A.nxt_frows * 64));
+    const int nitems = A.row_items ? COS_RF(nlist) : nm;
+    double sacc = 0.0;
+    bool any = false;
+    for (int it = wave; it < nitems; it = claim(&next_item, lane)) {
+        any = true;
+        const int word = A.row_items ? COS_RF((int)item_list[it]) : it << 4, k = word & 15;
+        const MaskRec<N> M = load_rec<N>(P, A.mask0 + blk0 + (word >> 4));
+        double tb[3];
+        close_adjoint<N, MASK>(M, Bn, grow, off, A.W, obar, tb);
+        // this item's head slots: all of the mask's, or slot k alone
+        adj_heads<N, MULTI, MASK, true, Unordered>(M, gaddr, gbaddr, FL, Fall, BnL, BcL, off, lam, A.row_items ? k : 0,
+                                            A.row_items ? k + 1 : 16, A.level == 1, tb, sg, sacc, {});
+    }
+    if (A.stubs && any) atomicAdd(A.sbar_T + (int64_t)(g * nfs + lam) * 64 + lane, sacc);
+    __syncthreads();
+    double *__restrict__ gb = A.Gbar_T + (int64_t)(g * nfs + lam) * N * N * 64;
+    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) {
+        const double x = Gb_all[i];
+        if (x != 0.0) atomicAdd(gb + i, x);
     }
 }
 
 // ---------------------------------------------------------------------------
 // reverse, deterministic: the same tiles, with an order of summation that
-// depends on nothing but the order n.  A level's masks (and its special masks)
-// are cut into kDetParts fixed parts; one workgroup takes one part of one
-// group, lists its (mask, head) items, deals them to its wavefronts in turn
-// (item i to wavefront i mod kAdjWaves), and lets the items add their dS/dG
-// terms to the LDS accumulator in the order of the list (InTurn): everything
-// else of a tile, 9/10 of its time, still overlaps with other tiles.  The
-// accumulator is added to the part's own slot of a partial buffer (no atomics:
-// one workgroup per slot and level, the levels follow one another on the
-// stream), and det_reduce_kernel sums the parts in order.
+// depends on nothing but the order n.  A level's masks are cut into kDetParts
+// fixed parts; one workgroup takes one part of one group and flavour, lists its
+// (mask, head) items, deals them to its wavefronts in turn (item i to wavefront
+// i mod kAdjWaves), and lets the items add their dS/dG terms to the LDS
+// accumulator in the order of the list (InTurn): everything else of a tile, 9/10
+// of its time, still overlaps with other tiles.  The accumulator is added to the
+// part's own slot of a partial buffer (no atomics: one workgroup per slot and
+// level, the levels follow one another on the stream), and det_reduce_kernel
+// sums the parts in order.
 // Measured (n = 9, 1024 configurations, the reverse levels): 2.87 -> 1.85 ms
 // against one wavefront per slot v, which read every child adjoint n times and
 // kept one row of dS/dG in registers.
 // ---------------------------------------------------------------------------
-template <int N, bool MASK>
+template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const LvlArgs A) {
-    constexpr int NB = N - 1;
     extern __shared__ double lds[];
     double *Gs_all = lds, *Gb_all = lds + N * N * 64;   // as in level_adj_kernel
     __shared__ int turn, nlist;
@@ -910,96 +949,57 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
     __shared__ double sums[kAdjWaves * 64];   // shift terms of the wavefronts
     const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6);   // wave index: uniform
     const DevPlan &P = A.plan;
-    const int part = blockIdx.x;
+    const int nfs = MULTI ? A.nfs : 1, part = blockIdx.x / nfs, lam = blockIdx.x - part * nfs;
     const int lo = (int)(((int64_t)part * A.nmasks) / kDetParts), hi = (int)(((int64_t)(part + 1) * A.nmasks) / kDetParts);
-    const int slo = A.nmasks + (int)(((int64_t)part * A.nspecial) / kDetParts),
-              shi = A.nmasks + (int)(((int64_t)(part + 1) * A.nspecial) / kDetParts);
-    if (lo >= hi && slo >= shi) return;
+    if (lo >= hi) return;
     const int gl = blockIdx.y, g = A.group0 + gl;
-    const int nfs = A.nfs;
-    const double *F = A.F + gl * A.F_gstride + (int64_t)A.F_row0 * NB * 64;
-    const int64_t fpl = A.F_frows * NB * 64, cpl = A.cur_frows * NB * 64, npl = A.nxt_frows * NB * 64;
-    const double *Bn = A.cur + gl * A.cur_gstride;   // level + 1
-    double *Bc = A.nxt + gl * A.nxt_gstride;         // level
+    const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};
+    const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * 64, nfs};   // level + 1
+    double *Bc = A.nxt + gl * A.nxt_gstride;                               // level
     const uint32_t lane8 = (uint32_t)lane * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
     const int cfg = A.lane_cfg[g * 64 + lane];
     const double obar = cfg >= 0 ? A.out_bar[cfg] : 0.0;
     const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane8;
-    const bool start = A.level == 1;
-
-    // pass 0: the head-b rows of the special masks; 1: their tiles; 2: the rest
-    for (int pass = slo < shi ? 0 : 2; pass < (lo < hi ? 3 : 2); ++pass) {
-        const int b0 = pass < 2 ? slo : lo, b1 = pass < 2 ? shi : hi;
-        for (int lam = 0; lam < nfs; ++lam) {
-            __syncthreads();   // the previous accumulator has been read
-            for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
-            stage_slots(Gs_all, A.GT + (int64_t)(g * nfs + lam) * N * N * 64, N * N);
-            const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
-            const plane_t FL = make_plane(F + lam * fpl), BnL = make_plane(Bn + lam * cpl),
-                          BcL = make_plane(Bc + lam * npl);
-            double sacc = 0.0;
-            for (int blk = b0; blk < b1; blk += kAdjListMasks) {
-                __syncthreads();   // the previous block's list has been read
-                if (wave == 0) {
-                    // as in level_adj_kernel; pass 0 lists the head-b rows
-                    const int m = blk + lane < b1 ? lane : -1;
-                    const uint32_t twos = m >= 0 ? (uint32_t)P.mrec[(int64_t)(A.mask0 + blk + m) * kRecInts] >> 16 : 0u;
-                    const int nh = 1 + ((twos & 1u) ? __builtin_popcount(twos & ~1u) : 0);
-                    const int cnt = m < 0 ? 0 : pass == 0 ? 1 : nh + (pass == 2 && (twos & 1u) ? 1 : 0);
-                    int end = cnt;
-#pragma unroll
-                    for (int d = 1; d < 64; d <<= 1) {
-                        const int x = __shfl_up(end, d);
-                        if (lane >= d) end += x;
-                    }
-                    for (int k = 0; k < cnt; ++k) item_list[end - cnt + k] = (uint16_t)(m << 4 | (pass ? k : nh));
-                    if (lane == 63) nlist = end;
-                    if (lane == 0) turn = 0;
-                }
-                __syncthreads();
-                const int nitems = COS_RF(nlist);
-                for (int it = wave; it < nitems; it += kAdjWaves) {
-                    const int word = COS_RF((int)item_list[it]), k = word & 15;
-                    const MaskRec<N> M = load_rec<N>(P, A.mask0 + blk + (word >> 4));
-                    const uint32_t heads = (M.twos & 1u) ? (M.twos & ~1u) : 0u;
-                    const uint32_t hb = (uint32_t)k * kTileB<N>;
-                    const InTurn order{(lds_int *)&turn, it};
-                    double tb[3];
-                    if (pass == 0) {
-                        const double fi = slot_ld(make_plane(F), lane8, M.rb + hb);
-                        const double bi = adj_brow<N, MASK, true, InTurn>(
-                            M, gaddr, gbaddr, FL, BnL, BcL, lane8, hb, fi,
-                            M.twos == (1u << NB) - 1u ? A.W * obar : 0.0, sg, sacc, order);
-                        slot_st(BcL, lane8, M.rb + hb, bi);
-                        continue;
-                    }
-                    close_adjoint<N, MASK>(M, Bn, Bc, cpl, npl, off, nfs, A.W, obar, tb);
-                    const int u = head_of(heads, k);
-                    if (k == 1 + __builtin_popcount(heads)) {
-                        adj_brow<N, MASK, true, InTurn>(M, gaddr, gbaddr, FL, BnL, BcL, lane8, hb, 0.0, tb[2], sg, sacc,
-                                                        order);
-                    } else if (!(MASK && empty_plane(u, lam, M.twos))) {
-                        adj_tile<N, MASK, true, InTurn>(M, gaddr, gbaddr, FL, BnL, BcL, off, u, hb, start, tb, sg, sacc,
-                                                        order);
-                    } else {
-                        order.wait();
-                        order.done();
-                    }
-                }
-            }
-            if (A.stubs) sums[wave * 64 + lane] = sacc;
-            __syncthreads();
-            // this part's slot of the partial sums (one workgroup per slot and level)
-            const int64_t at = ((int64_t)part * A.det_groups + g) * nfs + lam;
-            double *gp = A.Gbar_T + at * N * N * 64;
-            for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) gp[i] += Gb_all[i];
-            if (A.stubs && wave == 0) {
-                double x = 0.0;
-                for (int k = 0; k < kAdjWaves; ++k) x += sums[k * 64 + lane];
-                A.sbar_T[at * 64 + lane] += x;
-            }
+    const double *GT = A.GT + (int64_t)g * nfs * N * N * 64;
+    const auto grow = [&](int l, int w) {
+        return slot_ld(make_plane(GT + (l * N + N - 1) * N * 64), lane8, (uint32_t)w * 512u);
+    };
+    const plane_t FL = make_plane(Fall.base + lam * Fall.stride), BnL = make_plane(Bn.base + lam * Bn.stride),
+                  BcL = make_plane(Bc + lam * (A.nxt_frows * 64));
+    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
+    stage_slots(Gs_all, GT + lam * N * N * 64, N * N);
+    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+    double sacc = 0.0;
+    for (int blk = lo; blk < hi; blk += kAdjListMasks) {
+        __syncthreads();   // the previous block's list has been read
+        if (wave == 0) {
+            const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + blk) * kRecInts, min(kAdjListMasks, hi - blk),
+                                     lane);
+            if (lane == 63) nlist = n;
+            if (lane == 0) turn = 0;
         }
+        __syncthreads();
+        const int nitems = COS_RF(nlist);
+        for (int it = wave; it < nitems; it += kAdjWaves) {
+            const int word = COS_RF((int)item_list[it]), k = word & 15;
+            const MaskRec<N> M = load_rec<N>(P, A.mask0 + blk + (word >> 4));
+            double tb[3];
+            close_adjoint<N, MASK>(M, Bn, grow, off, A.W, obar, tb);
+            adj_heads<N, MULTI, MASK, true, InTurn>(M, gaddr, gbaddr, FL, Fall, BnL, BcL, off, lam, k, k + 1, A.level == 1, tb, sg,
+                                             sacc, InTurn{(lds_int *)&turn, it});
+        }
+    }
+    if (A.stubs) sums[wave * 64 + lane] = sacc;
+    __syncthreads();
+    // this part's slot of the partial sums (one workgroup per slot and level)
+    const int64_t slot = ((int64_t)part * A.det_groups + g) * nfs + lam;
+    double *gp = A.Gbar_T + slot * N * N * 64;
+    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) gp[i] += Gb_all[i];
+    if (A.stubs && wave == 0) {
+        double x = 0.0;
+        for (int k = 0; k < kAdjWaves; ++k) x += sums[k * 64 + lane];
+        A.sbar_T[slot * 64 + lane] += x;
     }
 }
 
@@ -1130,16 +1130,16 @@ static hipError_t allow_lds(const void *fn, size_t bytes) {
 hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s) {
     const int n = a.plan.n;
     const size_t shm = 2 * (size_t)n * n * 64 * sizeof(double);
-    const dim3 grid((unsigned)kDetParts, (unsigned)ngroups), block(64 * kAdjWaves);
+    const dim3 grid((unsigned)(kDetParts * a.nfs), (unsigned)ngroups), block(64 * kAdjWaves);
     switch (n) {
 #define COS_DET_CASE(K)                                                                              \
     case K: {                                                                                        \
-        const void *fn = a.mask_only ? (const void *)level_adj_det_kernel<K, true>                   \
-                                     : (const void *)level_adj_det_kernel<K, false>;                 \
-        hipError_t e = allow_lds(fn, shm);                                                           \
-        if (e != hipSuccess) return e;                                                               \
-        if (a.mask_only) hipLaunchKernelGGL((level_adj_det_kernel<K, true>), grid, block, shm, s, a); \
-        else hipLaunchKernelGGL((level_adj_det_kernel<K, false>), grid, block, shm, s, a);           \
+        void (*fn)(LvlArgs) = a.mask_only   ? level_adj_det_kernel<K, true, true>             \
+                              : a.nfs > 1 ? level_adj_det_kernel<K, true, false>              \
+                                          : level_adj_det_kernel<K, false, false>;            \
+        hipError_t e = allow_lds((const void *)fn, shm);                                      \
+        if (e != hipSuccess) return e;                                                        \
+        hipLaunchKernelGGL(fn, grid, block, shm, s, a);                                       \
         break;                                                                                       \
     }
         COS_DET_CASE(2) COS_DET_CASE(3) COS_DET_CASE(4) COS_DET_CASE(5)
@@ -1172,17 +1172,16 @@ hipError_t launch_level_adj(LvlArgs a, int ngroups, hipStream_t s) {
     const int n = a.plan.n, wpa = kAdjWaves;
     const size_t shm = 2 * (size_t)n * n * 64 * sizeof(double);
     if (a.row_items && a.mpb > kAdjListMasks) return hipErrorInvalidValue;
-    const int sm = a.row_items ? a.mpb : wpa;   // special masks of a block
-    const dim3 grid = xcd_grid(a, a.nblocks + (a.nspecial + sm - 1) / sm, ngroups);
+    const dim3 grid = xcd_grid(a, a.nblocks * a.nfs, ngroups);
     switch (n) {
 #define COS_ADJ_CASE(K)                                                                           \
     case K: {                                                                                     \
-        const void *fn = a.mask_only ? (const void *)level_adj_kernel<K, true>                    \
-                                     : (const void *)level_adj_kernel<K, false>;                  \
-        hipError_t e = allow_lds(fn, shm);                                                        \
-        if (e != hipSuccess) return e;                                                            \
-        if (a.mask_only) hipLaunchKernelGGL((level_adj_kernel<K, true>), grid, dim3(64 * wpa), shm, s, a);  \
-        else hipLaunchKernelGGL((level_adj_kernel<K, false>), grid, dim3(64 * wpa), shm, s, a);             \
+        void (*fn)(LvlArgs) = a.mask_only   ? level_adj_kernel<K, true, true>              \
+                              : a.nfs > 1 ? level_adj_kernel<K, true, false>               \
+                                          : level_adj_kernel<K, false, false>;             \
+        hipError_t e = allow_lds((const void *)fn, shm);                                   \
+        if (e != hipSuccess) return e;                                                     \
+        hipLaunchKernelGGL(fn, grid, dim3(64 * wpa), shm, s, a);                           \
         break;                                                                                    \
     }
         COS_ADJ_CASE(2) COS_ADJ_CASE(3) COS_ADJ_CASE(4) COS_ADJ_CASE(5)
@@ -1195,39 +1194,38 @@ hipError_t launch_level_adj(LvlArgs a, int ngroups, hipStream_t s) {
 }
 
 // LDS of a forward workgroup: G, and the close sums of the heads of a split
-// block (or of a special mask, at most n - 1)
-size_t fwd_lds_bytes(int n, int split_masks, int nspecial) {
-    const size_t items = std::max(split_masks * n, nspecial ? n - 1 : 0);
-    return ((size_t)n * n + 3 * items) * 512;
-}
+// block (the last level's one mask: n head slots)
+size_t fwd_lds_bytes(int n, int split_masks) { return ((size_t)n * n + 3 * (size_t)split_masks * n) * 512; }
 
 hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s) {
     const int n = a.plan.n;
     if (wpb < 1 || wpb > 16) return hipErrorInvalidValue;
     if (a.split && a.mpb > kSplitMasks) return hipErrorInvalidValue;
     const bool multi = a.nfs > 1;
-    const size_t shm = fwd_lds_bytes(n, a.split ? a.mpb : 0, a.nspecial);
-    const dim3 grid = xcd_grid(a, a.nblocks + a.nspecial, ngroups);
+    const bool last = a.level == 2 * (n - 1);
+    const size_t shm = fwd_lds_bytes(n, last ? 1 : a.split ? a.mpb : 0);
+    const dim3 grid = last ? dim3((unsigned)ngroups) : xcd_grid(a, a.nblocks * a.nfs, ngroups);
+    const void *fn = nullptr;
     switch (n) {
-#define COS_FWD_CASE(K)                                                                                    \
-    case K: {                                                                                              \
-        const void *fn = a.mask_only ? (const void *)level_fwd_kernel<K, true, true>                       \
-                         : multi     ? (const void *)level_fwd_kernel<K, true, false>                      \
-                                     : (const void *)level_fwd_kernel<K, false, false>;                    \
-        hipError_t e = allow_lds(fn, shm);                                                                 \
-        if (e != hipSuccess) return e;                                                                     \
-        if (a.mask_only) hipLaunchKernelGGL((level_fwd_kernel<K, true, true>), grid, dim3(64 * wpb), shm, s, a); \
-        else if (multi) hipLaunchKernelGGL((level_fwd_kernel<K, true, false>), grid, dim3(64 * wpb), shm, s, a); \
-        else hipLaunchKernelGGL((level_fwd_kernel<K, false, false>), grid, dim3(64 * wpb), shm, s, a);           \
-        break;                                                                                             \
-    }
+#define COS_FWD_KERNEL(NAME, K)                                    \
+    a.mask_only ? (const void *)NAME<K, true, true>                \
+    : multi     ? (const void *)NAME<K, true, false>               \
+                : (const void *)NAME<K, false, false>
+#define COS_FWD_CASE(K)                                                                              \
+    case K:                                                                                          \
+        fn = last ? (COS_FWD_KERNEL(level_last_kernel, K)) : (COS_FWD_KERNEL(level_fwd_kernel, K));  \
+        break;
         COS_FWD_CASE(2) COS_FWD_CASE(3) COS_FWD_CASE(4) COS_FWD_CASE(5)
         COS_FWD_CASE(6) COS_FWD_CASE(7) COS_FWD_CASE(8) COS_FWD_CASE(9)
         COS_FWD_CASE(10) COS_FWD_CASE(11) COS_FWD_CASE(12)
 #undef COS_FWD_CASE
+#undef COS_FWD_KERNEL
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    hipError_t e = allow_lds(fn, shm);
+    if (e != hipSuccess) return e;
+    void *args[] = {(void *)&a};
+    return hipLaunchKernel(fn, grid, dim3(64 * wpb), args, shm, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1270,13 +1268,12 @@ struct SmallCtx {
 // states of level l: all levels kept (reverse sweep) or two windows
 template <int N>
 __device__ __forceinline__ double *small_level(const SmallCtx<N> &C, bool keep, int l, int64_t *plane) {
-    constexpr int NB = N - 1;
     if (keep) {
-        *plane = C.A.plan.total_rows * NB * 64;
+        *plane = C.A.plan.total_rows * 64;
         const cint32 *p = (const cint32 *)(C.A.plan.levels + l);
-        return C.A.F + C.gl * C.A.F_gstride + (int64_t)p[0] * NB * 64;
+        return C.A.F + C.gl * C.A.F_gstride + (int64_t)p[0] * 64;
     }
-    *plane = (int64_t)C.A.plan.max_rows * NB * 64;
+    *plane = (int64_t)C.A.plan.max_rows * 64;
     return C.A.win + C.gl * C.A.win_gstride + (l & 1) * (*plane) * C.nfs;
 }
 
@@ -1296,87 +1293,77 @@ __device__ __forceinline__ void small_stage(const SmallCtx<N> &C) {
 }
 
 // every forward level; writes S
-template <int N, bool MASK>
+template <int N, bool MULTI, bool MASK>
 __device__ __forceinline__ void small_forward(const SmallCtx<N> &C, bool keep) {
     constexpr int NB = N - 1;
     const SmallArgs &A = C.A;
     const int wpb = blockDim.x >> 6, nfs = C.nfs, lane = C.lane;
     const cint32 *rounds = C.script + kSmallHeader, *items = rounds + C.nrounds * kSmallRoundInts;
-    double tfull = 0.0;   // close sum of the full mask (the wavefront that owns it)
     for (int r = 0; r < C.nrounds; ++r) {
         const cint32 *R = rounds + r * kSmallRoundInts;
         const int level = R[0], item0 = R[1], ni = R[2], close0 = R[3], nc = R[4];
         int64_t cpl, npl;
         double *cur = small_level<N>(C, keep, level, &cpl), *nxt = small_level<N>(C, keep, level + 1, &npl);
+        const Planes all{cur, cpl, nfs};
         const bool start = level == 1;
         for (int q = C.wave; q < ni * nfs; q += wpb) {
             const int lam = q / ni, i = q - lam * ni;
             const uint32_t word = (uint32_t)items[item0 + i];
             const int k = (word >> 4) & 15, u = word & 15;
             const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
-            const plane_t curL = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
+            const plane_t own = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
             const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
             const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
             double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
             if (u == kSmallBrow) {
-                const bool special = special_mask(M.ones, M.twos);
-                const double inj = special ? slot_ld(make_plane(cur), C.lane8, M.rb + k * kTileB<N>) : 0.0;
-                fwd_brow<N, MASK, false>(M, gaddr, curL, nxtL, C.lane8, k * kTileB<N>, inj, sg, T[2]);
+                T[2] = fwd_brow<N, MASK, false>(M, gaddr, own, all, nxtL, C.lane8, k * kTileB<N>, sg);
             } else if (!(MASK && empty_plane(u, lam, M.twos))) {
-                fwd_tile<N, MASK, false>(M, gaddr, curL, nxtL, C.off, u, k * kTileB<N>, start, sg, T, dext);
+                fwd_tile<N, MULTI, MASK, false>(M, gaddr, own, all, nxtL, C.off, u, k * kTileB<N>, start, sg, T, dext);
             }
-            // m_0 = 1: vertex 0's second visit, on the slot the next cycle opens on
-            if (!MASK && !(M.twos & 1u)) {
-                const uint32_t dst = M.crb[0];
-#pragma unroll
-                for (int j = 0; j < 3; ++j) slot_st(nxtL, C.off[j], dst, dext[j]);
+            if (!(M.twos & 1u)) {   // the mask's only head
+                close_mask<N, MULTI, MASK>(M, A.W, own, nxtL, C.off, T, dext);
+                continue;
             }
             double *t = C.Ts + (lam * kSmallItems + i) * 192 + lane;
 #pragma unroll
             for (int j = 0; j < 3; ++j) t[j * 64] = T[j];
         }
         __syncthreads();
-        // one wavefront per mask: t_m = W sum over heads and flavours
-        for (int c = C.wave; c < nc; c += wpb) {
+        // one wavefront per mask and flavour: W sum over its heads
+        for (int q = C.wave; q < nc * nfs; q += wpb) {
+            const int lam = q / nc, c = q - lam * nc;
             const uint32_t word = (uint32_t)items[close0 + c];
             const int first = (word >> 4) & 15, cnt = word & 15;
             const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
-            const bool full = M.twos == (1u << NB) - 1u;
+            if (!(M.twos & 1u)) continue;
             double T[3] = {0.0, 0.0, 0.0};
+            const double dext[3] = {0.0, 0.0, 0.0};
+            for (int i = first; i < first + cnt; ++i) {
+                const double *t = C.Ts + (lam * kSmallItems + i) * 192 + lane;
+#pragma unroll
+                for (int j = 0; j < 3; ++j) T[j] += t[j * 64];
+            }
+            const plane_t own = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
+            close_mask<N, MULTI, MASK>(M, A.W, own, nxtL, C.off, T, dext);
+        }
+        if (level == 2 * NB && C.wave == 0) {
+            // the full mask: S / W, as level_last_kernel adds it up
+            double T1 = 0.0, T2 = 0.0, gbb = 0.0;
             for (int lam = 0; lam < nfs; ++lam) {
-                double s[3] = {0.0, 0.0, 0.0};
-                for (int i = first; i < first + cnt; ++i) {
+                double s1 = 0.0, s2 = 0.0;
+                for (int i = 0; i < ni; ++i) {
                     const double *t = C.Ts + (lam * kSmallItems + i) * 192 + lane;
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) s[j] += t[j * 64];
+                    s1 += t[64];
+                    s2 += t[128];
                 }
-#pragma unroll
-                for (int j = 0; j < 3; ++j) T[j] += s[j];
-                if (R[5]) tfull += s[2];   // the full mask's head-b row, after its tiles
+                T1 += A.W * s1;
+                T2 += s2;
+                gbb += C.Gs[(lam * N * N + NB * N + NB) * 64 + lane];
             }
-            if (R[5]) continue;
-            if (special_mask(M.ones, M.twos)) {
-                const uint32_t brow = (1u + (uint32_t)__builtin_popcount(M.twos & ~1u)) * kTileB<N>;
-                slot_st(make_plane(cur), C.lane8, M.rb + brow, A.W * T[1]);
-                if (full) tfull = T[2];
-                continue;
-            }
-            const int h = __builtin_ctz(M.ones);
-            const uint32_t dst = child_rows<N>(M, h) + open_slot<N>(h, M.twos);
-            for (int k = 0; k < nfs; ++k) {
-                if (MASK && h == 0 && k == 0) continue;
-                const plane_t d = make_plane(nxt + k * npl);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const double x = (!MASK && h == 0) ? slot_ld(d, C.off[j], dst) : 0.0;
-                    slot_st(d, C.off[j], dst, __builtin_fma(A.W, T[j], x));
-                }
-            }
+            if (C.cfg >= 0 && A.out) A.out[C.cfg] = A.W * __builtin_fma(T1, gbb, T2);
         }
         __syncthreads();
     }
-    // the last two rounds close the full mask, each with one mask: wavefront 0
-    if (C.wave == 0 && C.cfg >= 0 && A.out) A.out[C.cfg] = A.W * tfull;
 }
 
 template <int N>
@@ -1390,18 +1377,18 @@ __device__ __forceinline__ SmallCtx<N> small_ctx(const SmallArgs &A, double *lds
                        slot < A.count ? A.order[slot] : -1, lane8, {lane8, lane8 + 512u, lane8 + 1024u}};
 }
 
-template <int N, bool MASK>
+template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kSmallWaves) small_fwd_kernel(const SmallArgs A) {
     extern __shared__ double lds[];
     const SmallCtx<N> C = small_ctx<N>(A, lds, (uint32_t)A.nfs * kSmallItems * 192u);
     small_stage<N>(C);
     __syncthreads();
-    small_forward<N, MASK>(C, false);
+    small_forward<N, MULTI, MASK>(C, false);
 }
 
 // forward (every level kept) and reverse; writes S, dS/dG and dS/dsigma.  The
 // accumulators take the place of the forward's close sums in LDS.
-template <int N, bool MASK>
+template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const SmallArgs A) {
     constexpr int NB = N - 1;
     extern __shared__ double lds[];
@@ -1411,7 +1398,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const Small
     double *Gb = C.Ts, *sb = C.sig + nfs * 64;
     small_stage<N>(C);
     __syncthreads();
-    small_forward<N, MASK>(C, true);
+    small_forward<N, MULTI, MASK>(C, true);
     const int n2 = nfs * N * N;
     for (int e = C.wave; e < n2; e += wpb) Gb[e * 64 + lane] = 0.0;
     for (int l = C.wave; l < nfs; l += wpb) sb[l * 64 + lane] = 0.0;
@@ -1421,42 +1408,27 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const Small
     for (int l = 2 * NB; l >= 1; --l) {
         int64_t fpl, cpl, npl;
         const double *F = small_level<N>(C, true, l, &fpl);
-        const double *Bn = small_level<N>(C, false, l + 1, &cpl);
+        const double *B1 = small_level<N>(C, false, l + 1, &cpl);
         double *Bc = small_level<N>(C, false, l, &npl);
-        const int item0 = lev[3 * l], ni = lev[3 * l + 1], nsb = lev[3 * l + 2];
-        const bool start = l == 1;
-        // the special masks' head-b rows, then everything else
-        for (int part = nsb ? 0 : 1; part < 2; ++part) {
-            const int i0 = part ? item0 : item0 + ni, n = part ? ni : nsb;
-            for (int q = C.wave; q < n * nfs; q += wpb) {
-                const int lam = q / n;
-                const uint32_t word = (uint32_t)items[i0 + (q - lam * n)];
-                const int k = (word >> 4) & 15, u = word & 15;
-                const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
-                const plane_t FL = make_plane(F + lam * fpl), BnL = make_plane(Bn + lam * cpl),
-                              BcL = make_plane(Bc + lam * npl);
-                const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
-                const uint32_t gbaddr = lds_addr(Gb + lam * N * N * 64) + C.lane8;
-                const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
-                const uint32_t hb = k * kTileB<N>;
-                double sacc = 0.0;
-                if (part == 0) {
-                    const double fi = slot_ld(make_plane(F), C.lane8, M.rb + hb);
-                    const double bi = adj_brow<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.lane8, hb, fi,
-                                                        M.twos == (1u << NB) - 1u ? A.W * obar : 0.0, sg, sacc, {});
-                    slot_st(BcL, C.lane8, M.rb + hb, bi);
-                } else {
-                    double tb[3];
-                    close_adjoint<N, MASK>(M, Bn, Bc, cpl, npl, C.off, nfs, A.W, obar, tb);
-                    if (u == kSmallBrow)
-                        adj_brow<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.lane8, hb, 0.0, tb[2], sg, sacc, {});
-                    else if (!(MASK && empty_plane(u, lam, M.twos)))
-                        adj_tile<N, MASK, false, Unordered>(M, gaddr, gbaddr, FL, BnL, BcL, C.off, u, hb, start, tb, sg, sacc, {});
-                }
-                if (A.stub) atomicAdd(sb + lam * 64 + lane, sacc);
-            }
-            __syncthreads();
+        const Planes Fall{F, fpl, nfs}, Bn{B1, cpl, nfs};
+        const int item0 = lev[2 * l], ni = lev[2 * l + 1];
+        for (int q = C.wave; q < ni * nfs; q += wpb) {
+            const int lam = q / ni;
+            const uint32_t word = (uint32_t)items[item0 + (q - lam * ni)];
+            const int k = (word >> 4) & 15;
+            const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
+            const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
+            const uint32_t gbaddr = lds_addr(Gb + lam * N * N * 64) + C.lane8;
+            const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
+            double sacc = 0.0, tb[3];
+            close_adjoint<N, MASK>(M, Bn, [&](int l, int w) { return C.Gs[((l * N + N - 1) * N + w) * 64 + lane]; }, C.off, A.W,
+                                   obar, tb);
+            adj_heads<N, MULTI, MASK, false, Unordered>(M, gaddr, gbaddr, make_plane(F + lam * fpl), Fall,
+                                                 make_plane(B1 + lam * cpl), make_plane(Bc + lam * npl), C.off, lam, k,
+                                                 k + 1, l == 1, tb, sg, sacc, {});
+            if (A.stub) atomicAdd(sb + lam * 64 + lane, sacc);
         }
+        __syncthreads();
     }
     if (C.cfg < 0) return;
     double *out = A.G_bar + (A.Goff ? A.Goff[C.cfg] : (int64_t)C.cfg * n2);
@@ -1473,23 +1445,23 @@ size_t small_lds_bytes(int n, int nfs, bool reverse) {
 hipError_t launch_small(const SmallArgs &a, bool reverse, int ngroups, hipStream_t s) {
     const size_t shm = small_lds_bytes(a.plan.n, a.nfs, reverse);
     const dim3 grid((unsigned)ngroups), block(64 * kSmallWaves);
-    const void *fn = nullptr;
+    void (*fn)(SmallArgs) = nullptr;
     switch (a.plan.n) {
 #define COS_SMALL_CASE(K)                                                                            \
     case K:                                                                                          \
-        fn = reverse ? (a.mask_only ? (const void *)small_adj_kernel<K, true>                        \
-                                    : (const void *)small_adj_kernel<K, false>)                      \
-                     : (a.mask_only ? (const void *)small_fwd_kernel<K, true>                        \
-                                    : (const void *)small_fwd_kernel<K, false>);                     \
+        fn = reverse ? (a.mask_only ? small_adj_kernel<K, true, true>                                \
+                        : a.nfs > 1 ? small_adj_kernel<K, true, false> : small_adj_kernel<K, false, false>)\
+                     : (a.mask_only ? small_fwd_kernel<K, true, true>                                \
+                        : a.nfs > 1 ? small_fwd_kernel<K, true, false> : small_fwd_kernel<K, false, false>);\
         break;
         COS_SMALL_CASE(2) COS_SMALL_CASE(3) COS_SMALL_CASE(4) COS_SMALL_CASE(5)
 #undef COS_SMALL_CASE
         default: return hipErrorInvalidValue;
     }
-    hipError_t e = allow_lds(fn, shm);
+    hipError_t e = allow_lds((const void *)fn, shm);
     if (e != hipSuccess) return e;
-    void *args[] = {(void *)&a};
-    return hipLaunchKernel(fn, grid, block, args, shm, s);
+    hipLaunchKernelGGL(fn, grid, block, shm, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace libcos

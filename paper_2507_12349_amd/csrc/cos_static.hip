@@ -30,7 +30,7 @@ struct StaticDevice {
     bool ready = false;
     int ncu = 0;
     char *base = nullptr;         // device address of `scratch` on this device
-    DevPlan plans[COS_STATIC_NMAX + 1]{};
+    DevPlan plans[2][COS_STATIC_NMAX + 1]{};   // for one flavour slot, for several
     size_t call_offset = 0;       // first byte of the per-call region
 };
 
@@ -51,9 +51,10 @@ cos_status setup_device(int dev, StaticDevice *sd) {
                       hipGetErrorString(e));
     char *base = (char *)ptr;
     size_t off = 0;
-    for (int n = 1; n <= COS_STATIC_NMAX; ++n) {
+    for (int i = 0; i < 2 * COS_STATIC_NMAX; ++i) {
+        const int n = 1 + i / 2, multi = i & 1;
         PlanTables t;
-        if (cos_status st = plan_tables(n, true, &t)) return st;
+        if (cos_status st = plan_tables(n, true, multi != 0, &t)) return st;
         const size_t mb = t.mrec_ints * sizeof(int32_t), lb = t.nlevels * sizeof(int4);
         const size_t sb = t.script_ints * sizeof(int32_t);
         if (off + up256(mb) + up256(lb) + up256(sb) > (size_t)COS_STATIC_SCRATCH_BYTES)
@@ -65,7 +66,7 @@ cos_status setup_device(int dev, StaticDevice *sd) {
         if (e != hipSuccess)
             return report(COS_EDEVICE, "upload of the state tables into the static scratch failed: %s",
                           hipGetErrorString(e));
-        DevPlan &p = sd->plans[n];
+        DevPlan &p = sd->plans[multi][n];
         p.mrec = (const int32_t *)(base + off);
         p.levels = (const int4 *)(base + off + up256(mb));
         p.n = n;
@@ -112,10 +113,11 @@ extern "C" cos_status cos_connected_sum_static(int32_t nconf, int32_t n, int32_t
     }
     // carve the per-call region: schedule, packed inputs, lane map, windows
     const int nfs = variant == COS_FLAVOUR ? nflav : 1;
-    const FixedSizes z = fixed_sizes(nconf, n, nfs, sd->plans[n].max_rows);
+    const DevPlan &plan = sd->plans[nfs > 1][n];
+    const FixedSizes z = fixed_sizes(nconf, n, nfs, plan.max_rows);
     size_t off = sd->call_offset;
     FixedWorkspace ws;
-    ws.plan = sd->plans[n];
+    ws.plan = plan;
     ws.order = (int32_t *)(sd->base + off);
     off += up256((size_t)z.order_ints * 4);
     ws.GT = (double *)(sd->base + off);

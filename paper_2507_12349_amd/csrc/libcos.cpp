@@ -90,7 +90,7 @@ struct HostPlan {
     std::vector<int32_t> masks;
     std::vector<int4> levels;       // [nlev + 2]
     std::vector<int32_t> mrec;      // [masks][rec_ints]
-    std::vector<int32_t> special;   // level kernels' tables: special masks per level (the last ones of it)
+    std::vector<int32_t> special;   // level kernels' tables: special masks per level
     std::vector<int32_t> script;    // small orders: the one-launch sweeps' table
     int nlev = 0;                   // levels (launches of a sweep)
     int slots = 0;                  // slots per row
@@ -178,11 +178,12 @@ void build_script(HostPlan &P);
 
 // The level kernels' tables (tiles of three rows over the first n - 1 vertices;
 // see cos_internal.hpp and cos_level.hip).  Order 1 has no levels (it runs in
-// closed form) and keeps one row, so that its workspaces are not empty.
-void build_host_plan_tiles(int n, HostPlan &P) {
+// closed form) and keeps one row, so that its workspaces are not empty.  multi:
+// for batches of several flavours.
+void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
     const int nb = n - 1, N3 = pow3(nb);
     P.n = n;
-    P.slots = std::max(nb, 1);
+    P.slots = 1;
     P.nlev = 2 * nb;
     P.levels.assign(P.nlev + 2, make_int4(0, 0, 0, 0));
     P.special.assign(P.nlev + 2, 0);
@@ -193,7 +194,7 @@ void build_host_plan_tiles(int n, HostPlan &P) {
     }
     P.rowbase.assign(N3, -1);
     P.minfo.assign(N3, 0);
-    std::vector<std::vector<int32_t>> plain(P.nlev + 2), special(P.nlev + 2);
+    std::vector<std::vector<int32_t>> bylevel(P.nlev + 2);
     for (int code = 0; code < N3; ++code) {
         uint32_t ones = 0, twos = 0;
         int c = code, lvl = 0;
@@ -206,37 +207,42 @@ void build_host_plan_tiles(int n, HostPlan &P) {
         }
         P.minfo[code] = ones | (twos << 16);
         if (!((ones | twos) & 1u)) continue;   // vertex 0 is always visited
-        ((twos & 1u) && !ones ? special : plain)[lvl].push_back(code);
+        bylevel[lvl].push_back(code);
     }
+    const int extra = multi ? 3 : 0;   // slots in front of a mask with m_0 = 2
     for (int l = 1; l <= P.nlev; ++l) {
-        int r = 0;
+        int64_t r = 0;
         const int mask0 = (int)P.masks.size();
-        for (auto *list : {&plain[l], &special[l]})
-            for (int code : *list) {
-                const uint32_t twos = P.minfo[code] >> 16;
-                P.rowbase[code] = r;
-                P.masks.push_back(code);
-                // three rows per head, and the one row of head n - 1 once vertex 0 is full
-                r += (twos & 1u) ? 3 * (1 + __builtin_popcount(twos & ~1u)) + 1 : 3;
+        for (int code : bylevel[l]) {
+            const uint32_t ones = P.minfo[code] & 0xffffu, twos = P.minfo[code] >> 16;
+            P.masks.push_back(code);
+            // three rows per head, and the one row of head n - 1 once vertex 0 is full
+            if (twos & 1u) {
+                P.rowbase[code] = (int32_t)(r + extra);
+                r += extra + (3 * (1 + __builtin_popcount(twos & ~1u)) + 1) * nb;
+                if (!ones) ++P.special[l];
+            } else {
+                P.rowbase[code] = (int32_t)r;
+                r += 3 * nb;
             }
+        }
         const int nm = (int)P.masks.size() - mask0;
-        P.levels[l] = make_int4((int)P.total_rows, r, mask0, nm);
-        P.special[l] = (int32_t)special[l].size();
+        P.levels[l] = make_int4((int)P.total_rows, (int)r, mask0, nm);
         P.total_rows += r;
-        P.max_rows = std::max(P.max_rows, r);
+        P.max_rows = std::max(P.max_rows, (int32_t)r);
         P.max_masks = std::max(P.max_masks, nm);
     }
     P.levels[P.nlev + 1] = make_int4((int)P.total_rows, 0, (int)P.masks.size(), 0);
     P.mrec.assign(P.masks.size() * kRecInts, 0);
-    const uint32_t row_bytes = (uint32_t)nb * 512u;   // 832 MB per level and flavour at n = 12
+    // (byte offsets: at most 0.86 GB per level and flavour, at n = 12)
     for (size_t i = 0; i < P.masks.size(); ++i) {
         const int code = P.masks[i];
         const uint32_t twos = P.minfo[code] >> 16;
         int32_t *r = &P.mrec[i * kRecInts];
         r[0] = (int32_t)P.minfo[code];
-        r[1] = (int32_t)((uint32_t)P.rowbase[code] * row_bytes);
+        r[1] = (int32_t)((uint32_t)P.rowbase[code] * 512u);
         for (int w = 0; w < nb; ++w)
-            if (!((twos >> w) & 1u)) r[2 + w] = (int32_t)((uint32_t)P.rowbase[code + pow3(w)] * row_bytes);
+            if (!((twos >> w) & 1u)) r[2 + w] = (int32_t)((uint32_t)P.rowbase[code + pow3(w)] * 512u);
     }
     if (n <= kSmallMax) build_script(P);
 }
@@ -244,48 +250,35 @@ void build_host_plan_tiles(int n, HostPlan &P) {
 // The table of the one-launch sweeps (see cos_internal.hpp).
 void build_script(HostPlan &P) {
     const int nb = P.n - 1;
-    std::vector<int32_t> rounds, words, levels(3 * (P.nlev + 1), 0);
+    std::vector<int32_t> rounds, words, levels(2 * (P.nlev + 1), 0);
     for (int l = 1; l <= P.nlev; ++l) {
-        const int m0 = P.levels[l].z, nm = P.levels[l].w, nsp = P.special[l];
-        struct Close { int mask, items; };
-        std::vector<int32_t> items, brows;
-        std::vector<Close> closes;
-        for (int i = 0; i < nm; ++i) {
-            const uint32_t twos = P.minfo[P.masks[m0 + i]] >> 16;
-            const uint32_t heads = (twos & 1u) ? (twos & ~1u) : 0u;
-            const size_t before = items.size();
+        const int m0 = P.levels[l].z, nm = P.levels[l].w, item0 = (int)words.size();
+        std::vector<std::pair<int, int>> closes;   // (mask, items)
+        for (int i = m0; i < m0 + nm; ++i) {
+            const uint32_t twos = P.minfo[P.masks[i]] >> 16;
+            const size_t before = words.size();
             int k = 0;
-            items.push_back((m0 + i) << 8 | k++ << 4);
-            for (int h = 1; h < nb; ++h)
-                if ((heads >> h) & 1u) items.push_back((m0 + i) << 8 | k++ << 4 | h);
-            if (twos & 1u) (i < nm - nsp ? items : brows).push_back((m0 + i) << 8 | k << 4 | kSmallBrow);
-            closes.push_back({m0 + i, (int)(items.size() - before)});
+            words.push_back(i << 8 | k++ << 4);
+            if (twos & 1u) {
+                for (int h = 1; h < nb; ++h)
+                    if ((twos >> h) & 1u) words.push_back(i << 8 | k++ << 4 | h);
+                words.push_back(i << 8 | k << 4 | kSmallBrow);
+            }
+            closes.push_back({i, (int)(words.size() - before)});
         }
-        const int item0 = (int)words.size();
-        words.insert(words.end(), items.begin(), items.end());
-        words.insert(words.end(), brows.begin(), brows.end());
-        levels[3 * l] = item0;
-        levels[3 * l + 1] = (int32_t)items.size();
-        levels[3 * l + 2] = (int32_t)brows.size();
+        levels[2 * l] = item0;
+        levels[2 * l + 1] = (int32_t)words.size() - item0;
         // rounds of whole masks
         for (size_t c = 0, at = 0; c < closes.size();) {
             int ni = 0, nc = 0;
             const int close0 = (int)words.size();
-            while (c < closes.size() && ni + closes[c].items <= kSmallItems) {
-                words.push_back(closes[c].mask << 8 | ni << 4 | closes[c].items);
-                ni += closes[c].items;
+            while (c < closes.size() && ni + closes[c].second <= kSmallItems) {
+                words.push_back(closes[c].first << 8 | ni << 4 | closes[c].second);
+                ni += closes[c].second;
                 ++nc, ++c;
             }
-            for (int32_t x : {l, item0 + (int32_t)at, ni, close0, nc, 0}) rounds.push_back(x);
+            for (int32_t x : {l, item0 + (int32_t)at, ni, close0, nc}) rounds.push_back(x);
             at += ni;
-        }
-        // head-b rows of the special masks; the full mask's closes the sum
-        for (size_t at = 0; at < brows.size(); at += kSmallItems) {
-            const int ni = (int)std::min<size_t>(kSmallItems, brows.size() - at), close0 = (int)words.size();
-            const bool last = l == P.nlev;
-            if (last) words.push_back(m0 << 8 | 0 << 4 | 1);
-            for (int32_t x : {l, item0 + (int32_t)(items.size() + at), ni, close0, last ? 1 : 0, last ? 1 : 0})
-                rounds.push_back(x);
         }
     }
     P.script = {(int32_t)(rounds.size() / kSmallRoundInts), (int32_t)words.size()};
@@ -395,7 +388,8 @@ struct DevTables {
 
 std::mutex g_mu;
 // the plain state tables (counts), the labelled ones, the level kernels' tiles
-enum PlanKind { kPlain = 0, kSub = 1, kTiles = 2 };
+// for one and for several flavours
+enum PlanKind { kPlain = 0, kSub = 1, kTiles = 2, kTilesMulti = 3 };
 std::map<std::pair<int, int>, std::shared_ptr<HostPlan>> g_host;   // (n, kind)
 std::map<std::tuple<int, int, int>, DevTables> g_dev;              // (device, n, kind)
 int64_t g_live = 0;   // batch handles alive: they hold pointers into g_dev's tables
@@ -406,11 +400,13 @@ std::shared_ptr<HostPlan> host_plan(int n, PlanKind kind) {
     if (it != g_host.end()) return it->second;
     auto p = std::make_shared<HostPlan>();
     if (kind == kSub) build_host_plan_sub(n, *p);
-    else if (kind == kTiles) build_host_plan_tiles(n, *p);
+    else if (kind != kPlain) build_host_plan_tiles(n, kind == kTilesMulti, *p);
     else build_host_plan(n, *p);
     g_host[key] = p;
     return p;
 }
+
+PlanKind tile_kind(int nfs) { return nfs > 1 ? kTilesMulti : kTiles; }
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -747,7 +743,7 @@ cos_status cos_batch_create(int32_t nconf, const int32_t *n, int32_t nflav, int3
     for (int c = 0; c < nconf; ++c) seen[n[c]] = true;
     for (int k = 1; k <= COS_NMAX; ++k)
         if (seen[k]) {
-            if ((st = device_plan(dev, k, sub ? kSub : kTiles, &b->plans[k]))) return st;
+            if ((st = device_plan(dev, k, sub ? kSub : tile_kind(b->nfs), &b->plans[k]))) return st;
         }
     b->uniform_n = std::all_of(n, n + nconf, [&](int32_t x) { return x == n[0]; });
 
@@ -771,7 +767,7 @@ cos_status cos_batch_create(int32_t nconf, const int32_t *n, int32_t nflav, int3
         if (sub) o.shape.fwd_wpb = 16;   // (2n)^2 matrices in LDS: one workgroup per CU, make it wide
         {
             std::lock_guard<std::mutex> lk(g_mu);
-            o.hp = host_plan(o.n, sub ? kSub : kTiles);
+            o.hp = host_plan(o.n, sub ? kSub : tile_kind(b->nfs));
         }
         gt += (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
         sg += (int64_t)o.ngroups * b->nfs * 64;
@@ -934,7 +930,7 @@ static int fwd_cap(const LaunchShape &sh, int nfs, bool sub) {
 }
 static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu, bool sub) {
     const int cap = fwd_cap(sh, nfs, sub);
-    const int64_t per = ((int64_t)nm * ng) / std::max<int64_t>(1, (int64_t)ncu * 16);
+    const int64_t per = ((int64_t)nm * ng * (sub ? 1 : nfs)) / std::max<int64_t>(1, (int64_t)ncu * 16);
     return (int)std::max<int64_t>(1, std::min<int64_t>(cap, per));
 }
 
@@ -965,8 +961,12 @@ static int64_t level_rows(const HostPlan &p, int a, int c) { return (int64_t)p.l
 // the masks of an unlabelled level
 static void level_masks(const OrderGroup &o, int l, LvlArgs *a) {
     a->mask0 = o.hp->levels[l].z;
-    a->nspecial = o.hp->special[l];
-    a->nmasks = o.hp->levels[l].w - a->nspecial;
+    a->nmasks = o.hp->levels[l].w;
+}
+
+// tiles of a mask of an unlabelled level, on average
+static int level_heads(const OrderGroup &o, int l) {
+    return (int)std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)(o.n - 1) * o.hp->levels[l].w));
 }
 
 // steps of the dynamic programme that the launch of level l does: a labelled
@@ -992,25 +992,17 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
     // three flavours 79 + 46 and 29 + 20.  On the lower levels, and with more
     // masks than that, loading G for fewer masks costs more than it gains (n = 10,
     // three flavours, level 4: 54 -> 107 us)
-    const int heads = (int)std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)o.hp->levels[l].w));
-    a.split = a.nmasks > 0 && 3 * heads >= o.n && (int64_t)a.nmasks * cg <= (int64_t)b->ncu * 8;
+    const int heads = level_heads(o, l);
+    a.split = 3 * heads >= o.n && (int64_t)a.nmasks * b->nfs * cg <= (int64_t)b->ncu * 8;
     if (a.split) {
         // about one head per wavefront of a workgroup, in 80 KB of LDS so that
         // two workgroups fit a CU
         a.mpb = std::max(1, std::min({kSplitMasks, (wpb + heads - 1) / heads, a.nmasks}));
-        while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb, a.nspecial) > 80 * 1024) --a.mpb;
+        while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb) > 80 * 1024) --a.mpb;
         a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
     } else {
         a.mpb = fwd_masks(o.shape, b->nfs, a.nmasks, cg, b->ncu, false);
         a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
-    }
-    if (a.nblocks && a.nspecial && 2 * fwd_lds_bytes(o.n, 0, 0) <= 160 * 1024 &&
-        2 * fwd_lds_bytes(o.n, a.split ? a.mpb : 0, a.nspecial) > 160 * 1024) {
-        // n = 12: the special masks' close sums would leave one workgroup per CU
-        LvlArgs p = a;
-        p.nspecial = 0;
-        HIP_TRY(launch_level_fwd(p, cg, wpb, s));
-        a.nblocks = a.split = 0;
     }
     LAUNCH_STEPS(level_steps(o, l), launch_level_fwd(a, cg, wpb, s));
     return COS_OK;
@@ -1118,9 +1110,9 @@ cos_status cos_connected_sum_batched(cos_batch_t b, const double *d_G, const int
 
 // the split level h of a two-segment reverse sweep that minimises the larger
 // segment (levels 1..h, recomputed, or h+1..2n, stored by the first forward)
-// (a level with special masks cannot be h: their head-b rows get the value
-// their cycle opens with when their own level is processed, and level h is not
-// processed again)
+// (a level with special masks cannot be h: the value with which the cycle of
+// head n - 1 opens there is stored when their own level is processed, and level
+// h is not processed again)
 static int best_split(const HostPlan &p) {
     int best = 0;
     int64_t bv = INT64_MAX;
@@ -1327,13 +1319,13 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 // spreads the heads of its masks over wavefronts, in blocks of
                 // about one (mask, head) item per wavefront (n = 8, 1000
                 // configurations: reverse levels 440 -> 385 us)
-                a.row_items = (int64_t)nm * cg <= (int64_t)b->ncu * per_cu ? 1 : 0;
+                a.row_items = (int64_t)nm * b->nfs * cg <= (int64_t)b->ncu * per_cu ? 1 : 0;
                 if (a.row_items) {
-                    const int64_t tiles = std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)nm));
-                    a.mpb = (int)std::max<int64_t>(1, std::min<int64_t>(kAdjListMasks, (kAdjWaves + tiles - 1) / tiles));
+                    const int heads = level_heads(o, l);
+                    a.mpb = std::min(kAdjListMasks, (kAdjWaves + heads - 1) / heads);
                     a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
                 } else {
-                    a.mpb = adj_masks(o.shape, a.nmasks, cg, b->ncu, per_cu);
+                    a.mpb = adj_masks(o.shape, a.nmasks, cg * b->nfs, b->ncu, per_cu);
                     a.nblocks = (a.nmasks + kAdjWaves * a.mpb - 1) / (kAdjWaves * a.mpb);
                 }
                 LAUNCH_STEPS(level_steps(o, l), launch_level_adj(a, cg, s));
@@ -1796,12 +1788,12 @@ cos_status libcos::report(cos_status s, const char *fmt, ...) {
 
 cos_status libcos::current_device(int *dev, int *ncu) { return check_device(dev, ncu); }
 
-cos_status libcos::plan_tables(int n, bool tiles, PlanTables *out) {
+cos_status libcos::plan_tables(int n, bool tiles, bool multi, PlanTables *out) {
     if (n < 1 || n > COS_NMAX) return fail(COS_ERANGE, "n must be in [1, %d], got %d", COS_NMAX, n);
     std::shared_ptr<HostPlan> p;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        p = host_plan(n, tiles ? kTiles : kPlain);
+        p = host_plan(n, !tiles ? kPlain : multi ? kTilesMulti : kTiles);
     }
     // the plan stays in the process-wide cache, which only cos_release clears
     out->mrec = p->mrec.data();
@@ -1823,7 +1815,7 @@ FixedSizes libcos::fixed_sizes(int nconf, int n, int nfs, int32_t max_rows) {
     z.gt_doubles = ngroups * nfs * n * n * 64;
     z.sig_doubles = ngroups * nfs * 64;
     z.lane_ints = ngroups * 64;
-    z.win_doubles_per_group = 2 * (int64_t)max_rows * nfs * std::max(n - 1, 1) * 64;
+    z.win_doubles_per_group = 2 * (int64_t)max_rows * nfs * 64;
     return z;
 }
 
@@ -1853,7 +1845,7 @@ cos_status libcos::forward_fixed(int dev, int ncu, const FixedWorkspace &ws, int
     o.chunk_fwd = std::max(1, std::min(ws.chunk, o.ngroups));
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        o.hp = host_plan(n, kTiles);
+        o.hp = host_plan(n, tile_kind(b.nfs));
     }
     LAUNCH_TRY(launch_iota(ws.order, nconf, s));
     return forward_order(&b, o, d_G, nullptr, d_stub, cycle_weight, d_out, s);
