@@ -153,6 +153,7 @@ struct LvlArgs {
     // masks)
     int32_t mask0, nmasks, nblocks;
     int32_t split;            // forward: blocks of mpb masks whose heads go to different wavefronts
+    int32_t count;            // configurations of the order
     int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)
     int32_t det_groups;       // deterministic reverse: groups of the order (stride of the partial sums)

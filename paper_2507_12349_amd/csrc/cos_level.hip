@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(1024) level_last_kernel(const LvlArgs A) {
     const int gl = blockIdx.x, g = A.group0 + gl, nfs = MULTI ? A.nfs : 1;
     const Planes all{A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * 64, A.cur_frows * 64, nfs};
     const plane_t nxt = make_plane(A.nxt);   // (nothing is open: never written)
-    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t wl = work_lane(A, g, lane), lane8 = wl * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
     const MaskRec<N> M = load_rec<N>(A.plan, A.mask0);
     const uint32_t heads = M.twos & ~1u, brow = (uint32_t)NB * kTileB<N>;
@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(1024) level_last_kernel(const LvlArgs A) {
         if (MULTI && lam) __syncthreads();
         stage_slots(Gs_all, A.GT + (int64_t)(g * nfs + lam) * N * N * 64, N * N);
         __syncthreads();
-        const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+        const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + wl] : 0.0;
         const plane_t own = make_plane(all.base + lam * all.stride);
         for (int k = wave; k <= NB; k += wpb) {
             double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
@@ -496,7 +496,7 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
     // stored by flavour plane: [flavour][row][v][lane], planes of *_frows slots
     const Planes all{A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * 64, A.cur_frows * 64, nfs};
     double *nxt = A.nxt + gl * A.nxt_gstride + (int64_t)A.nxt_row0 * 64;
-    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t wl = work_lane(A, g, lane), lane8 = wl * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
     const uint32_t gaddr = lds_addr(Gs_all) + lane8;
     const bool start = A.level == 1;
@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
     if (threadIdx.x == 0) next_mask = mb0 + wpb;   // the first wpb masks go to the waves in order
     stage_slots(Gs_all, GT + (int64_t)lam * N * N * 64, N * N);
     __syncthreads();
-    const double sg = sigT ? sigT[lam * 64 + lane] : 0.0;
+    const double sg = sigT ? sigT[lam * 64 + wl] : 0.0;
     const plane_t own = make_plane(all.base + lam * all.stride), nxtL = make_plane(nxt + lam * (A.nxt_frows * 64));
     if (A.split) {
         const int ni = COS_RF(nitems);
@@ -882,11 +882,10 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
     const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};
     const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * 64, nfs};   // level + 1
     double *Bc = A.nxt + gl * A.nxt_gstride;                               // level
-    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t wl = work_lane(A, g, lane), lane8 = wl * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
-    const int cfg = A.lane_cfg[g * 64 + lane];
-    const double obar = cfg >= 0 ? A.out_bar[cfg] : 0.0;
-    const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane8;
+    const double obar = A.out_bar[A.lane_cfg[g * 64 + wl]];
+    const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane * 8u;
     const double *GT = A.GT + (int64_t)g * nfs * N * N * 64;
     const auto grow = [&](int l, int w) {
         return slot_ld(make_plane(GT + (l * N + N - 1) * N * 64), lane8, (uint32_t)w * 512u);
@@ -900,7 +899,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
     for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
     stage_slots(Gs_all, GT + lam * N * N * 64, N * N);
     __syncthreads();
-    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + wl] : 0.0;
     const plane_t FL = make_plane(Fall.base + lam * Fall.stride), BnL = make_plane(Bn.base + lam * Bn.stride),
                   BcL = make_plane(Bc + lam * (A.nxt_frows * 64));
     const int nitems = A.row_items ? COS_RF(nlist) : nm;
@@ -919,9 +918,10 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
     if (A.stubs && any) atomicAdd(A.sbar_T + (int64_t)(g * nfs + lam) * 64 + lane, sacc);
     __syncthreads();
     double *__restrict__ gb = A.Gbar_T + (int64_t)(g * nfs + lam) * N * N * 64;
+    const bool own = g * 64 + lane < A.count;
     for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) {
-        const double x = Gb_all[i];
-        if (x != 0.0) atomicAdd(gb + i, x);
+        const double x = Gb_all[i];   // (i's column is this lane's)
+        if (x != 0.0 && own) atomicAdd(gb + i, x);
     }
 }
 
@@ -956,11 +956,10 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
     const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};
     const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * 64, nfs};   // level + 1
     double *Bc = A.nxt + gl * A.nxt_gstride;                               // level
-    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t wl = work_lane(A, g, lane), lane8 = wl * 8u;
     const uint32_t off[3] = {lane8, lane8 + 512u, lane8 + 1024u};
-    const int cfg = A.lane_cfg[g * 64 + lane];
-    const double obar = cfg >= 0 ? A.out_bar[cfg] : 0.0;
-    const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane8;
+    const double obar = A.out_bar[A.lane_cfg[g * 64 + wl]];
+    const uint32_t gaddr = lds_addr(Gs_all) + lane8, gbaddr = lds_addr(Gb_all) + lane * 8u;
     const double *GT = A.GT + (int64_t)g * nfs * N * N * 64;
     const auto grow = [&](int l, int w) {
         return slot_ld(make_plane(GT + (l * N + N - 1) * N * 64), lane8, (uint32_t)w * 512u);
@@ -969,7 +968,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
                   BcL = make_plane(Bc + lam * (A.nxt_frows * 64));
     for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
     stage_slots(Gs_all, GT + lam * N * N * 64, N * N);
-    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + lane] : 0.0;
+    const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + wl] : 0.0;
     double sacc = 0.0;
     for (int blk = lo; blk < hi; blk += kAdjListMasks) {
         __syncthreads();   // the previous block's list has been read
@@ -1259,6 +1258,7 @@ struct SmallCtx {
     const SmallArgs &A;
     cint32 *script;
     int nrounds, lane, wave, nfs, gl;
+    uint32_t wl;             // as work_lane
     double *Gs, *Ts, *sig;   // LDS: G [nfs][N * N][64], close sums, shift weights [nfs][64]
     int cfg;
     uint32_t lane8;
@@ -1313,7 +1313,7 @@ __device__ __forceinline__ void small_forward(const SmallCtx<N> &C, bool keep) {
             const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
             const plane_t own = make_plane(cur + lam * cpl), nxtL = make_plane(nxt + lam * npl);
             const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
-            const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
+            const double sg = A.stub ? C.sig[lam * 64 + C.wl] : 0.0;
             double T[3] = {0.0, 0.0, 0.0}, dext[3] = {0.0, 0.0, 0.0};
             if (u == kSmallBrow) {
                 T[2] = fwd_brow<N, MASK, false>(M, gaddr, own, all, nxtL, C.lane8, k * kTileB<N>, sg);
@@ -1371,10 +1371,11 @@ __device__ __forceinline__ SmallCtx<N> small_ctx(const SmallArgs &A, double *lds
     const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6), g = A.group0 + (int)blockIdx.x;
     cint32 *script = (cint32 *)A.plan.script;
     const int slot = g * 64 + lane;
-    const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t wl = slot < A.count ? lane : 0, lane8 = wl * 8u;
     double *Ts = lds + (int64_t)A.nfs * N * N * 64;
-    return SmallCtx<N>{A,    script, (int)script[0], lane, wave, A.nfs, (int)blockIdx.x, lds, Ts, Ts + tail_doubles,
-                       slot < A.count ? A.order[slot] : -1, lane8, {lane8, lane8 + 512u, lane8 + 1024u}};
+    return SmallCtx<N>{A,  script, (int)script[0], lane, wave, A.nfs, (int)blockIdx.x, wl,
+                       lds, Ts, Ts + tail_doubles, slot < A.count ? A.order[slot] : -1,
+                       lane8, {lane8, lane8 + 512u, lane8 + 1024u}};
 }
 
 template <int N, bool MULTI, bool MASK>
@@ -1403,7 +1404,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const Small
     for (int e = C.wave; e < n2; e += wpb) Gb[e * 64 + lane] = 0.0;
     for (int l = C.wave; l < nfs; l += wpb) sb[l * 64 + lane] = 0.0;
     __syncthreads();
-    const double obar = C.cfg >= 0 ? A.out_bar[C.cfg] : 0.0;
+    const double obar = A.out_bar[A.order[(A.group0 + C.gl) * 64 + (int)C.wl]];
     const cint32 *items = C.script + kSmallHeader + C.nrounds * kSmallRoundInts, *lev = items + C.script[1];
     for (int l = 2 * NB; l >= 1; --l) {
         int64_t fpl, cpl, npl;
@@ -1418,10 +1419,10 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const Small
             const int k = (word >> 4) & 15;
             const MaskRec<N> M = load_rec<N>(A.plan, (int)(word >> 8));
             const uint32_t gaddr = lds_addr(C.Gs + lam * N * N * 64) + C.lane8;
-            const uint32_t gbaddr = lds_addr(Gb + lam * N * N * 64) + C.lane8;
-            const double sg = A.stub ? C.sig[lam * 64 + lane] : 0.0;
+            const uint32_t gbaddr = lds_addr(Gb + lam * N * N * 64) + lane * 8u;
+            const double sg = A.stub ? C.sig[lam * 64 + C.wl] : 0.0;
             double sacc = 0.0, tb[3];
-            close_adjoint<N, MASK>(M, Bn, [&](int l, int w) { return C.Gs[((l * N + N - 1) * N + w) * 64 + lane]; }, C.off, A.W,
+            close_adjoint<N, MASK>(M, Bn, [&](int l, int w) { return C.Gs[((l * N + N - 1) * N + w) * 64 + C.wl]; }, C.off, A.W,
                                    obar, tb);
             adj_heads<N, MULTI, MASK, false, Unordered>(M, gaddr, gbaddr, make_plane(F + lam * fpl), Fall,
                                                  make_plane(B1 + lam * cpl), make_plane(Bc + lam * npl), C.off, lam, k,

@@ -911,6 +911,7 @@ static LvlArgs level_args(cos_batch_t b, const OrderGroup &o, double cycle_weigh
     a.GT = b->d_GT + o.gt_off;
     a.sigT = b->d_sigT + o.sig_off;
     a.lane_cfg = b->d_lane + o.lane_off;
+    a.count = o.count;
     a.nfs = b->nfs;
     a.stubs = (b->flags & COS_F_STUBS) ? 1 : 0;
     a.W = cycle_weight * (b->variant == COS_UNIFORM ? (double)b->nflav : 1.0);
