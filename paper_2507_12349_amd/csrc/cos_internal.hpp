@@ -148,7 +148,7 @@ struct LvlArgs {
     int64_t F_gstride, F_frows;
     int32_t F_row0;
     int32_t level, group0, nfs, stubs, mpb;
-    // unlabelled levels: the level's first mask and its masks, in nblocks blocks
+    // the level's first mask and its masks, in nblocks blocks
     // of mpb masks per wavefront (split, and the reverse with row_items: of mpb
     // masks)
     int32_t mask0, nmasks, nblocks;
@@ -157,7 +157,7 @@ struct LvlArgs {
     int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)
     int32_t det_groups;       // deterministic reverse: groups of the order (stride of the partial sums)
-    int32_t row_items;        // reverse: the work items are (mask, row) pairs (unlabelled: (mask, head)), not masks
+    int32_t row_items;        // reverse: the work items are (mask, head) pairs (labelled: both labels of a head), not masks
     double W;                 // factor of one closed cycle: w * nflav (uniform) or w
     double *out;              // forward, last level: S per configuration (may be null)
     const double *out_bar;    // reverse: dL/dS per configuration
@@ -190,9 +190,9 @@ hipError_t launch_unpack(const PackArgs &a, const double *GbT, const double *sbT
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
 // sublattice forward level (cos_sub.hip): `a.plan` is a sublattice plan, rows
 // hold 2n slots, GT holds 2n x 2n matrices; wpb <= 16
-hipError_t launch_sub_level(const LvlArgs &a, int nblocks, int ngroups, int wpb, hipStream_t s);
+hipError_t launch_sub_level(LvlArgs a, int ngroups, int wpb, hipStream_t s);
 // sublattice reverse level: kSubAdjWaves wavefronts per workgroup
-hipError_t launch_sub_adj_level(const LvlArgs &a, int nblocks, int ngroups, hipStream_t s);
+hipError_t launch_sub_adj_level(LvlArgs a, int ngroups, hipStream_t s);
 // unlabelled levels of orders n >= 2: forward with `wpb` wavefronts per
 // workgroup (at most 16), reverse with kAdjWaves
 hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s);
@@ -202,7 +202,7 @@ hipError_t launch_order1(const LvlArgs &a, int ngroups, hipStream_t s);
 // wavefronts per workgroup of the reverse sweeps
 constexpr int kAdjWaves = 8, kSubAdjWaves = 16;
 // most masks of a split forward block, and of a reverse block with row_items
-constexpr int kSplitMasks = 8, kAdjListMasks = 64;
+constexpr int kSplitMasks = 8, kSubSplitMasks = 4, kAdjListMasks = 64;
 size_t fwd_lds_bytes(int n, int split_masks);
 // deterministic reverse sweep: every level's masks in kDetParts fixed parts;
 // Gbar_T / sbar_T of the LvlArgs point to the partial sums
@@ -212,8 +212,6 @@ hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s);
 // GbT and sbT = the sums of the parts (gsize and ssize elements each) in order
 hipError_t launch_det_reduce(const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize, double *GbT,
                              double *sbT, hipStream_t s);
-// most masks per wavefront of the labelled forward kernel when there are several flavours
-constexpr int kMultiMasks = 4;
 // launchers (cos_kernels.hip)
 hipError_t launch_g0(int nconf, const int32_t *n, const int64_t *voff, const int32_t *sites,
                      const double *tau, int L, double t, double beta, int nmat, const double *mu,

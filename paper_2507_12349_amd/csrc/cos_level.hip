@@ -106,18 +106,6 @@ __device__ __forceinline__ uint32_t child_rows(const MaskRec<N> &M, int h) {
 constexpr uint32_t kSlotB = 3u * 512u;
 template <int N> constexpr uint32_t kTileB = (N - 1) * kSlotB;
 
-// every flavour's plane of a level
-struct Planes {
-    const double *base;
-    int64_t stride;   // doubles
-    int n;
-    __device__ __forceinline__ double sum(uint32_t lane_off, uint32_t at) const {
-        double x = 0.0;
-        for (int k = 0; k < n; ++k) x += slot_ld(make_plane(base + k * stride), lane_off, at);
-        return x;
-    }
-};
-
 // vertex 0 visited twice and no other vertex (but b) visited once
 __device__ __forceinline__ bool special_mask(uint32_t ones, uint32_t twos) { return (twos & 1u) && ones == 0u; }
 
@@ -160,29 +148,6 @@ __global__ void pack_kernel(const PackArgs A) {
         if (A.sigT) A.sigT[si] = (c >= 0 && A.stub) ? A.stub[(int64_t)c * A.nstub + (A.variant ? l : 0)] : 0.0;
         if (l == 0) A.lane_cfg[slot] = c;
     }
-}
-
-// The workgroups of a launch, nx per group, are dealt to the chip's 8 XCDs round
-// robin in the order of blockIdx.  Each XCD takes a contiguous part of them
-// (groups one after another), so that the workgroups that run on it at a time
-// serve one or two groups: their states lie in few pages and their G is in the
-// XCD's own L2 (n = 10, 2048 configurations: forward 3.69 -> 3.64 ms, three
-// flavours 6.30 -> 6.22 ms).  Returns false for the padding workgroups.
-struct BlockAt {
-    int x, group;
-};
-__device__ __forceinline__ bool xcd_block(const LvlArgs &A, BlockAt &at) {
-    const int per = gridDim.x >> 3, id = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
-    at.group = id / A.gridx;
-    at.x = id - at.group * A.gridx;
-    return at.group < A.ngroups;
-}
-
-// the next item of a workgroup's block, claimed by one wavefront
-__device__ __forceinline__ int claim(int *next, int lane) {
-    int nx = 0;
-    if (lane == 0) nx = atomicAdd(next, 1);
-    return COS_RF(nx);   // lane 0's claim (every lane is active here)
 }
 
 // ---------------------------------------------------------------------------

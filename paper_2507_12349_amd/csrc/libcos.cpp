@@ -919,33 +919,36 @@ static LvlArgs level_args(cos_batch_t b, const OrderGroup &o, double cycle_weigh
     return a;
 }
 
-// masks per wavefront of a forward level launch with `nm` masks and `ng`
-// groups: up to the shape's cap (to amortise loading G into LDS), fewer when
+// masks per wavefront of an unlabelled forward level launch with `nm` masks and
+// `ng` groups: up to the shape's cap (to amortise loading G into LDS), fewer when
 // the level is small so that its rows spread over enough wavefronts
-static int fwd_cap(const LaunchShape &sh, int nfs, bool sub) {
+static int fwd_cap(const LaunchShape &sh, bool sub) {
     // unlabelled: 2 (n = 10, 2048 configurations: 3.58 ms at 1 or 2, 3.67 at 4,
     // 3.84 at 8: small blocks keep the masks in work close together in memory)
-    if (!sub) return sh.fwd_cap ? sh.fwd_cap : 2;
-    const int cap = sh.fwd_cap ? sh.fwd_cap : (nfs <= 1 ? 8 : kMultiMasks);
-    return nfs > 1 ? std::min(cap, kMultiMasks) : cap;   // close sums of several flavours in registers
+    return sh.fwd_cap ? sh.fwd_cap : (sub ? 16 : 2);
 }
-static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu, bool sub) {
-    const int cap = fwd_cap(sh, nfs, sub);
-    const int64_t per = ((int64_t)nm * ng * (sub ? 1 : nfs)) / std::max<int64_t>(1, (int64_t)ncu * 16);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(cap, per));
+static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu) {
+    const int64_t per = ((int64_t)nm * ng * nfs) / std::max<int64_t>(1, (int64_t)ncu * 16);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(fwd_cap(sh, false), per));
 }
 
-// masks per wavefront of a reverse level launch: one workgroup (16
-// wavefronts, one per CU by its LDS footprint) loads G and flushes its dS/dG
-// accumulator once per flavour, so blocks should be large; its wavefronts
+// masks per wavefront of a reverse level launch, and of a labelled forward one:
+// a workgroup loads a large G (and flushes its dS/dG accumulator) once, so
+// blocks should be large (labelled n = 8, 1024 configurations: 7.80 ms at up to
+// 8 masks, 7.47 at up to 16); its wavefronts
 // share the block's masks dynamically, so workgroups take equal time, and the
 // level is cut into as few rounds of one workgroup per CU as the cap allows,
 // with the masks spread evenly over them
-static int adj_masks(const LaunchShape &sh, int nm, int ng, int ncu, int per_cu) {
+static int even_masks(int cap, int nm, int ng, int ncu, int per_cu, int wpb) {
     const int64_t slots = (int64_t)std::max(1, ncu) * per_cu;             // wavefronts of one round
     const int64_t work = (int64_t)nm * ng;
-    const int64_t rounds = std::max<int64_t>(1, (work + slots * sh.adj_cap - 1) / (slots * sh.adj_cap));
-    return (int)std::max<int64_t>(1, std::min<int64_t>(sh.adj_cap, (work + slots * rounds - 1) / (slots * rounds)));
+    const int64_t rounds = std::max<int64_t>(1, (work + slots * cap - 1) / (slots * cap));
+    int m = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (work + slots * rounds - 1) / (slots * rounds)));
+    // a group's last block is not full: a little more per block where the blocks
+    // would run into another round (n = 7, 600 configurations: 260 blocks of 13
+    // masks per wavefront on 256 CUs took 276 us, 240 of 14 take 221)
+    while (m < cap && (int64_t)((nm + wpb * m - 1) / (wpb * m)) * ng * wpb > slots * rounds) ++m;
+    return m;
 }
 
 // wavefronts of the reverse that a CU holds: workgroups of kAdjWaves as their
@@ -978,14 +981,27 @@ static int level_steps(const OrderGroup &o, int l) { return !o.sub && l == o.hp-
 // one forward level of `cg` groups, its masks filled in here
 static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, int l, int cg, hipStream_t s) {
     a.level = l;
-    if (o.sub) {
-        const int nm = o.hp->levels[l].w;
-        a.mpb = fwd_masks(o.shape, b->nfs, nm, cg, b->ncu, true);
-        LAUNCH_TRY(launch_sub_level(a, (nm + a.mpb - 1) / a.mpb, cg, o.shape.fwd_wpb, s));
-        return COS_OK;
-    }
     level_masks(o, l, &a);
     const int wpb = o.shape.fwd_wpb;
+    if (o.sub) {
+        const int per_cu = 4 * o.n * o.n * 512 * 2 <= 160 * 1024 ? 2 * wpb : wpb;   // wavefronts, by G in LDS
+        // as below: the row pairs of a mask go to different wavefronts on the
+        // upper levels, while the masks are fewer than a quarter of the
+        // wavefronts that fit (n = 8, 1024 configurations, two flavours: level 15
+        // 92 -> 28 us; level 14, with more masks than that, 100 us split and 78
+        // not, as each workgroup loads G for fewer of them)
+        a.split = l == 2 * o.n || (2 * level_rows(*o.hp, l, l) >= (int64_t)a.nmasks * o.slots() &&
+                                   (int64_t)a.nmasks * b->nfs * cg <= (int64_t)b->ncu * 4);
+        if (a.split) {
+            a.mpb = std::min(kSubSplitMasks, a.nmasks);
+            a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
+        } else {
+            a.mpb = even_masks(fwd_cap(o.shape, true), a.nmasks, cg * b->nfs, b->ncu, per_cu, wpb);
+            a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
+        }
+        LAUNCH_TRY(launch_sub_level(a, cg, wpb, s));
+        return COS_OK;
+    }
     // the heads of a mask go to different wavefronts on the upper levels (at
     // least n / 3 heads a mask on average), while the masks are fewer than half
     // the wavefronts that fit the chip: at n = 10, 2048 configurations, the last
@@ -1002,7 +1018,7 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
         while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb) > 80 * 1024) --a.mpb;
         a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
     } else {
-        a.mpb = fwd_masks(o.shape, b->nfs, a.nmasks, cg, b->ncu, false);
+        a.mpb = fwd_masks(o.shape, b->nfs, a.nmasks, cg, b->ncu);
         a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
     }
     LAUNCH_STEPS(level_steps(o, l), launch_level_fwd(a, cg, wpb, s));
@@ -1294,21 +1310,22 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 a.out_bar = d_out_bar;
                 a.Gbar_T = GbT;
                 a.sbar_T = sbT;
+                level_masks(o, l, &a);
                 if (o.sub) {
                     // a level whose masks fill at most an eighth of one round
                     // (its rows are split over two workgroups at n = 7, 8 and
-                    // each row reloads its mask's close adjoints in every
-                    // flavour), and whose masks hold at least half the most
-                    // rows a mask can have (2n) on average (the upper levels),
-                    // gives every row a wavefront of its own
-                    a.row_items = ((int64_t)nm * cg * 8 <= (int64_t)b->ncu * 16 &&
+                    // each pair reloads its mask's close adjoints), and whose
+                    // masks hold at least half the most rows a mask can have
+                    // (2n) on average (the upper levels), gives every pair of
+                    // rows a wavefront of its own
+                    a.row_items = ((int64_t)nm * cg * b->nfs * 8 <= (int64_t)b->ncu * 16 &&
                                    2 * level_rows(*o.hp, l, l) >= (int64_t)nm * o.slots()) ? 1 : 0;
-                    const int items = a.row_items ? nm * o.slots() : nm;
-                    a.mpb = adj_masks(o.shape, items, cg, b->ncu, per_cu);
-                    LAUNCH_TRY(launch_sub_adj_level(a, (items + a.mpb - 1) / a.mpb, cg, s));
+                    const int items = a.row_items ? nm * o.n : nm;
+                    a.mpb = even_masks(o.shape.adj_cap, items, cg * b->nfs * (o.n > 6 ? 2 : 1), b->ncu, per_cu, kSubAdjWaves);
+                    a.nblocks = (items + kSubAdjWaves * a.mpb - 1) / (kSubAdjWaves * a.mpb);
+                    LAUNCH_TRY(launch_sub_adj_level(a, cg, s));
                     continue;
                 }
-                level_masks(o, l, &a);
                 if (det) {
                     a.Gbar_T = Gp;
                     a.sbar_T = Sp;
@@ -1326,7 +1343,7 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                     a.mpb = std::min(kAdjListMasks, (kAdjWaves + heads - 1) / heads);
                     a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
                 } else {
-                    a.mpb = adj_masks(o.shape, a.nmasks, cg * b->nfs, b->ncu, per_cu);
+                    a.mpb = even_masks(o.shape.adj_cap, a.nmasks, cg * b->nfs, b->ncu, per_cu, kAdjWaves);
                     a.nblocks = (a.nmasks + kAdjWaves * a.mpb - 1) / (kAdjWaves * a.mpb);
                 }
                 LAUNCH_STEPS(level_steps(o, l), launch_level_adj(a, cg, s));
@@ -1468,7 +1485,7 @@ cos_status cos_batch_launch_shape(cos_batch_t b, int32_t n, int32_t *fwd_waves, 
     for (const OrderGroup &o : b->orders)
         if (o.n == n) {
             *fwd_waves = o.shape.fwd_wpb;
-            *fwd_masks_cap = fwd_cap(o.shape, b->nfs, o.sub);
+            *fwd_masks_cap = fwd_cap(o.shape, o.sub);
             *adj_masks_cap = o.shape.adj_cap;
             return COS_OK;
         }
