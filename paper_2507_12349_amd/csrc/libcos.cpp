@@ -922,14 +922,18 @@ static LvlArgs level_args(cos_batch_t b, const OrderGroup &o, double cycle_weigh
 // masks per wavefront of an unlabelled forward level launch with `nm` masks and
 // `ng` groups: up to the shape's cap (to amortise loading G into LDS), fewer when
 // the level is small so that its rows spread over enough wavefronts
-static int fwd_cap(const LaunchShape &sh, bool sub) {
-    // unlabelled: 2 (n = 10, 2048 configurations: 3.58 ms at 1 or 2, 3.67 at 4,
-    // 3.84 at 8: small blocks keep the masks in work close together in memory)
-    return sh.fwd_cap ? sh.fwd_cap : (sub ? 16 : 2);
+static int fwd_cap(const LaunchShape &sh, int n, bool sub) {
+    if (sh.fwd_cap) return sh.fwd_cap;
+    if (sub) return 16;
+    // small blocks keep the masks in work close together in memory (n = 10, 2048
+    // configurations: 3.58 ms at 1 or 2, 3.67 at 4, 3.84 at 8; n = 11, 512: 3.50
+    // at 2, 3.58 at 4), but at n = 12 each loads 74 KB of G (86 configurations,
+    // six flavours: 17.8 ms at 2, 16.7 at 4 and 8; 512, one flavour: 11.35 at both)
+    return n >= 12 ? 4 : 2;
 }
-static int fwd_masks(const LaunchShape &sh, int nfs, int nm, int ng, int ncu) {
+static int fwd_masks(const LaunchShape &sh, int n, int nfs, int nm, int ng, int ncu) {
     const int64_t per = ((int64_t)nm * ng * nfs) / std::max<int64_t>(1, (int64_t)ncu * 16);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(fwd_cap(sh, false), per));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(fwd_cap(sh, n, false), per));
 }
 
 // masks per wavefront of a reverse level launch, and of a labelled forward one:
@@ -996,7 +1000,7 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
             a.mpb = std::min(kSubSplitMasks, a.nmasks);
             a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
         } else {
-            a.mpb = even_masks(fwd_cap(o.shape, true), a.nmasks, cg * b->nfs, b->ncu, per_cu, wpb);
+            a.mpb = even_masks(fwd_cap(o.shape, o.n, true), a.nmasks, cg * b->nfs, b->ncu, per_cu, wpb);
             a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
         }
         LAUNCH_TRY(launch_sub_level(a, cg, wpb, s));
@@ -1018,7 +1022,7 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
         while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb) > 80 * 1024) --a.mpb;
         a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
     } else {
-        a.mpb = fwd_masks(o.shape, b->nfs, a.nmasks, cg, b->ncu);
+        a.mpb = fwd_masks(o.shape, o.n, b->nfs, a.nmasks, cg, b->ncu);
         a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
     }
     LAUNCH_STEPS(level_steps(o, l), launch_level_fwd(a, cg, wpb, s));
@@ -1485,7 +1489,7 @@ cos_status cos_batch_launch_shape(cos_batch_t b, int32_t n, int32_t *fwd_waves, 
     for (const OrderGroup &o : b->orders)
         if (o.n == n) {
             *fwd_waves = o.shape.fwd_wpb;
-            *fwd_masks_cap = fwd_cap(o.shape, o.sub);
+            *fwd_masks_cap = fwd_cap(o.shape, o.n, o.sub);
             *adj_masks_cap = o.shape.adj_cap;
             return COS_OK;
         }
