@@ -1337,14 +1337,19 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                     LAUNCH_STEPS(level_steps(o, l), launch_level_det(a, cg, s));
                     continue;
                 }
-                // a level with fewer masks than the wavefronts of one round
-                // spreads the heads of its masks over wavefronts, in blocks of
-                // about one (mask, head) item per wavefront (n = 8, 1000
-                // configurations: reverse levels 440 -> 385 us)
-                a.row_items = (int64_t)nm * b->nfs * cg <= (int64_t)b->ncu * per_cu ? 1 : 0;
+                // a level with fewer masks than the wavefronts of two rounds
+                // spreads the heads of its masks over wavefronts: blocks of at
+                // least one (mask, head) item per wavefront, and no more blocks
+                // than fit the chip, as each loads G, clears its accumulator and
+                // flushes it (n = 8, 1000 configurations, the reverse levels: 440
+                // us with one item per wavefront and fewer masks than one round,
+                // 418 with blocks that fit the chip, 405 up to two rounds, 407 up
+                // to four)
+                a.row_items = (int64_t)nm * b->nfs * cg <= 2 * (int64_t)b->ncu * per_cu ? 1 : 0;
                 if (a.row_items) {
                     const int heads = level_heads(o, l);
-                    a.mpb = std::min(kAdjListMasks, (kAdjWaves + heads - 1) / heads);
+                    const int blocks = std::max(1, b->ncu * per_cu / kAdjWaves / (cg * b->nfs));   // per group and flavour
+                    a.mpb = std::min(kAdjListMasks, std::max((kAdjWaves + heads - 1) / heads, (nm + blocks - 1) / blocks));
                     a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
                 } else {
                     a.mpb = even_masks(o.shape.adj_cap, a.nmasks, cg * b->nfs, b->ncu, per_cu, kAdjWaves);
