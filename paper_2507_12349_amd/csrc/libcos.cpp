@@ -986,7 +986,7 @@ static int level_steps(const OrderGroup &o, int l) { return !o.sub && l == o.hp-
 static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, int l, int cg, hipStream_t s) {
     a.level = l;
     level_masks(o, l, &a);
-    const int wpb = o.shape.fwd_wpb;
+    int wpb = o.shape.fwd_wpb;
     if (o.sub) {
         const int per_cu = 4 * o.n * o.n * 512 * 2 <= 160 * 1024 ? 2 * wpb : wpb;   // wavefronts, by G in LDS
         // as below: the row pairs of a mask go to different wavefronts on the
@@ -1014,7 +1014,12 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
     // masks than that, loading G for fewer masks costs more than it gains (n = 10,
     // three flavours, level 4: 54 -> 107 us)
     const int heads = level_heads(o, l);
-    a.split = 3 * heads >= o.n && (int64_t)a.nmasks * b->nfs * cg <= (int64_t)b->ncu * 8;
+    // Where even the tiles do not fill half the chip's wavefronts, they spread from
+    // two heads a mask on, and over workgroups of four wavefronts, one per SIMD
+    // (n = 8, 107 configurations, the forward levels 146 -> 128 us)
+    const int64_t masks = (int64_t)a.nmasks * b->nfs * cg, tiles = masks * heads;
+    a.split = (3 * heads >= o.n && masks <= (int64_t)b->ncu * 8) || (heads >= 2 && tiles <= (int64_t)b->ncu * 8);
+    if (tiles <= (int64_t)b->ncu * 4) wpb = std::min(wpb, 4);
     if (a.split) {
         // about one head per wavefront of a workgroup, in 80 KB of LDS so that
         // two workgroups fit a CU
@@ -1349,7 +1354,11 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 if (a.row_items) {
                     const int heads = level_heads(o, l);
                     const int blocks = std::max(1, b->ncu * per_cu / kAdjWaves / (cg * b->nfs));   // per group and flavour
-                    a.mpb = std::min(kAdjListMasks, std::max((kAdjWaves + heads - 1) / heads, (nm + blocks - 1) / blocks));
+                    // (few tiles: half the items, so that each SIMD of twice the
+                    // CUs has one wavefront; n = 8, 107 configurations, the
+                    // reverse levels 214 -> 177 us)
+                    const int items = (int64_t)nm * heads * b->nfs * cg <= (int64_t)b->ncu * 4 ? kAdjWaves / 2 : kAdjWaves;
+                    a.mpb = std::min(kAdjListMasks, std::max((items + heads - 1) / heads, (nm + blocks - 1) / blocks));
                     a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
                 } else {
                     a.mpb = even_masks(o.shape.adj_cap, a.nmasks, cg * b->nfs, b->ncu, per_cu, kAdjWaves);
