@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP64 = 78.6e12           # MI355X FP64 vector peak, FLOP/s
 PEAK_HBM = 8.0e12             # MI355X HBM3E, bytes/s
-REV_KERNEL = "level_adj_kernel<%d, false>"
+REV_KERNEL = "level_adj_kernel<%d, false, false>"
 WORKLOAD = "adjoint"
 
 
@@ -145,7 +145,7 @@ def honeycomb_forward(B, torch, reps):
     grad = {"configs_per_s": n.size / (a0.elapsed_time(a1) / reps * 1e-3),
             "ms_per_step": a0.elapsed_time(a1) / reps,
             "phases_ms": {k: v / reps for k, v in aph.items()},
-            "kernel": "sub_adj_kernel<8, false>", "launch_shape": ba.launch_shape(nn),
+            "kernel": "sub_adj_kernel<8, true, false>", "launch_shape": ba.launch_shape(nn),
             "S_equals_forward": bool(torch.equal(Sg, S))}
     ba.close()
     mask_only = {"forward_levels_ms": m0.elapsed_time(m1) / reps,
@@ -448,7 +448,7 @@ def workload_legs(B, torch, reps, cpu_threads=0, only=None):
                         "adjoint_S_equals_forward": bool(torch.equal(Sa, S))})
             del Gb, sb, Sa
         if name in ("plain_single", "plain_batch"):
-            # the plain form: one call per configuration (2n level launches, one of 64 lanes busy)
+            # the plain form: one call per configuration (a launch per level, one of 64 lanes busy)
             n0 = int(d.n[0])
             one = B.Batch([n0], w.nflav, w.variant)
             Sp = torch.empty_like(S)
@@ -469,7 +469,7 @@ def workload_legs(B, torch, reps, cpu_threads=0, only=None):
             plain = npl / (p0.elapsed_time(p1) * 1e-3)
             leg.update({"plain_configs_per_s": plain, "batched_over_plain": leg["configs_per_s"] / plain,
                         "plain_equals_batched_bitwise": bool(torch.equal(Sp, S)),
-                        "plain_note": "one call per configuration: 2n level launches with one of the 64 lanes of "
+                        "plain_note": "one call per configuration: a launch per level with one of the 64 lanes of "
                                       "each wavefront busy"})
             if name == "plain_single":
                 Gh = G.cpu().numpy().reshape(nmat, n0, n0)
@@ -791,13 +791,14 @@ def main():
     del Gbd, Gbd2, sbd
 
     # roofline of the dominant kernel, the reverse level kernel: one launch
-    # per level, 2n launches per sweep; algorithmic FLOP of the sweep per
+    # per level, 2n - 2 launches per sweep (one vertex's two visits stay inside
+    # the launches); algorithmic FLOP of the sweep per
     # configuration = 4 (E + C) (the adjoint of every extension and close
     # edge: one FMA into B, one into dS/dG)
     pc = B.plan_counts(n)
     flop_fwd = 2.0 * (pc["ext"] + pc["closes"])
     flop_rev = 2.0 * flop_fwd
-    nlaunch = 2 * n
+    nlaunch = 2 * n - 2
     rev_ms = phases["reverse"] / args.steps            # per sweep
     launch_ms = rev_ms / nlaunch                       # average launch
     flop_launch = flop_rev * nconf / nlaunch
@@ -859,7 +860,7 @@ def main():
         "forward_kernel_ms": fwd_kernel_ms,
         "forward_plain_configs_per_s": nconf / (plain_ms * 1e-3),
         "forward_plain_synced_configs_per_s": plain_sync_rate,
-        "plain_note": "one call per configuration: 2n level launches with one of the 64 lanes of each wavefront busy",
+        "plain_note": "one call per configuration: a launch per level with one of the 64 lanes of each wavefront busy",
         "batched_over_plain": (nconf / (fwd_ms * 1e-3)) / (nconf / (plain_ms * 1e-3)),
         "plain_equals_batched_bitwise": plain_equal,
         "adjoint_batched_configs_per_s": nconf / (acc["adj"] / args.steps * 1e-3),
