@@ -95,10 +95,10 @@ enum { COS_UNIFORM = 0, COS_FLAVOUR = 1 };
 /* COS_F_DETERMINISTIC: gradients that are the same bit for bit on every run,
  * whatever the launch shapes, the chunking of the groups or the reverse
  * variant: the reverse sweep cuts each level's masks into a fixed number of
- * parts, sums the dS/dG and dS/dsigma terms of a part in a fixed order in
- * registers (one wavefront per matrix row) and the parts in a fixed order
- * afterwards, with no atomics.  Slower than the default reverse (the child
- * adjoints are read once per row of G, from the caches); the forward and S
+ * parts, adds the dS/dG and dS/dsigma terms of a part in a fixed order (each
+ * work item of a workgroup waits for its turn) and the parts in a fixed order
+ * afterwards, with no atomics.  Slower than the default reverse (1.6 times at
+ * n = 9, 1024 configurations); the forward and S
  * are unchanged (they are deterministic anyway).  Not combinable with
  * COS_F_SUBLATTICE. */
 enum { COS_F_STUBS = 1, COS_F_SUBLATTICE = 2, COS_F_MASK_ONLY = 4, COS_F_DETERMINISTIC = 8 };
@@ -139,8 +139,11 @@ cos_status cos_batch_destroy(cos_batch_t b);
  * opened on the lowest once-visited vertex, SB-CoS shift heads), asynchronous
  * on `stream` (a hipStream_t, NULL = default stream).  Configurations are packed 64 to a
  * group (one per lane) by order, largest order first; for each order there is
- * one launch per level of the state space (level = number of visited points,
- * 2n levels), each covering every group of that order.  With two or more
+ * one launch per level of the state space (level = number of visited points;
+ * unlabelled, the two visits of one vertex stay inside the launches: 2n - 2
+ * launches, and 2n with labels), each covering every group of that order.
+ * Orders 2 to 5 without labels run all levels in one launch while the matrices
+ * of every flavour fit a workgroup's LDS.  With two or more
  * orders, the orders after the largest (after the two largest when the
  * others' windows would not fit) run on a second stream of the batch (made
  * at cos_batch_create, default priority, with level windows of their own,
@@ -286,11 +289,12 @@ cos_status cos_batch_adjoint_plan(cos_batch_t b, int32_t n, int32_t *split_level
 /* Autotuner (Results, GPU parallelization: launch shape per problem size).
  * For every order in the batch, times the level kernels over the caller's
  * inputs for each candidate launch shape -- wavefronts per workgroup of the
- * forward kernel (4, 8, 16; 8, 16 with COS_F_SUBLATTICE) and the most masks
+ * forward kernel (4, 8, 16; 8, 16 with COS_F_SUBLATTICE; levels with few masks
+ * may use fewer) and the most masks
  * (state-table tiles) per wavefront of the forward (1, 2, 4, 8, 16) and, when
  * d_out_bar is not NULL, of the reverse kernel (2, 4, 6, 8, 12, 16, 24, 32, 48, 64;
- * a reverse level is cut into as few rounds of one workgroup per CU as that
- * cap allows, its masks spread evenly) -- keeps the fastest per order and
+ * a reverse level is cut into as few rounds of the workgroups that fit the
+ * chip as that cap allows, its masks spread evenly) -- keeps the fastest per order and
  * uses it for every later call on b.  Arguments as cos_connected_sum_batched
  * / _adjoint; the output
  * buffers are overwritten and on return hold what a call with the chosen
@@ -305,8 +309,7 @@ cos_status cos_batch_launch_shape(cos_batch_t b, int32_t n, int32_t *fwd_waves,
                                   int32_t *fwd_masks, int32_t *adj_masks);
 /* Set the launch shape of order n instead of tuning it (for instance one that
  * cos_batch_autotune found before): fwd_waves in [1, 16], fwd_masks in
- * [1, 16], adj_masks in [1, 64] (the forward clamps
- * its masks per wavefront to 4 with several flavour slots).  COS_EINVAL for
+ * [1, 16], adj_masks in [1, 64].  COS_EINVAL for
  * values outside these ranges or an order the batch does not have. */
 cos_status cos_batch_set_launch_shape(cos_batch_t b, int32_t n, int32_t fwd_waves, int32_t fwd_masks,
                                       int32_t adj_masks);
@@ -402,7 +405,10 @@ cos_status cos_connected_count(int32_t n, int64_t cycle_weight, int64_t *count);
  * allocation as if the device were out of memory (the calls then return
  * COS_ENOMEM, or retry the level workspaces with smaller chunks, see
  * cos_set_workspace_limit), a launch is skipped and its call returns
- * COS_EDEVICE (launches queued before it stay queued).  count = 0 clears.
+ * COS_EDEVICE (launches queued before it stay queued).  A launch that does
+ * several steps of the dynamic programme (a level's, or a whole sweep of a
+ * small order) counts as as many: a forward order as 1 + 2n launches, whatever
+ * the number of kernels.  count = 0 clears.
  * Process-wide; COS_EINVAL for another kind or negative numbers. */
 cos_status cos_inject_failures(int32_t kind, int32_t skip, int32_t count);
 

@@ -13,46 +13,12 @@ typedef __attribute__((address_space(3))) int lds_int;
 // address space they are fetched with scalar loads
 typedef const __attribute__((address_space(4))) int32_t cint32;
 
-__device__ __forceinline__ int4 load_level(const DevPlan &P, int l) {
-    const cint32 *p = (const cint32 *)(P.levels + l);
-    return make_int4(p[0], p[1], p[2], p[3]);
-}
-
 // LDS byte address of a __shared__ pointer
 __device__ __forceinline__ uint32_t lds_addr(double *p) {
     return (uint32_t)(uintptr_t)(lds_double *)p;
 }
 
-// a lane's word of a 64-wide slot: wave-uniform base + the lane's byte offset
-// (scalar base registers, one 32-bit offset register per lane)
-// (the empty asm pins the base in scalar registers, so that it is not folded
-// into a per-lane 64-bit address)
-typedef __attribute__((address_space(1))) char global_char;
-__device__ __forceinline__ double lane_ld(const double *base, uint32_t lane8) {
-    const global_char *p = (const global_char *)base;
-    asm volatile("" : "+s"(p));
-    return *(const __attribute__((address_space(1))) double *)(p + lane8);
-}
-// the same with the nontemporal hint, for DP states: a level writes or reads
-// each state once, and a level's states are far larger than the caches, so
-// they stream past them instead of evicting the tables and matrices
-__device__ __forceinline__ double lane_ld_nt(const double *base, uint32_t lane8) {
-    const global_char *p = (const global_char *)base;
-    asm volatile("" : "+s"(p));
-    return __builtin_nontemporal_load((const __attribute__((address_space(1))) double *)(p + lane8));
-}
-__device__ __forceinline__ void lane_st_nt(double *base, uint32_t lane8, double x) {
-    global_char *p = (global_char *)base;
-    asm volatile("" : "+s"(p));
-    __builtin_nontemporal_store(x, (__attribute__((address_space(1))) double *)(p + lane8));
-}
-__device__ __forceinline__ void lane_st(double *base, uint32_t lane8, double x) {
-    global_char *p = (global_char *)base;
-    asm volatile("" : "+s"(p));
-    *(__attribute__((address_space(1))) double *)(p + lane8) = x;
-}
-
-// accesses of the tile kernels: a buffer descriptor over a plane of states
+// accesses of the level kernels: a buffer descriptor over a plane of states
 // (scalar registers), a byte offset per lane (one vector register) and a
 // wave-uniform byte offset (one scalar register): no address arithmetic beyond
 // one scalar add per slot.  Offsets inside a plane stay below 2^32.
@@ -68,8 +34,9 @@ __device__ __forceinline__ double slot_ld(plane_t p, uint32_t lane_off, uint32_t
 __device__ __forceinline__ void slot_st(plane_t p, uint32_t lane_off, uint32_t off, double x) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), p, (int)lane_off, (int)off, 0);
 }
-// STREAM: with the nontemporal hint (states far larger than the caches, read
-// and written once)
+// STREAM: with the nontemporal hint, for states far larger than the caches, which
+// a level reads or writes once: they stream past the caches instead of evicting
+// the tables and matrices
 template <bool STREAM>
 __device__ __forceinline__ double state_ld(plane_t p, uint32_t lane_off, uint32_t off) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(p, (int)lane_off, (int)off, STREAM ? kNt : 0));

@@ -45,7 +45,9 @@
 // part is kept in slot 0 of the mask's own head-b row (never a current slot) for
 // the reverse sweep, and in slot 0 of the head-b row of every child m + e_w,
 // which then adds the opened cycle's first step, 2 t G[b][w], to its slot w.  So
-// no part of a level waits for another.
+// no part of a level waits for another.  Against the flavours in turn in one
+// workgroup: three flavours, n = 10, 1024 configurations, forward 5.94 -> 5.28 ms;
+// n = 6, 333, with gradients 531 -> 274 us.
 //
 // Forward rules per row (m, u) and flavour l (Results; Alg. 2/3):
 //   acc = f . G_l;  extension to w (m_w < 2): child (m + e_w, u)[w] = c_w acc[w]
