@@ -560,23 +560,31 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
 // wavefronts come (Unordered), or (InTurn) only once every item before it has
 // added its terms, so that the order of summation is that of the items.  A
 // wavefront takes its items in ascending order, so the one with the lowest
-// item left never waits and every turn comes.
+// item left never waits and every turn comes.  The accumulator's rows v have
+// kTurns turns, so that an item adds to the first rows while the one before it
+// is still at the later ones.  A turn orders LDS accesses alone: its adds have
+// arrived (lgkmcnt) before the next item's turn is stored, while the item's
+// stores of adjoints to memory may still be on their way.
+constexpr int kTurns = 3;
+template <int N>
+__device__ __forceinline__ constexpr int first_row(int stage) { return (stage * N + kTurns - 1) / kTurns; }
 struct Unordered {
     static constexpr bool kDefer = false;
-    __device__ __forceinline__ void wait() const {}
-    __device__ __forceinline__ void done() const {}
+    __device__ __forceinline__ void wait(int) const {}
+    __device__ __forceinline__ void done(int) const {}
 };
 struct InTurn {
     static constexpr bool kDefer = true;
-    lds_int *turn;   // the item whose turn it is
+    lds_int *turn;   // the item whose turn it is, for each part of the rows
     int item;
-    __device__ __forceinline__ void wait() const {
-        while (COS_RF(__hip_atomic_load(turn, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) != item)
+    __device__ __forceinline__ void wait(int stage) const {
+        while (COS_RF(__hip_atomic_load(turn + stage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != item)
             __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
     }
-    // the release orders this item's adds before the next one's
-    __device__ __forceinline__ void done() const {
-        __hip_atomic_store(turn, item + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __device__ __forceinline__ void done(int stage) const {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __hip_atomic_store(turn + stage, item + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
 __device__ __forceinline__ void lds_add(lds_double *p, double x) {
@@ -691,11 +699,15 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
     const double fb1 = MASK ? c0 : 2.0 * c0;
     const double fb2 = __builtin_fma(-sg, fb1, __builtin_fma(fb1, gbb, c1));
     sacc = __builtin_fma(-fb1, a[1][NB], sacc);   // its shift edge
-    order.wait();
     if (Order::kDefer) {
 #pragma unroll
-        for (int v = 0; v < NB; ++v)
-            if ((cm >> v) & 1u) add_row(v);
+        for (int stage = 0; stage < kTurns; ++stage) {
+            order.wait(stage);
+#pragma unroll
+            for (int v = first_row<N>(stage); v < NB && v < first_row<N>(stage + 1); ++v)
+                if ((cm >> v) & 1u) add_row(v);
+            if (stage < kTurns - 1) order.done(stage);
+        }
     }
 #pragma unroll
     for (int w = 0; w < N; ++w) {
@@ -704,7 +716,7 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
         if (w < NB) x = __builtin_fma(fb2, a[2][w], x);
         lds_add(Gb + (NB * N + w) * 64, x);
     }
-    order.done();
+    order.done(kTurns - 1);
 }
 
 // the row of head b; tb: W times the adjoint of its close.  In special masks
@@ -738,7 +750,8 @@ __device__ __forceinline__ void adj_brow(const MaskRec<N> &M, uint32_t gaddr, ui
         if ((ones & bit) && (cm & bit)) sacc = __builtin_fma(-f[w], a[w], sacc);
     }
     a[NB] = tb;
-    order.wait();   // (a head-b row is short: its turn covers all of the following)
+#pragma unroll
+    for (int stage = 0; stage < kTurns; ++stage) order.wait(stage);   // (a head-b row is short: it takes all turns at once)
 #pragma unroll
     for (int v = 0; v < N; ++v) {
         const uint32_t bit = 1u << v;
@@ -755,7 +768,8 @@ __device__ __forceinline__ void adj_brow(const MaskRec<N> &M, uint32_t gaddr, ui
         for (int w = 0; w < N; ++w)
             if (w == NB || !((twos >> w) & 1u)) lds_add(Gb + (v * N + w) * 64, fv * a[w]);   // wave-uniform
     }
-    order.done();
+#pragma unroll
+    for (int stage = 0; stage < kTurns; ++stage) order.done(stage);
 }
 
 // W tbar of a mask's three rows.  Special masks: row 1 opens the cycle of head
@@ -815,8 +829,11 @@ __device__ __forceinline__ void adj_heads(const MaskRec<N> &M, uint32_t gaddr, u
             adj_tile<N, MULTI, MASK, STREAM, Order>(M, gaddr, gbaddr, F, Fall, Bn, Bc, off, u, (uint32_t)k * kTileB<N>, start, tb,
                                              sg, sacc, order);
         } else {
-            order.wait();
-            order.done();
+#pragma unroll
+            for (int stage = 0; stage < kTurns; ++stage) {
+                order.wait(stage);
+                order.done(stage);
+            }
         }
     }
     if ((twos & 1u) && s1 > nh)   // the close of the head-b row feeds row 2
@@ -903,15 +920,17 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
 // part's own slot of a partial buffer (no atomics: one workgroup per slot and
 // level, the levels follow one another on the stream), and det_reduce_kernel
 // sums the parts in order.
-// Measured (n = 9, 1024 configurations, the reverse levels): 2.87 -> 1.85 ms
+// Measured (n = 9, 1024 configurations, the reverse levels): 2.87 -> 1.76 ms
 // against one wavefront per slot v, which read every child adjoint n times and
-// kept one row of dS/dG in registers.
+// kept one row of dS/dG in registers; 1.53 ms with three turns per item that
+// order LDS accesses alone (1.54 with five, 1.58 with nine; the default reverse
+// takes 1.00).
 // ---------------------------------------------------------------------------
 template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const LvlArgs A) {
     extern __shared__ double lds[];
     double *Gs_all = lds, *Gb_all = lds + N * N * 64;   // as in level_adj_kernel
-    __shared__ int turn, nlist;
+    __shared__ int turn[kTurns], nlist;
     __shared__ uint16_t item_list[kAdjListMasks * N];
     __shared__ double sums[kAdjWaves * 64];   // shift terms of the wavefronts
     const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6);   // wave index: uniform
@@ -943,7 +962,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
             const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + blk) * kRecInts, min(kAdjListMasks, hi - blk),
                                      lane);
             if (lane == 63) nlist = n;
-            if (lane == 0) turn = 0;
+            if (lane < kTurns) turn[lane] = 0;
         }
         __syncthreads();
         const int nitems = COS_RF(nlist);
@@ -953,7 +972,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
             double tb[3];
             close_adjoint<N, MASK>(M, Bn, grow, off, A.W, obar, tb);
             adj_heads<N, MULTI, MASK, true, InTurn>(M, gaddr, gbaddr, FL, Fall, BnL, BcL, off, lam, k, k + 1, A.level == 1, tb, sg,
-                                             sacc, InTurn{(lds_int *)&turn, it});
+                                             sacc, InTurn{(lds_int *)turn, it});
         }
     }
     if (A.stubs) sums[wave * 64 + lane] = sacc;
