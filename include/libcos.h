@@ -97,7 +97,7 @@ enum { COS_UNIFORM = 0, COS_FLAVOUR = 1 };
  * variant: the reverse sweep cuts each level's masks into a fixed number of
  * parts, adds the dS/dG and dS/dsigma terms of a part in a fixed order (each
  * work item of a workgroup waits for its turn) and the parts in a fixed order
- * afterwards, with no atomics.  Slower than the default reverse (1.6 times at
+ * afterwards, with no atomics.  Slower than the default reverse (1.3 times at
  * n = 9, 1024 configurations); the forward and S
  * are unchanged (they are deterministic anyway).  Not combinable with
  * COS_F_SUBLATTICE. */
