@@ -955,13 +955,13 @@ static int even_masks(int cap, int nm, int ng, int ncu, int per_cu, int wpb) {
     return m;
 }
 
-// wavefronts of the reverse that a CU holds: workgroups of kAdjWaves as their
-// LDS (G and the dS/dG accumulator) and registers (at most 16 wavefronts of up
-// to 128 each fit) allow; the labelled reverse always has 16
-static int adj_waves_per_cu(const OrderGroup &o) {
-    if (o.sub) return kSubAdjWaves;
-    return 2 * o.n * o.n * 512 * 2 <= 160 * 1024 ? 2 * kAdjWaves : kAdjWaves;
-}
+// wavefronts of the reverse that a CU holds: unlabelled one workgroup of kAdjWaves
+// (its 147 to 256 registers from n = 6 on leave room for two or three wavefronts
+// a SIMD), labelled one of kSubAdjWaves.  (Counted as two workgroups where LDS
+// alone allows it, n <= 8, the blocks of a level ran in two rounds: gradients of
+// 2269 configurations of order 8 1164 us against 1066, 1000 of order 8 655 against
+// 622, 1570 of order 7 with four flavours 1072 against 1031.)
+static int adj_waves_per_cu(const OrderGroup &o) { return o.sub ? kSubAdjWaves : kAdjWaves; }
 
 // rows of levels a..c (inclusive) of a plan
 static int64_t level_rows(const HostPlan &p, int a, int c) { return (int64_t)p.levels[c + 1].x - p.levels[a].x; }
@@ -1342,15 +1342,14 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                     LAUNCH_STEPS(level_steps(o, l), launch_level_det(a, cg, s));
                     continue;
                 }
-                // a level with fewer masks than the wavefronts of two rounds
+                // a level with fewer masks than the wavefronts of four rounds
                 // spreads the heads of its masks over wavefronts: blocks of at
                 // least one (mask, head) item per wavefront, and no more blocks
                 // than fit the chip, as each loads G, clears its accumulator and
                 // flushes it (n = 8, 1000 configurations, the reverse levels: 440
-                // us with one item per wavefront and fewer masks than one round,
-                // 418 with blocks that fit the chip, 405 up to two rounds, 407 up
-                // to four)
-                a.row_items = (int64_t)nm * b->nfs * cg <= 2 * (int64_t)b->ncu * per_cu ? 1 : 0;
+                // us with one item per wavefront, 405 with blocks that fit; a
+                // pass 622 us at four rounds, 637 at two)
+                a.row_items = (int64_t)nm * b->nfs * cg <= 4 * (int64_t)b->ncu * kAdjWaves ? 1 : 0;
                 if (a.row_items) {
                     const int heads = level_heads(o, l);
                     const int blocks = std::max(1, b->ncu * per_cu / kAdjWaves / (cg * b->nfs));   // per group and flavour
