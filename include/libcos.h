@@ -322,8 +322,12 @@ cos_status cos_batch_set_launch_shape(cos_batch_t b, int32_t n, int32_t fwd_wave
  * and into *ncalls (may be NULL) the number of those calls, and starts a new
  * accumulation.  Phases: packing of the inputs and zeroing of the gradient
  * accumulators; the forward levels (recomputed inside the adjoint); the
- * reverse levels; unpacking of the gradients.  Not for use under stream
- * capture. */
+ * reverse levels; unpacking of the gradients.  Orders 2 to 5 whose sweep is
+ * one launch (cos_connected_sum_batched) read and write the caller's layout in
+ * it: their packing counts as forward and their unpacking as reverse, and
+ * while timing is enabled their adjoint takes two launches, so that the two
+ * phases show.  Order 1 has no levels: its adjoint is one launch, counted as
+ * reverse.  Not for use under stream capture. */
 enum { COS_PHASE_PACK = 0, COS_PHASE_FORWARD = 1, COS_PHASE_REVERSE = 2, COS_PHASE_UNPACK = 3,
        COS_NPHASES = 4 };
 cos_status cos_batch_timing_enable(cos_batch_t b, int32_t enable);

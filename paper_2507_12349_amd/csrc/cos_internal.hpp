@@ -164,7 +164,8 @@ struct LvlArgs {
     double *Gbar_T, *sbar_T;  // reverse: packed gradient accumulators
 };
 
-// a one-launch sweep (forward; with G_bar forward and reverse)
+// a one-launch sweep (forward; with G_bar the parts of forward and reverse)
+constexpr int kSmallForward = 1, kSmallReverse = 2;
 struct SmallArgs {
     DevPlan plan;
     const double *G;          // caller matrices, offsets (may be null), shift weights (null: none)
@@ -179,6 +180,7 @@ struct SmallArgs {
     const double *out_bar;
     double *G_bar, *stub_bar; // caller layout
     int32_t nfs, count, group0, mask_only;
+    int32_t parts;            // reverse: kSmallForward (every level kept in F, S) and / or kSmallReverse
 };
 
 // launchers (cos_level.hip)

@@ -1374,7 +1374,8 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_fwd_kernel(const Small
 }
 
 // forward (every level kept) and reverse; writes S, dS/dG and dS/dsigma.  The
-// accumulators take the place of the forward's close sums in LDS.
+// accumulators take the place of the forward's close sums in LDS.  Both run in
+// one launch; to be timed apart, in two (A.parts).
 template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const SmallArgs A) {
     constexpr int NB = N - 1;
@@ -1385,7 +1386,8 @@ __global__ void __launch_bounds__(64 * kSmallWaves) small_adj_kernel(const Small
     double *Gb = C.Ts, *sb = C.sig + nfs * 64;
     small_stage<N>(C);
     __syncthreads();
-    small_forward<N, MULTI, MASK>(C, true);
+    if (A.parts & kSmallForward) small_forward<N, MULTI, MASK>(C, true);
+    if (!(A.parts & kSmallReverse)) return;
     const int n2 = nfs * N * N;
     for (int e = C.wave; e < n2; e += wpb) Gb[e * 64 + lane] = 0.0;
     for (int l = C.wave; l < nfs; l += wpb) sb[l * 64 + lane] = 0.0;

@@ -1224,8 +1224,6 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
     const PackArgs pa = pack_args(b, o, d_G, d_Goff, d_stub);
     HIP_TRY(tmark(b, COS_PHASE_PACK, s));
     if (small_order(b, o, true) && !(b->flags & COS_F_DETERMINISTIC) && !o.adj_split) {
-        HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
-        HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
         SmallArgs a = small_args(b, o, d_G, d_Goff, d_stub, cycle_weight, d_out);
         a.out_bar = d_out_bar;
         a.G_bar = d_G_bar;
@@ -1234,9 +1232,21 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
         a.win_gstride = 2 * (int64_t)o.hp->max_rows * b->nfs * o.slots() * 64;
         a.F = b->d_Fall;
         a.win = b->d_Fall + a.F_gstride * o.chunk_adj;
-        for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_adj)
+        for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_adj) {
+            const int cg = std::min(o.chunk_adj, o.ngroups - a.group0);
             // (counted as the packing, zeroing, unpacking and the 4n levels that it does)
-            LAUNCH_STEPS(4 + 4 * o.n, launch_small(a, true, std::min(o.chunk_adj, o.ngroups - a.group0), s));
+            a.parts = kSmallForward | kSmallReverse;
+            if (b->timing) {   // each phase in a launch of its own
+                HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
+                a.parts = kSmallForward;
+                LAUNCH_STEPS(1 + 2 * o.n, launch_small(a, true, cg, s));
+                HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
+                a.parts = kSmallReverse;
+                LAUNCH_STEPS(3 + 2 * o.n, launch_small(a, true, cg, s));
+            } else {
+                LAUNCH_STEPS(4 + 4 * o.n, launch_small(a, true, cg, s));
+            }
+        }
         HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
         return COS_OK;
     }
