@@ -411,8 +411,9 @@ cos_status cos_connected_count(int32_t n, int64_t cycle_weight, int64_t *count);
  * cos_set_workspace_limit), a launch is skipped and its call returns
  * COS_EDEVICE (launches queued before it stay queued).  A launch that does
  * several steps of the dynamic programme (a level's, or a whole sweep of a
- * small order) counts as as many: a forward order as 1 + 2n launches, whatever
- * the number of kernels.  count = 0 clears.
+ * small order) counts as as many: a forward order as 1 + 2n launches, and 2n
+ * for each further chunk of its groups, whatever the number of kernels.
+ * count = 0 clears.
  * Process-wide; COS_EINVAL for another kind or negative numbers. */
 cos_status cos_inject_failures(int32_t kind, int32_t skip, int32_t count);
 

@@ -1070,8 +1070,8 @@ static cos_status forward_order(cos_batch_t b, const OrderGroup &o, const double
         a.win = o.side ? b->d_win2 : b->d_win;
         a.win_gstride = 2 * (int64_t)o.hp->max_rows * b->nfs * o.slots() * 64;
         for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_fwd)
-            // (counted as the packing and the 2n levels that it does)
-            LAUNCH_STEPS(1 + 2 * o.n, launch_small(a, false, std::min(o.chunk_fwd, o.ngroups - a.group0), s));
+            // (counted as the packing, once, and the 2n levels that it does)
+            LAUNCH_STEPS((a.group0 ? 0 : 1) + 2 * o.n, launch_small(a, false, std::min(o.chunk_fwd, o.ngroups - a.group0), s));
         return COS_OK;
     }
     LAUNCH_TRY(launch_pack(pack_args(b, o, d_G, d_Goff, d_stub), s));
@@ -1234,17 +1234,18 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
         a.win = b->d_Fall + a.F_gstride * o.chunk_adj;
         for (a.group0 = 0; a.group0 < o.ngroups; a.group0 += o.chunk_adj) {
             const int cg = std::min(o.chunk_adj, o.ngroups - a.group0);
-            // (counted as the packing, zeroing, unpacking and the 4n levels that it does)
+            // (counted as the packing, zeroing and unpacking, once, and the 4n levels that it does)
+            const int once = a.group0 ? 0 : 1, levels = 2 * o.n;
             a.parts = kSmallForward | kSmallReverse;
             if (b->timing) {   // each phase in a launch of its own
                 HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
                 a.parts = kSmallForward;
-                LAUNCH_STEPS(1 + 2 * o.n, launch_small(a, true, cg, s));
+                LAUNCH_STEPS(once + levels, launch_small(a, true, cg, s));
                 HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
                 a.parts = kSmallReverse;
-                LAUNCH_STEPS(3 + 2 * o.n, launch_small(a, true, cg, s));
+                LAUNCH_STEPS(3 * once + levels, launch_small(a, true, cg, s));
             } else {
-                LAUNCH_STEPS(4 + 4 * o.n, launch_small(a, true, cg, s));
+                LAUNCH_STEPS(4 * once + 2 * levels, launch_small(a, true, cg, s));
             }
         }
         HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
