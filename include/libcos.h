@@ -94,9 +94,9 @@ enum { COS_UNIFORM = 0, COS_FLAVOUR = 1 };
  * and the reverse sweep. */
 /* COS_F_DETERMINISTIC: gradients that are the same bit for bit on every run,
  * whatever the launch shapes, the chunking of the groups or the reverse
- * variant: the reverse sweep cuts each level's masks into a fixed number of
- * parts, adds the dS/dG and dS/dsigma terms of a part in a fixed order (each
- * work item of a workgroup waits for its turn) and the parts in a fixed order
+ * variant: the reverse sweep cuts each level's masks into parts that depend on
+ * the order alone, adds the dS/dG and dS/dsigma terms of a part in a fixed order
+ * (each work item waits for its turn) and the parts in a fixed order
  * afterwards, with no atomics.  Slower than the default reverse (1.3 times at
  * n = 9, 1024 configurations); the forward and S
  * are unchanged (they are deterministic anyway).  Not combinable with

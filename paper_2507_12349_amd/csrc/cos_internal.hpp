@@ -157,6 +157,7 @@ struct LvlArgs {
     int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)
     int32_t det_groups;       // deterministic reverse: groups of the order (stride of the partial sums)
+    int32_t det_parts, det_per;   // parts of the level, parts of a workgroup
     int32_t row_items;        // reverse: the work items are (mask, head) pairs (labelled: both labels of a head), not masks
     double W;                 // factor of one closed cycle: w * nflav (uniform) or w
     double *out;              // forward, last level: S per configuration (may be null)
@@ -206,14 +207,16 @@ constexpr int kAdjWaves = 8, kSubAdjWaves = 16;
 // most masks of a split forward block, and of a reverse block with row_items
 constexpr int kSplitMasks = 8, kSubSplitMasks = 4, kAdjListMasks = 64;
 size_t fwd_lds_bytes(int n, int split_masks);
-// deterministic reverse sweep: every level's masks in kDetParts fixed parts;
+// deterministic reverse sweep: every level's masks in a.det_parts parts, which
+// depend on the order and the level alone, a.det_per of them per workgroup;
 // Gbar_T / sbar_T of the LvlArgs point to the partial sums
 // [part][group][flavour][v][w][64] and [part][group][flavour][64]
-constexpr int kDetParts = 32;
+constexpr int kDetParts = 32, kDetPer = 8;   // at most
+size_t det_lds_bytes(int n, int per);
 hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s);
 // GbT and sbT = the sums of the parts (gsize and ssize elements each) in order
-hipError_t launch_det_reduce(const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize, double *GbT,
-                             double *sbT, hipStream_t s);
+hipError_t launch_det_reduce(int parts, const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize,
+                             double *GbT, double *sbT, hipStream_t s);
 // launchers (cos_kernels.hip)
 hipError_t launch_g0(int nconf, const int32_t *n, const int64_t *voff, const int32_t *sites,
                      const double *tau, int L, double t, double beta, int nmat, const double *mu,

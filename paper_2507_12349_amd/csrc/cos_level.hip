@@ -566,17 +566,21 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
 // arrived (lgkmcnt) before the next item's turn is stored, while the item's
 // stores of adjoints to memory may still be on their way.
 constexpr int kTurns = 3;
+__device__ __forceinline__ void lds_add(lds_double *p, double x) {
+    __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 template <int N>
 __device__ __forceinline__ constexpr int first_row(int stage) { return (stage * N + kTurns - 1) / kTurns; }
 struct Unordered {
     static constexpr bool kDefer = false;
     __device__ __forceinline__ void wait(int) const {}
     __device__ __forceinline__ void done(int) const {}
+    __device__ __forceinline__ void last(lds_double *, double) const {}
 };
 struct InTurn {
     static constexpr bool kDefer = true;
     lds_int *turn;   // the item whose turn it is, for each part of the rows
-    int item;
+    int item, stubs;
     __device__ __forceinline__ void wait(int stage) const {
         while (COS_RF(__hip_atomic_load(turn + stage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != item)
             __builtin_amdgcn_s_sleep(1);
@@ -586,10 +590,12 @@ struct InTurn {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __hip_atomic_store(turn + stage, item + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+    // the end of an item: its shift terms too
+    __device__ __forceinline__ void last(lds_double *sig, double s) const {
+        if (stubs) lds_add(sig, s);
+        done(kTurns - 1);
+    }
 };
-__device__ __forceinline__ void lds_add(lds_double *p, double x) {
-    __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
 template <int N, bool MULTI, bool MASK, bool STREAM, class Order>
 __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, uint32_t gbaddr, plane_t F,
@@ -716,7 +722,7 @@ __device__ __forceinline__ void adj_tile(const MaskRec<N> &M, uint32_t gaddr, ui
         if (w < NB) x = __builtin_fma(fb2, a[2][w], x);
         lds_add(Gb + (NB * N + w) * 64, x);
     }
-    order.done(kTurns - 1);
+    order.last(Gb + N * N * 64, sacc);
 }
 
 // the row of head b; tb: W times the adjoint of its close.  In special masks
@@ -769,7 +775,8 @@ __device__ __forceinline__ void adj_brow(const MaskRec<N> &M, uint32_t gaddr, ui
             if (w == NB || !((twos >> w) & 1u)) lds_add(Gb + (v * N + w) * 64, fv * a[w]);   // wave-uniform
     }
 #pragma unroll
-    for (int stage = 0; stage < kTurns; ++stage) order.done(stage);
+    for (int stage = 0; stage < kTurns - 1; ++stage) order.done(stage);
+    order.last(Gb + N * N * 64, sacc);
 }
 
 // W tbar of a mask's three rows.  Special masks: row 1 opens the cycle of head
@@ -911,33 +918,38 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
 
 // ---------------------------------------------------------------------------
 // reverse, deterministic: the same tiles, with an order of summation that
-// depends on nothing but the order n.  A level's masks are cut into kDetParts
-// fixed parts; one workgroup takes one part of one group and flavour, lists its
-// (mask, head) items, deals them to its wavefronts in turn (item i to wavefront
-// i mod kAdjWaves), and lets the items add their dS/dG terms to the LDS
-// accumulator in the order of the list (InTurn): everything else of a tile, 9/10
-// of its time, still overlaps with other tiles.  The accumulator is added to the
-// part's own slot of a partial buffer (no atomics: one workgroup per slot and
-// level, the levels follow one another on the stream), and det_reduce_kernel
-// sums the parts in order.
+// depends on nothing but the order n.  A level's masks are cut into parts (a mask
+// each, or more where there are more than kDetParts); one workgroup takes one or
+// several parts of one group and flavour, lists their (mask, head) items, deals
+// them to its wavefronts in turn (item i to wavefront i mod kAdjWaves), and lets
+// the items of a part add their dS/dG terms to the part's LDS accumulator in the
+// order of the list (InTurn): everything else of a tile, 9/10 of its time, still
+// overlaps with other tiles.  The accumulators are added to their parts' own
+// slots of a partial buffer (no atomics: one workgroup per slot and level, the
+// levels follow one another on the stream), and det_reduce_kernel sums the parts
+// in order.
 // Measured (n = 9, 1024 configurations, the reverse levels): 2.87 -> 1.76 ms
 // against one wavefront per slot v, which read every child adjoint n times and
 // kept one row of dS/dG in registers; 1.53 ms with three turns per item that
 // order LDS accesses alone (1.54 with five, 1.58 with nine; the default reverse
-// takes 1.00).
+// takes 1.00).  Eight loads in flight per thread where the accumulators are added
+// to the partial buffer: the whole pass 2.17 -> 2.08 ms.
 // ---------------------------------------------------------------------------
+// first mask of part p
+__device__ __forceinline__ int det_mask(const LvlArgs &A, int p) { return p * A.nmasks / A.det_parts; }
+
 template <int N, bool MULTI, bool MASK>
 __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const LvlArgs A) {
     extern __shared__ double lds[];
-    double *Gs_all = lds, *Gb_all = lds + N * N * 64;   // as in level_adj_kernel
-    __shared__ int turn[kTurns], nlist;
+    double *Gs_all = lds, *Gb_all = lds + N * N * 64;   // G; per part dS/dG [N * N][64] and dS/dsigma [64]
+    constexpr int kPart = (N * N + 1) * 64;
+    __shared__ int turn[kDetPer][kTurns], nlist;
     __shared__ uint16_t item_list[kAdjListMasks * N];
-    __shared__ double sums[kAdjWaves * 64];   // shift terms of the wavefronts
     const int lane = threadIdx.x & 63, wave = COS_RF(threadIdx.x >> 6);   // wave index: uniform
     const DevPlan &P = A.plan;
-    const int nfs = MULTI ? A.nfs : 1, part = blockIdx.x / nfs, lam = blockIdx.x - part * nfs;
-    const int lo = (int)(((int64_t)part * A.nmasks) / kDetParts), hi = (int)(((int64_t)(part + 1) * A.nmasks) / kDetParts);
-    if (lo >= hi) return;
+    const int nfs = MULTI ? A.nfs : 1, blk0 = blockIdx.x / nfs, lam = blockIdx.x - blk0 * nfs;
+    const int p0 = blk0 * A.det_per, np = min(A.det_per, A.det_parts - p0);
+    const int lo = det_mask(A, p0), hi = det_mask(A, p0 + np);   // np > 1: at most kAdjListMasks masks
     const int gl = blockIdx.y, g = A.group0 + gl;
     const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};
     const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * 64, nfs};   // level + 1
@@ -952,55 +964,67 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
     };
     const plane_t FL = make_plane(Fall.base + lam * Fall.stride), BnL = make_plane(Bn.base + lam * Bn.stride),
                   BcL = make_plane(Bc + lam * (A.nxt_frows * 64));
-    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) Gb_all[i] = 0.0;
+    for (int i = threadIdx.x; i < np * kPart; i += blockDim.x) Gb_all[i] = 0.0;
     stage_slots(Gs_all, GT + lam * N * N * 64, N * N);
     const double sg = A.stubs ? A.sigT[(int64_t)(g * nfs + lam) * 64 + wl] : 0.0;
-    double sacc = 0.0;
     for (int blk = lo; blk < hi; blk += kAdjListMasks) {
         __syncthreads();   // the previous block's list has been read
         if (wave == 0) {
             const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + blk) * kRecInts, min(kAdjListMasks, hi - blk),
                                      lane);
             if (lane == 63) nlist = n;
-            if (lane < kTurns) turn[lane] = 0;
+            if (lane < kTurns) turn[0][lane] = 0;
+            for (int j = 1; j < np; ++j) {   // the first turn of a part is that of its first item
+                const int first = __shfl(n, det_mask(A, p0 + j) - lo - 1);
+                if (lane < kTurns) turn[j][lane] = first;
+            }
         }
         __syncthreads();
         const int nitems = COS_RF(nlist);
-        for (int it = wave; it < nitems; it += kAdjWaves) {
+        for (int it = wave, j = 0; it < nitems; it += kAdjWaves) {
             const int word = COS_RF((int)item_list[it]), k = word & 15;
+            while (j + 1 < np && (word >> 4) >= det_mask(A, p0 + j + 1) - lo) ++j;   // the item's part
             const MaskRec<N> M = load_rec<N>(P, A.mask0 + blk + (word >> 4));
-            double tb[3];
+            double tb[3], sacc = 0.0;   // (the shift terms go to the part's sums at the end of the item)
             close_adjoint<N, MASK>(M, Bn, grow, off, A.W, obar, tb);
-            adj_heads<N, MULTI, MASK, true, InTurn>(M, gaddr, gbaddr, FL, Fall, BnL, BcL, off, lam, k, k + 1, A.level == 1, tb, sg,
-                                             sacc, InTurn{(lds_int *)turn, it});
+            adj_heads<N, MULTI, MASK, true, InTurn>(M, gaddr, gbaddr + j * (kPart * 8), FL, Fall, BnL, BcL, off, lam, k, k + 1,
+                                             A.level == 1, tb, sg, sacc, InTurn{(lds_int *)turn[j], it, A.stubs});
         }
     }
-    if (A.stubs) sums[wave * 64 + lane] = sacc;
     __syncthreads();
-    // this part's slot of the partial sums (one workgroup per slot and level)
-    const int64_t slot = ((int64_t)part * A.det_groups + g) * nfs + lam;
-    double *gp = A.Gbar_T + slot * N * N * 64;
-    for (int i = threadIdx.x; i < N * N * 64; i += blockDim.x) gp[i] += Gb_all[i];
-    if (A.stubs && wave == 0) {
-        double x = 0.0;
-        for (int k = 0; k < kAdjWaves; ++k) x += sums[k * 64 + lane];
-        A.sbar_T[slot * 64 + lane] += x;
+    // the parts' slots of the partial sums (one workgroup per slot and level)
+    for (int j = 0; j < np; ++j) {
+        const int64_t slot = ((int64_t)(p0 + j) * A.det_groups + g) * nfs + lam;
+        const double *gb = Gb_all + j * kPart;
+        double *gp = A.Gbar_T + slot * N * N * 64;
+        constexpr int kT = 64 * kAdjWaves, kU = 8;   // kU loads in flight per thread
+        for (int i0 = threadIdx.x; i0 < N * N * 64; i0 += kU * kT) {
+            double x[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) x[u] = i0 + u * kT < N * N * 64 ? gp[i0 + u * kT] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (i0 + u * kT < N * N * 64) gp[i0 + u * kT] = x[u] + gb[i0 + u * kT];
+        }
+        if (A.stubs && wave == 0) A.sbar_T[slot * 64 + lane] += gb[N * N * 64 + lane];
     }
 }
 
 // sums the parts in order: GbT[i] = sum_p Gpart[p][i], sbT[g][l] = sum_p Spart[p][g][l]
-__global__ void det_reduce_kernel(const double *__restrict__ Gpart, const double *__restrict__ Spart, int64_t gsize,
+__global__ void det_reduce_kernel(int parts, const double *__restrict__ Gpart, const double *__restrict__ Spart, int64_t gsize,
                                   int64_t ssize, double *__restrict__ GbT, double *__restrict__ sbT) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < gsize) {
         double x = 0.0;
-        for (int p = 0; p < kDetParts; ++p) x += Gpart[(int64_t)p * gsize + i];
+#pragma unroll 8
+        for (int p = 0; p < parts; ++p) x += Gpart[(int64_t)p * gsize + i];
         GbT[i] = x;
     }
     if (Spart && i < ssize) {   // i = (g * nfs + l) * 64 + lane
         const int64_t gl = i >> 6, lane = i & 63;
         double x = 0.0;
-        for (int p = 0; p < kDetParts; ++p) x += Spart[((int64_t)p * (ssize >> 6) + gl) * 64 + lane];
+#pragma unroll 8
+        for (int p = 0; p < parts; ++p) x += Spart[((int64_t)p * (ssize >> 6) + gl) * 64 + lane];
         sbT[i] = x;
     }
 }
@@ -1112,10 +1136,16 @@ static hipError_t allow_lds(const void *fn, size_t bytes) {
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// LDS of a workgroup of the deterministic reverse: G, and per part the sums
+size_t det_lds_bytes(int n, int per) { return ((size_t)n * n + per * ((size_t)n * n + 1)) * 512; }
+
 hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s) {
     const int n = a.plan.n;
-    const size_t shm = 2 * (size_t)n * n * 64 * sizeof(double);
-    const dim3 grid((unsigned)(kDetParts * a.nfs), (unsigned)ngroups), block(64 * kAdjWaves);
+    const size_t shm = det_lds_bytes(n, a.det_per);
+    if (a.det_per < 1 || a.det_per > kDetPer) return hipErrorInvalidValue;
+    if (a.det_per > 1 && a.det_per * ((a.nmasks + a.det_parts - 1) / a.det_parts) > kAdjListMasks) return hipErrorInvalidValue;
+    if (a.det_parts < 1 || a.det_parts > kDetParts) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((a.det_parts + a.det_per - 1) / a.det_per * a.nfs), (unsigned)ngroups), block(64 * kAdjWaves);
     switch (n) {
 #define COS_DET_CASE(K)                                                                              \
     case K: {                                                                                        \
@@ -1136,12 +1166,12 @@ hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_det_reduce(const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize,
+hipError_t launch_det_reduce(int parts, const double *Gpart, const double *Spart, int64_t gsize, int64_t ssize,
                              double *GbT, double *sbT, hipStream_t s) {
     const int64_t tot = (Spart && ssize > gsize) ? ssize : gsize;
     if (tot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(det_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, Gpart, Spart, gsize,
-                       ssize, GbT, sbT);
+    hipLaunchKernelGGL(det_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, parts, Gpart, Spart,
+                       gsize, ssize, GbT, sbT);
     return hipGetLastError();
 }
 

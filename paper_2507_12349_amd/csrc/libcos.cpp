@@ -91,6 +91,7 @@ struct HostPlan {
     std::vector<int4> levels;       // [nlev + 2]
     std::vector<int32_t> mrec;      // [masks][rec_ints]
     std::vector<int32_t> special;   // level kernels' tables: special masks per level
+    std::vector<int32_t> items;     // and (mask, head) pairs per level
     std::vector<int32_t> script;    // small orders: the one-launch sweeps' table
     int nlev = 0;                   // levels (launches of a sweep)
     int slots = 0;                  // slots per row
@@ -187,6 +188,7 @@ void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
     P.nlev = 2 * nb;
     P.levels.assign(P.nlev + 2, make_int4(0, 0, 0, 0));
     P.special.assign(P.nlev + 2, 0);
+    P.items.assign(P.nlev + 2, 0);
     if (nb == 0) {
         P.max_rows = 1;
         P.total_rows = 1;
@@ -220,10 +222,12 @@ void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
             if (twos & 1u) {
                 P.rowbase[code] = (int32_t)(r + extra);
                 r += extra + (3 * (1 + __builtin_popcount(twos & ~1u)) + 1) * nb;
+                P.items[l] += 2 + __builtin_popcount(twos & ~1u);
                 if (!ones) ++P.special[l];
             } else {
                 P.rowbase[code] = (int32_t)r;
                 r += 3 * nb;
+                ++P.items[l];
             }
         }
         const int nm = (int)P.masks.size() - mask0;
@@ -536,13 +540,14 @@ struct OrderGroup {
     int adj_split = 0;                 // reverse sweep: 0 = every forward level stored; h > 0 = levels
                                        // h+1..2n stored by the forward, levels 1..h recomputed later
     int64_t gb_off = 0, sb_off = 0;    // offsets into the packed gradient accumulators
-    int64_t sp_off = 0;                // deterministic reverse: offset into the shift partial sums
+    int64_t gp_off = 0, sp_off = 0;    // deterministic reverse: offsets into the partial sums
     LaunchShape shape;                 // launch shape of the level kernels (autotuned)
     bool sub = false;                  // sublattice-labelled states (2n slots per row)
     bool side = false;                 // forward on the batch's side stream, in the side windows
     std::shared_ptr<HostPlan> hp;
     int mat_side() const { return sub ? 2 * n : n; }     // of a matrix
     int slots() const { return hp->slots; }          // per row of states
+    int det_parts() const { return std::max(1, std::min(hp->max_masks, kDetParts)); }   // of the level with most
 };
 
 struct cos_batch_s {
@@ -977,6 +982,21 @@ static int level_heads(const OrderGroup &o, int l) {
     return (int)std::max<int64_t>(1, level_rows(*o.hp, l, l) / (3 * (int64_t)(o.n - 1) * o.hp->levels[l].w));
 }
 
+// parts of a workgroup of the deterministic reverse (the results do not depend on
+// it): one while the workgroups fit the CUs, else as many as make two items for
+// each wavefront and still leave a workgroup per CU, as the parts are small (a
+// mask of two to four items each at n <= 6) and a CU holds one workgroup from n =
+// 5 on: gradients of 8192 configurations, one flavour, with one part each and
+// with several: n = 4 337 -> 95 us, n = 5 942 -> 227, n = 7 2784 -> 1412 (one
+// item per wavefront: 1572)
+static int det_per(const OrderGroup &o, int l, int parts, int64_t planes, int ncu) {
+    const int masks = (o.hp->levels[l].w + parts - 1) / parts, items = std::max(1, o.hp->items[l] / parts);
+    int per = (int)std::min<int64_t>({kDetPer, parts, (2 * kAdjWaves + items - 1) / items, parts * planes / ncu,
+                                      kAdjListMasks / masks});
+    while (per > 1 && det_lds_bytes(o.n, per) > 156 * 1024) --per;
+    return std::max(1, per);
+}
+
 // steps of the dynamic programme that the launch of level l does: a labelled
 // level is one; of the unlabelled ones the last counts the two visits of the
 // vertex that the tiles keep out of the levels
@@ -1157,19 +1177,23 @@ static int64_t adj_store_rows(const HostPlan &p, int h) {
 
 static cos_status prepare_adjoint(cos_batch_t b) {
     if (b->d_Fall) return COS_OK;
-    int64_t gb = 0, sb = 0, sp = 0;
+    const bool det = (b->flags & COS_F_DETERMINISTIC) != 0;
+    int64_t gb = 0, sb = 0, gp = 0, sp = 0;
     for (OrderGroup &o : b->orders) {
         o.gb_off = gb;
         o.sb_off = sb;
+        o.gp_off = gp;
         o.sp_off = sp;
         gb += (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
         sb += (int64_t)o.ngroups * b->nfs * 64;
-        sp += (int64_t)kDetParts * o.ngroups * b->nfs * 64;
+        if (!det) continue;
+        const int64_t ng = (int64_t)o.det_parts() * o.ngroups * b->nfs;
+        gp += ng * o.mat_side() * o.mat_side() * 64;
+        sp += ng * 64;
     }
-    const bool det = (b->flags & COS_F_DETERMINISTIC) != 0;
     if (dev_malloc((void **)&b->d_GbT, sizeof(double) * gb) != hipSuccess ||
         dev_malloc((void **)&b->d_sbT, sizeof(double) * sb) != hipSuccess ||
-        (det && (dev_malloc((void **)&b->d_Gpart, sizeof(double) * kDetParts * gb) != hipSuccess ||
+        (det && (dev_malloc((void **)&b->d_Gpart, sizeof(double) * gp) != hipSuccess ||
                  dev_malloc((void **)&b->d_Spart, sizeof(double) * sp) != hipSuccess))) {
         (void)hipFree(b->d_GbT);
         (void)hipFree(b->d_sbT);
@@ -1256,12 +1280,12 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
     const int64_t ngb = (int64_t)o.ngroups * b->nfs * o.mat_side() * o.mat_side() * 64;
     const int64_t nsb = (int64_t)o.ngroups * b->nfs * 64;
     const bool det = (b->flags & COS_F_DETERMINISTIC) != 0;
-    double *Gp = det ? b->d_Gpart + (int64_t)kDetParts * o.gb_off : nullptr;
+    const int parts = det ? o.det_parts() : 0;
+    double *Gp = det ? b->d_Gpart + o.gp_off : nullptr;
     double *Sp = det ? b->d_Spart + o.sp_off : nullptr;
-    const int64_t nsp = (int64_t)kDetParts * nsb;
     if (det) {
-        LAUNCH_TRY(launch_zero(Gp, (int64_t)kDetParts * ngb, s));
-        LAUNCH_TRY(launch_zero(Sp, nsp, s));
+        LAUNCH_TRY(launch_zero(Gp, parts * ngb, s));
+        LAUNCH_TRY(launch_zero(Sp, parts * nsb, s));
     } else {
         LAUNCH_TRY(launch_zero(GbT, ngb, s));
         LAUNCH_TRY(launch_zero(sbT, nsb, s));
@@ -1350,6 +1374,8 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                     a.Gbar_T = Gp;
                     a.sbar_T = Sp;
                     a.det_groups = o.ngroups;
+                    a.det_parts = std::min(a.nmasks, kDetParts);
+                    a.det_per = det_per(o, l, a.det_parts, (int64_t)cg * b->nfs, b->ncu);
                     LAUNCH_STEPS(level_steps(o, l), launch_level_det(a, cg, s));
                     continue;
                 }
@@ -1392,7 +1418,7 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
     }
     HIP_TRY(tmark(b, COS_PHASE_UNPACK, s));
     if (det)
-        LAUNCH_TRY(launch_det_reduce(Gp, (b->flags & COS_F_STUBS) ? Sp : nullptr, ngb, nsb, GbT, sbT, s));
+        LAUNCH_TRY(launch_det_reduce(parts, Gp, (b->flags & COS_F_STUBS) ? Sp : nullptr, ngb, nsb, GbT, sbT, s));
     LAUNCH_TRY(launch_unpack(pa, GbT, sbT, d_G_bar, (b->flags & COS_F_STUBS) ? d_stub_bar : nullptr, s));
     return COS_OK;
 }
