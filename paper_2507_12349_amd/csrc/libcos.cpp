@@ -1008,7 +1008,13 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
     level_masks(o, l, &a);
     int wpb = o.shape.fwd_wpb;
     if (o.sub) {
-        const int per_cu = 4 * o.n * o.n * 512 * 2 <= 160 * 1024 ? 2 * wpb : wpb;   // wavefronts, by G in LDS
+        // wavefronts that a CU holds: by G in LDS, and by registers (64 or fewer at n
+        // <= 2 and n = 3 with one flavour, 73 at n = 3, up to 128 from n = 4 on;
+        // counted as two workgroups of 16 by LDS alone, the blocks of a level of n =
+        // 6 ran in two rounds: 1000 configurations, one flavour, 376 us, in one
+        // round 346)
+        const int regs = o.n <= 2 || (o.n == 3 && b->nfs == 1) ? 32 : o.n == 3 ? 24 : 16;
+        const int per_cu = wpb * std::max(1, std::min(160 * 1024 / (4 * o.n * o.n * 512), regs / wpb));
         // as below: the row pairs of a mask go to different wavefronts on the
         // upper levels, while the masks are fewer than a quarter of the
         // wavefronts that fit (n = 8, 1024 configurations, two flavours: level 15
