@@ -147,12 +147,11 @@ struct LvlArgs {
     const double *F;          // reverse: forward states of all levels
     int64_t F_gstride, F_frows;
     int32_t F_row0;
-    int32_t level, group0, nfs, stubs, mpb;
-    // the level's first mask and its masks, in nblocks blocks
-    // of mpb masks per wavefront (split, and the reverse with row_items: of mpb
-    // masks)
-    int32_t mask0, nmasks, nblocks;
-    int32_t split;            // forward: blocks of mpb masks whose heads go to different wavefronts
+    int32_t level, group0, nfs, stubs;
+    // the level's first mask and its masks, in nblocks blocks of mpb masks (labelled
+    // reverse with row_items: of mpb items)
+    int32_t mask0, nmasks, nblocks, mpb;
+    int32_t split;            // forward: the heads of a mask go to different wavefronts
     int32_t count;            // configurations of the order
     int32_t gridx, ngroups;   // workgroups per group and groups of the launch (filled in by the launcher)
     int32_t mask_only;        // SU(2) mask-only rules (two spin blocks as the two planes)

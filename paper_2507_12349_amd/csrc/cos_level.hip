@@ -470,8 +470,7 @@ __global__ void __launch_bounds__(1024) level_fwd_kernel(const LvlArgs A) {
     const double *GT = A.GT + (int64_t)g * nfs * N * N * 64, *sigT = A.stubs ? A.sigT + (int64_t)g * nfs * 64 : nullptr;
 
     const int blk = MULTI ? at.x / nfs : at.x, lam = MULTI ? at.x - blk * nfs : 0;
-    const int bm = A.split ? A.mpb : wpb * A.mpb;   // masks of a block
-    const int mb0 = blk * bm, mb1 = min(mb0 + bm, A.nmasks);
+    const int mb0 = blk * A.mpb, mb1 = min(mb0 + A.mpb, A.nmasks);
     if (A.split && wave == 0) {
         const int n = list_items(item_list, P.mrec + (int64_t)(A.mask0 + mb0) * kRecInts, mb1 - mb0, lane);
         if (lane == 63) nitems = n;
@@ -866,8 +865,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_kernel(const LvlArgs
     BlockAt at;
     if (!xcd_block(A, at)) return;
     const int nfs = MULTI ? A.nfs : 1, blk = at.x / nfs, lam = at.x - blk * nfs;
-    const int bm = A.row_items ? A.mpb : wpb * A.mpb;   // masks of a block
-    const int blk0 = blk * bm, nm = min(bm, A.nmasks - blk0);
+    const int blk0 = blk * A.mpb, nm = min(A.mpb, A.nmasks - blk0);
     const int gl = at.group, g = A.group0 + gl;
     // wave-uniform bases; the lane's word is added at each access; flavour planes
     const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * 64, A.F_frows * 64, nfs};

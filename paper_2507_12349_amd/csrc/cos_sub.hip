@@ -210,8 +210,7 @@ __global__ void __launch_bounds__(1024) sub_fwd_kernel(const LvlArgs A) {
     const int gl = at.group, g = A.group0 + gl, nfs = MULTI ? A.nfs : 1;
     const bool last = A.level == 2 * N, start = A.level == 1, each = MULTI && !last;
     const int blk = each ? at.x / nfs : at.x, lam0 = each ? at.x - blk * nfs : 0, lam1 = each ? lam0 + 1 : nfs;
-    const int bm = A.split ? A.mpb : wpb * A.mpb;   // masks of a block
-    const int mb0 = blk * bm, nm = min(bm, A.nmasks - mb0);
+    const int mb0 = blk * A.mpb, nm = min(A.mpb, A.nmasks - mb0);
     const Planes all{A.cur + gl * A.cur_gstride + (int64_t)A.cur_row0 * D * 64, A.cur_frows * D * 64, nfs};
     double *nxt = A.nxt + gl * A.nxt_gstride + (int64_t)A.nxt_row0 * D * 64;
     const uint32_t lane8 = work_lane(A, g, lane) * 8u;
@@ -408,7 +407,7 @@ __global__ void __launch_bounds__(64 * kSubAdjWaves) sub_adj_kernel(const LvlArg
     const int i0 = (at.x % Z) * RI;   // first owned row i
     const int blk = at.x / Z / nfs, lam = at.x / Z - blk * nfs;
     const int nitems = A.row_items ? A.nmasks * N : A.nmasks;
-    const int blk0 = blk * wpb * A.mpb, ni = min(wpb * A.mpb, nitems - blk0);
+    const int blk0 = blk * A.mpb, ni = min(A.mpb, nitems - blk0);
     const Planes Fall{A.F + gl * A.F_gstride + (int64_t)A.F_row0 * D * 64, A.F_frows * D * 64, nfs};
     const Planes Bn{A.cur + gl * A.cur_gstride, A.cur_frows * D * 64, nfs};   // level + 1
     double *Bc = A.nxt + gl * A.nxt_gstride;                                   // level

@@ -941,32 +941,24 @@ static int fwd_masks(const LaunchShape &sh, int n, int nfs, int nm, int ng, int 
     return (int)std::max<int64_t>(1, std::min<int64_t>(fwd_cap(sh, n, false), per));
 }
 
-// masks per wavefront of a reverse level launch, and of a labelled forward one:
-// a workgroup loads a large G (and flushes its dS/dG accumulator) once, so
-// blocks should be large (labelled n = 8, 1024 configurations: 7.80 ms at up to
-// 8 masks, 7.47 at up to 16); its wavefronts
-// share the block's masks dynamically, so workgroups take equal time, and the
-// level is cut into as few rounds of one workgroup per CU as the cap allows,
-// with the masks spread evenly over them
-static int even_masks(int cap, int nm, int ng, int ncu, int per_cu, int wpb) {
-    const int64_t slots = (int64_t)std::max(1, ncu) * per_cu;             // wavefronts of one round
+// masks of a block of a reverse level launch, and of a labelled forward one,
+// between `least` and `most` and a multiple of `step`: a workgroup loads a large G
+// (and flushes its dS/dG accumulator) once, so blocks should be large (labelled n =
+// 8, 1024 configurations: 7.80 ms at up to 8 masks per wavefront, 7.47 at up to
+// 16); its wavefronts share the block's masks dynamically, so workgroups take equal
+// time, and the level is cut into as few rounds of the `slots` workgroups that the
+// chip holds as `most` allows, with the masks spread evenly over them
+static int even_block(int least, int most, int step, int nm, int ng, int64_t slots) {
     const int64_t work = (int64_t)nm * ng;
-    const int64_t rounds = std::max<int64_t>(1, (work + slots * cap - 1) / (slots * cap));
-    int m = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (work + slots * rounds - 1) / (slots * rounds)));
+    const int64_t rounds = std::max<int64_t>(1, (work + slots * most - 1) / (slots * most));
+    const int64_t even = ((work + slots * rounds - 1) / (slots * rounds) + step - 1) / step * step;
+    int m = (int)std::max<int64_t>(least, std::min<int64_t>(most, even));
     // a group's last block is not full: a little more per block where the blocks
     // would run into another round (n = 7, 600 configurations: 260 blocks of 13
     // masks per wavefront on 256 CUs took 276 us, 240 of 14 take 221)
-    while (m < cap && (int64_t)((nm + wpb * m - 1) / (wpb * m)) * ng * wpb > slots * rounds) ++m;
+    while (m + step <= most && (int64_t)((nm + m - 1) / m) * ng > slots * rounds) m += step;
     return m;
 }
-
-// wavefronts of the reverse that a CU holds: unlabelled one workgroup of kAdjWaves
-// (its 147 to 256 registers from n = 6 on leave room for two or three wavefronts
-// a SIMD), labelled one of kSubAdjWaves.  (Counted as two workgroups where LDS
-// alone allows it, n <= 8, the blocks of a level ran in two rounds: gradients of
-// 2269 configurations of order 8 1164 us against 1066, 1000 of order 8 655 against
-// 622, 1570 of order 7 with four flavours 1072 against 1031.)
-static int adj_waves_per_cu(const OrderGroup &o) { return o.sub ? kSubAdjWaves : kAdjWaves; }
 
 // rows of levels a..c (inclusive) of a plan
 static int64_t level_rows(const HostPlan &p, int a, int c) { return (int64_t)p.levels[c + 1].x - p.levels[a].x; }
@@ -1008,27 +1000,32 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
     level_masks(o, l, &a);
     int wpb = o.shape.fwd_wpb;
     if (o.sub) {
-        // wavefronts that a CU holds: by G in LDS, and by registers (64 or fewer at n
-        // <= 2 and n = 3 with one flavour, 73 at n = 3, up to 128 from n = 4 on;
-        // counted as two workgroups of 16 by LDS alone, the blocks of a level of n =
-        // 6 ran in two rounds: 1000 configurations, one flavour, 376 us, in one
-        // round 346)
-        const int regs = o.n <= 2 || (o.n == 3 && b->nfs == 1) ? 32 : o.n == 3 ? 24 : 16;
-        const int per_cu = wpb * std::max(1, std::min(160 * 1024 / (4 * o.n * o.n * 512), regs / wpb));
-        // as below: the row pairs of a mask go to different wavefronts on the
-        // upper levels, while the masks are fewer than a quarter of the
-        // wavefronts that fit (n = 8, 1024 configurations, two flavours: level 15
-        // 92 -> 28 us; level 14, with more masks than that, 100 us split and 78
-        // not, as each workgroup loads G for fewer of them)
-        a.split = l == 2 * o.n || (2 * level_rows(*o.hp, l, l) >= (int64_t)a.nmasks * o.slots() &&
-                                   (int64_t)a.nmasks * b->nfs * cg <= (int64_t)b->ncu * 4);
+        // workgroups that a CU holds: by G in LDS, and by registers (75 to 128 from n =
+        // 4 on; counted as two workgroups of 16 by LDS alone, the blocks of a level
+        // of n = 6 ran in two rounds: 1000 configurations, one flavour, 376 us, in
+        // one round 346.  n = 3 with several flavours, 73 registers, is counted as
+        // two all the same, as its G is loaded quickly: three flavours, 4096
+        // configurations, 54 us and 60)
+        const int per_cu = std::max(1, std::min(160 * 1024 / (4 * o.n * o.n * 512), (o.n <= 3 ? 32 : 16) / wpb));
+        // as below: the row pairs of a mask go to different wavefronts from three
+        // rows a mask on, while the masks are fewer than half the wavefronts that fit
+        // (n = 8, 1024 configurations, two flavours: level 15 92 -> 28 us; level 14,
+        // with more masks than that, 100 us split and 78 not, as each workgroup loads
+        // G for fewer of them.  64 configurations, two flavours, forward, split from
+        // half the most rows a mask can have and half as many masks on, and here: n =
+        // 6 187 and 163 us, n = 7 324 and 299; at n = 3, three flavours, 4096
+        // configurations, twice the masks cost 4 of 55 us)
+        a.split = l == 2 * o.n || (level_rows(*o.hp, l, l) >= 3 * (int64_t)a.nmasks &&
+                                   (int64_t)a.nmasks * b->nfs * cg <= (int64_t)b->ncu * (o.n >= 5 ? 8 : 4));
         if (a.split) {
             a.mpb = std::min(kSubSplitMasks, a.nmasks);
-            a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
         } else {
-            a.mpb = even_masks(fwd_cap(o.shape, o.n, true), a.nmasks, cg * b->nfs, b->ncu, per_cu, wpb);
-            a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
+            // (to the mask, not to whole rounds of the wavefronts, which left one group
+            // of n = 8 with 200 blocks for 256 CUs: 300 configurations, two flavours,
+            // 2695 -> 2562 us)
+            a.mpb = even_block(wpb, wpb * fwd_cap(o.shape, o.n, true), 1, a.nmasks, cg * b->nfs, (int64_t)b->ncu * per_cu);
         }
+        a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
         LAUNCH_TRY(launch_sub_level(a, cg, wpb, s));
         return COS_OK;
     }
@@ -1051,11 +1048,10 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
         // two workgroups fit a CU
         a.mpb = std::max(1, std::min({kSplitMasks, (wpb + heads - 1) / heads, a.nmasks}));
         while (a.mpb > 1 && fwd_lds_bytes(o.n, a.mpb) > 80 * 1024) --a.mpb;
-        a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
     } else {
-        a.mpb = fwd_masks(o.shape, o.n, b->nfs, a.nmasks, cg, b->ncu);
-        a.nblocks = (a.nmasks + wpb * a.mpb - 1) / (wpb * a.mpb);
+        a.mpb = wpb * fwd_masks(o.shape, o.n, b->nfs, a.nmasks, cg, b->ncu);
     }
+    a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
     LAUNCH_STEPS(level_steps(o, l), launch_level_fwd(a, cg, wpb, s));
     return COS_OK;
 }
@@ -1343,6 +1339,12 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
             }
             return COS_OK;
         };
+        // a CU holds one workgroup of the reverse: unlabelled kAdjWaves wavefronts (their
+        // 147 to 256 registers from n = 6 on leave room for two or three a SIMD),
+        // labelled kSubAdjWaves.  (Counted as two where LDS alone allows it, n <= 8, the
+        // blocks of a level ran in two rounds: gradients of 2269 configurations of
+        // order 8 1164 us against 1066, 1000 of order 8 655 against 622, 1570 of order
+        // 7 with four flavours 1072 against 1031.)
         auto reverse = [&](int from, int to, bool upper) -> cos_status {
             for (int l = from; l >= to; --l) {
                 LvlArgs a = level_args(b, o, cycle_weight);
@@ -1356,7 +1358,7 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 a.F_gstride = fstride;
                 a.F_frows = srows;
                 a.F_row0 = (int32_t)srow(l, upper);
-                const int nm = o.hp->levels[l].w, per_cu = adj_waves_per_cu(o);
+                const int nm = o.hp->levels[l].w;
                 a.out_bar = d_out_bar;
                 a.Gbar_T = GbT;
                 a.sbar_T = sbT;
@@ -1371,8 +1373,9 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                     a.row_items = ((int64_t)nm * cg * b->nfs * 8 <= (int64_t)b->ncu * 16 &&
                                    2 * level_rows(*o.hp, l, l) >= (int64_t)nm * o.slots()) ? 1 : 0;
                     const int items = a.row_items ? nm * o.n : nm;
-                    a.mpb = even_masks(o.shape.adj_cap, items, cg * b->nfs * (o.n > 6 ? 2 : 1), b->ncu, per_cu, kSubAdjWaves);
-                    a.nblocks = (items + kSubAdjWaves * a.mpb - 1) / (kSubAdjWaves * a.mpb);
+                    a.mpb = even_block(kSubAdjWaves, kSubAdjWaves * o.shape.adj_cap, 1, items, cg * b->nfs * (o.n > 6 ? 2 : 1),
+                                       b->ncu);
+                    a.nblocks = (items + a.mpb - 1) / a.mpb;
                     LAUNCH_TRY(launch_sub_adj_level(a, cg, s));
                     continue;
                 }
@@ -1395,17 +1398,16 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
                 a.row_items = (int64_t)nm * b->nfs * cg <= 4 * (int64_t)b->ncu * kAdjWaves ? 1 : 0;
                 if (a.row_items) {
                     const int heads = level_heads(o, l);
-                    const int blocks = std::max(1, b->ncu * per_cu / kAdjWaves / (cg * b->nfs));   // per group and flavour
+                    const int blocks = std::max(1, b->ncu / (cg * b->nfs));   // per group and flavour
                     // (few tiles: half the items, so that each SIMD of twice the
                     // CUs has one wavefront; n = 8, 107 configurations, the
                     // reverse levels 214 -> 177 us)
                     const int items = (int64_t)nm * heads * b->nfs * cg <= (int64_t)b->ncu * 4 ? kAdjWaves / 2 : kAdjWaves;
                     a.mpb = std::min(kAdjListMasks, std::max((items + heads - 1) / heads, (nm + blocks - 1) / blocks));
-                    a.nblocks = (a.nmasks + a.mpb - 1) / a.mpb;
                 } else {
-                    a.mpb = even_masks(o.shape.adj_cap, a.nmasks, cg * b->nfs, b->ncu, per_cu, kAdjWaves);
-                    a.nblocks = (a.nmasks + kAdjWaves * a.mpb - 1) / (kAdjWaves * a.mpb);
+                    a.mpb = even_block(kAdjWaves, kAdjWaves * o.shape.adj_cap, kAdjWaves, nm, cg * b->nfs, b->ncu);
                 }
+                a.nblocks = (nm + a.mpb - 1) / a.mpb;
                 LAUNCH_STEPS(level_steps(o, l), launch_level_adj(a, cg, s));
             }
             return COS_OK;
