@@ -113,6 +113,11 @@ __device__ __forceinline__ void sub_states(double (&f)[R][NI], uint32_t (&cs)[R]
 #pragma unroll
             for (int r = 0; r < R; ++r) y[r] += slot_ld(make_plane(all.base + p * all.stride), lane8, oat + r * ostep);
     }
+    // (one flavour: nothing opens elsewhere, and the start row is no pair.  Adding
+    // zeros all the same, which the compiler must keep, made every load wait for
+    // the one before it: 64 configurations of n = 8, forward 646 us, without 451;
+    // 1000 4407 and 3350; of n = 6 306 and 226)
+    if (!MULTI && R == 2) return;
     // (selects: branches here made the compiler keep the reads of G in registers
     // across the two instances, and spill)
 #pragma unroll
