@@ -1265,7 +1265,10 @@ hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s) {
 // forward n = 4 26 / 28 -> 16 / 17 us, n = 5 43 / 54 -> 34 / 36 us; with the
 // reverse n = 4 69 / 74 -> 32 / 34 us, n = 5 121 / 165 -> 79 / 95 us.  At n = 6
 // one CU per group is too little (65 -> 96 us at 300 configurations, with the
-// reverse 179 -> 334 us): the line lies at n = 5.
+// reverse 179 -> 334 us): the line lies at n = 5, and with three or more flavours
+// at n = 4 for small batches.  At n <= 4 one launch took 0.3 to 0.95 of the level
+// kernels' time for one to four flavours and 1 to 32768 configurations (100000 of
+// n = 2, forward, 21 us against 17).
 // ---------------------------------------------------------------------------
 template <int N>
 struct SmallCtx {

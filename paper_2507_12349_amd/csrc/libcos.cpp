@@ -1057,8 +1057,13 @@ static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, i
 }
 
 // orders that run a whole sweep in one launch: their tables are there, and G
-// (and the dS/dG accumulators) of every flavour fit LDS
+// (and the dS/dG accumulators) of every flavour fit LDS.  Not order 5 with three or
+// more flavours in up to 32 groups: one workgroup then takes all flavours of a group
+// in turn while most CUs are idle (four flavours, 300 configurations, with gradients
+// 221 us in one launch and 147 by levels, 2048 244 and 192, 8192 292 and 425; three
+// flavours 169 and 135, 189 and 171, 207 and 357)
 static bool small_order(cos_batch_t b, const OrderGroup &o, bool reverse) {
+    if (o.n == kSmallMax && b->nfs > 2 && o.ngroups <= 32) return false;
     return !o.sub && b->plans[o.n].script && small_lds_bytes(o.n, b->nfs, reverse) <= 160 * 1024;
 }
 
