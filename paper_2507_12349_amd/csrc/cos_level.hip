@@ -1197,7 +1197,11 @@ hipError_t launch_level_adj(LvlArgs a, int ngroups, hipStream_t s) {
         hipLaunchKernelGGL(fn, grid, dim3(64 * wpa), shm, s, a);                           \
         break;                                                                                    \
     }
-        COS_ADJ_CASE(2) COS_ADJ_CASE(3) COS_ADJ_CASE(4) COS_ADJ_CASE(5)
+        case 2:   // (other batches of order 2 run in one launch)
+            if (a.nfs <= 2 || a.mask_only) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((level_adj_kernel<2, true, false>), grid, dim3(64 * wpa), shm, s, a);
+            break;
+        COS_ADJ_CASE(3) COS_ADJ_CASE(4) COS_ADJ_CASE(5)
         COS_ADJ_CASE(6) COS_ADJ_CASE(7) COS_ADJ_CASE(8) COS_ADJ_CASE(9)
         COS_ADJ_CASE(10) COS_ADJ_CASE(11) COS_ADJ_CASE(12)
 #undef COS_ADJ_CASE
