@@ -469,8 +469,8 @@ def workload_legs(B, torch, reps, cpu_threads=0, only=None):
             plain = npl / (p0.elapsed_time(p1) * 1e-3)
             leg.update({"plain_configs_per_s": plain, "batched_over_plain": leg["configs_per_s"] / plain,
                         "plain_equals_batched_bitwise": bool(torch.equal(Sp, S)),
-                        "plain_note": "one call per configuration: a launch per level with one of the 64 lanes of "
-                                      "each wavefront busy"})
+                        "plain_note": "one call per configuration: %s, with one of the 64 lanes of each wavefront busy"
+                                      % ("a launch per level" if n0 > 5 else "the levels in one launch")})
             if name == "plain_single":
                 Gh = G.cpu().numpy().reshape(nmat, n0, n0)
                 t0 = time.perf_counter()

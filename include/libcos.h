@@ -143,7 +143,8 @@ cos_status cos_batch_destroy(cos_batch_t b);
  * unlabelled, the two visits of one vertex stay inside the launches: 2n - 2
  * launches, and 2n with labels), each covering every group of that order.
  * Orders 2 to 5 without labels run all levels in one launch while the matrices
- * of every flavour fit a workgroup's LDS.  With two or more
+ * of every flavour fit a workgroup's LDS (order 5 with three or more flavours:
+ * in batches of more than 2048 configurations of that order).  With two or more
  * orders, the orders after the largest (after the two largest when the
  * others' windows would not fit) run on a second stream of the batch (made
  * at cos_batch_create, default priority, with level windows of their own,
@@ -267,8 +268,8 @@ cos_status cos_plan_counts(int32_t n, int64_t *states, int64_t *extensions, int6
 
 /* Memory of the reverse sweep.  The reverse levels need the forward states of
  * every level; segments = 1 stores them all (about 7 times the largest
- * level per group at n = 12), segments = 2 stores only levels h+1..2n during
- * the forward, reverses them, then computes levels 1..h again into the same
+ * level per group at n = 12), segments = 2 stores only the levels above a level
+ * h during the forward, reverses them, then computes levels 1..h again into the same
  * store and reverses those (h chosen so that both halves hold about the same
  * number of rows: about 40% less memory per group, the lower levels'
  * forward run twice).  0 (the default) takes 2 when storing every level would
@@ -291,11 +292,12 @@ cos_status cos_batch_adjoint_plan(cos_batch_t b, int32_t n, int32_t *split_level
  * inputs for each candidate launch shape -- wavefronts per workgroup of the
  * forward kernel (4, 8, 16; 8, 16 with COS_F_SUBLATTICE; levels with few masks
  * may use fewer) and the most masks
- * (state-table tiles) per wavefront of the forward (1, 2, 4, 8, 16) and, when
+ * per wavefront of the forward (1, 2, 4, 8, 16) and, when
  * d_out_bar is not NULL, of the reverse kernel (2, 4, 6, 8, 12, 16, 24, 32, 48, 64;
  * a reverse level is cut into as few rounds of the workgroups that fit the
  * chip as that cap allows, its masks spread evenly) -- keeps the fastest per order and
- * uses it for every later call on b.  Arguments as cos_connected_sum_batched
+ * uses it for every later call on b.  Orders whose sweeps are one launch
+ * (cos_connected_sum_batched) have one shape and are not timed.  Arguments as cos_connected_sum_batched
  * / _adjoint; the output
  * buffers are overwritten and on return hold what a call with the chosen
  * shapes writes.  Synchronous (waits for the stream).  S does not depend on
@@ -304,7 +306,10 @@ cos_status cos_batch_adjoint_plan(cos_batch_t b, int32_t n, int32_t *split_level
 cos_status cos_batch_autotune(cos_batch_t b, const double *d_G, const int64_t *d_Goff,
                               const double *d_stub, double cycle_weight, const double *d_out_bar,
                               double *d_out, double *d_G_bar, double *d_stub_bar, void *stream);
-/* The launch shape in use for order n (COS_EINVAL if the batch has none). */
+/* The launch shape of order n's level launches (COS_EINVAL if the batch has
+ * none).  Sweeps that are one launch do not use it: it then holds for the calls
+ * of that order that run by levels all the same (reproducible gradients,
+ * gradients in two segments). */
 cos_status cos_batch_launch_shape(cos_batch_t b, int32_t n, int32_t *fwd_waves,
                                   int32_t *fwd_masks, int32_t *adj_masks);
 /* Set the launch shape of order n instead of tuning it (for instance one that

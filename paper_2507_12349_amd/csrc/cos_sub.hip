@@ -301,14 +301,14 @@ __global__ void __launch_bounds__(1024) sub_fwd_kernel(const LvlArgs A) {
 //   tbar_m = sum_l B(m', h, s_h, l)[(h, s_h)] of the slot the next cycle opens
 //   on (1 at the full mask), B(m, u, s_u)[i] = sum_j G[i][j] a[j] over the
 //   current slots i, and dS/dG[i][j] += f[i] a[j].
-// A wavefront owns whole rows.  The workgroup keeps the rows i of G it needs
-// and their dS/dG accumulator for its 64 configurations in LDS ([i][j][lane]),
-// adding the accumulator to the packed gradient once per flavour.  Up to
-// n = 6 one workgroup owns every row i (2 x 72 KB at n = 6); at n = 7, 8 the
-// two matrices would not fit (2 x 128 KB at n = 8), so two workgroups share
-// a block of masks, each owning half of the rows i (grid z): both read the
-// child adjoints a, each reads its half of the states and writes its half of
-// B.
+// A wavefront takes the two rows of a head (its two labels) together.  The
+// workgroup keeps the rows i of its flavour's G that it needs and their dS/dG
+// accumulator for its 64 configurations in LDS ([i][j][lane]), and adds the
+// accumulator to the packed gradient at its end.  Up to n = 6 one workgroup owns
+// every row i (2 x 72 KB at n = 6); at n = 7, 8 the two matrices would not fit (2 x
+// 128 KB at n = 8), so two workgroups, next to each other in the grid, share a block
+// of masks, each owning half of the rows i: both read the child adjoints a, each
+// reads its half of the states and writes its half of B.
 // ---------------------------------------------------------------------------
 template <int N>
 struct SubAdjShape {

@@ -526,8 +526,8 @@ cos_status check_weight(int32_t flags, double cycle_weight) {
 
 // launch shape of the level kernels of one order
 struct LaunchShape {
-    int fwd_wpb = 8;    // forward: wavefronts per workgroup (<= 8; sublattice: <= 16, default 16)
-    int fwd_cap = 0;    // forward: most masks per wavefront (0: by flavour count)
+    int fwd_wpb = 8;    // forward: wavefronts per workgroup (<= 16; sublattice: default 16)
+    int fwd_cap = 0;    // forward: most masks per wavefront (0: by order, see fwd_cap below)
     int adj_cap = 8;    // reverse: most masks per wavefront
 };
 
@@ -538,7 +538,7 @@ struct OrderGroup {
     int64_t gt_off = 0, sig_off = 0, lane_off = 0;   // offsets into the packed buffers
     int chunk_fwd = 1, chunk_adj = 1;  // groups per chunk (bounded workspace)
     int adj_split = 0;                 // reverse sweep: 0 = every forward level stored; h > 0 = levels
-                                       // h+1..2n stored by the forward, levels 1..h recomputed later
+                                       // above h stored by the forward, levels 1..h recomputed later
     int64_t gb_off = 0, sb_off = 0;    // offsets into the packed gradient accumulators
     int64_t gp_off = 0, sp_off = 0;    // deterministic reverse: offsets into the partial sums
     LaunchShape shape;                 // launch shape of the level kernels (autotuned)
@@ -924,9 +924,7 @@ static LvlArgs level_args(cos_batch_t b, const OrderGroup &o, double cycle_weigh
     return a;
 }
 
-// masks per wavefront of an unlabelled forward level launch with `nm` masks and
-// `ng` groups: up to the shape's cap (to amortise loading G into LDS), fewer when
-// the level is small so that its rows spread over enough wavefronts
+// most masks per wavefront of a forward level launch: the shape's, or by order
 static int fwd_cap(const LaunchShape &sh, int n, bool sub) {
     if (sh.fwd_cap) return sh.fwd_cap;
     if (sub) return 16;
@@ -936,6 +934,9 @@ static int fwd_cap(const LaunchShape &sh, int n, bool sub) {
     // six flavours: 17.8 ms at 2, 16.7 at 4 and 8; 512, one flavour: 11.35 at both)
     return n >= 12 ? 4 : 2;
 }
+// masks per wavefront of an unlabelled forward level launch with `nm` masks and
+// `ng` groups: up to that cap (to amortise loading G into LDS), fewer when the level
+// is small so that its rows spread over enough wavefronts
 static int fwd_masks(const LaunchShape &sh, int n, int nfs, int nm, int ng, int ncu) {
     const int64_t per = ((int64_t)nm * ng * nfs) / std::max<int64_t>(1, (int64_t)ncu * 16);
     return (int)std::max<int64_t>(1, std::min<int64_t>(fwd_cap(sh, n, false), per));
@@ -1162,7 +1163,7 @@ cos_status cos_connected_sum_batched(cos_batch_t b, const double *d_G, const int
 }
 
 // the split level h of a two-segment reverse sweep that minimises the larger
-// segment (levels 1..h, recomputed, or h+1..2n, stored by the first forward)
+// segment (levels 1..h, recomputed, or those above, stored by the first forward)
 // (a level with special masks cannot be h: the value with which the cycle of
 // head n - 1 opens there is stored when their own level is processed, and level
 // h is not processed again)
@@ -1246,7 +1247,7 @@ static cos_status prepare_adjoint(cos_batch_t b) {
 }
 
 // forward (levels kept) and reverse levels of one order.  Every forward level
-// is stored, or with a split level h only levels h+1..2n: their reverse runs
+// is stored, or with a split level h only the levels above: their reverse runs
 // first, then levels 1..h are computed again into the same store and
 // reversed (the adjoint windows keep B(h+1) meanwhile)
 static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double *d_G, const int64_t *d_Goff,
