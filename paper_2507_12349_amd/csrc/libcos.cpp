@@ -1509,12 +1509,14 @@ cos_status cos_batch_autotune(cos_batch_t b, const double *d_G, const int64_t *d
     static const int kAdjCaps[] = {2, 4, 6, 8, 12, 16, 24, 32, 48, 64};
     for (OrderGroup &o : b->orders) {
         // a one-launch sweep has one shape
-        if (small_order(b, o, false) && (!d_out_bar || (small_order(b, o, true) && !o.adj_split))) continue;
+        const bool one_launch = small_order(b, o, false);
+        if (one_launch && (!d_out_bar || (small_order(b, o, true) && !o.adj_split))) continue;
         // forward: waves per workgroup x masks per wavefront
         LaunchShape best = o.shape;
         float tbest = 1e30f;
         for (int wv : (o.sub ? kSubWaves : kWaves))
             for (int cap : kCaps) {
+                if (one_launch) break;
                 o.shape.fwd_wpb = wv;
                 o.shape.fwd_cap = cap;
                 float t;
