@@ -1009,8 +1009,8 @@ __global__ void __launch_bounds__(64 * kAdjWaves) level_adj_det_kernel(const Lvl
 }
 
 // sums the parts in order: GbT[i] = sum_p Gpart[p][i], sbT[g][l] = sum_p Spart[p][g][l]
-__global__ void det_reduce_kernel(int parts, const double *__restrict__ Gpart, const double *__restrict__ Spart, int64_t gsize,
-                                  int64_t ssize, double *__restrict__ GbT, double *__restrict__ sbT) {
+__global__ void det_reduce_kernel(int parts, const double *__restrict__ Gpart, const double *__restrict__ Spart,
+                                  int64_t gsize, int64_t ssize, double *__restrict__ GbT, double *__restrict__ sbT) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < gsize) {
         double x = 0.0;
@@ -1141,7 +1141,8 @@ hipError_t launch_level_det(const LvlArgs &a, int ngroups, hipStream_t s) {
     const int n = a.plan.n;
     const size_t shm = det_lds_bytes(n, a.det_per);
     if (a.det_per < 1 || a.det_per > kDetPer) return hipErrorInvalidValue;
-    if (a.det_per > 1 && a.det_per * ((a.nmasks + a.det_parts - 1) / a.det_parts) > kAdjListMasks) return hipErrorInvalidValue;
+    if (a.det_per > 1 && a.det_per * ((a.nmasks + a.det_parts - 1) / a.det_parts) > kAdjListMasks)
+        return hipErrorInvalidValue;
     if (a.det_parts < 1 || a.det_parts > kDetParts) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((a.det_parts + a.det_per - 1) / a.det_per * a.nfs), (unsigned)ngroups), block(64 * kAdjWaves);
     switch (n) {
@@ -1270,9 +1271,9 @@ hipError_t launch_level_fwd(LvlArgs a, int ngroups, int wpb, hipStream_t s) {
 // reverse n = 4 69 / 74 -> 32 / 34 us, n = 5 121 / 165 -> 79 / 95 us.  At n = 6
 // one CU per group is too little (65 -> 96 us at 300 configurations, with the
 // reverse 179 -> 334 us): the line lies at n = 5, and with three or more flavours
-// at n = 4 for small batches.  At n <= 4 one launch took 0.3 to 0.95 of the level
-// kernels' time for one to four flavours and 1 to 32768 configurations (100000 of
-// n = 2, forward, 21 us against 17).
+// at n = 4 for small batches.  At n <= 4 one launch took 0.26 to 0.86 of the level
+// kernels' time for one to four flavours and 1 to 32768 configurations (forward of
+// 100000 with one flavour: n = 2 21 us against 17, n = 3 42 and 39).
 // ---------------------------------------------------------------------------
 template <int N>
 struct SmallCtx {
