@@ -90,7 +90,8 @@ struct HostPlan {
     std::vector<int32_t> masks;
     std::vector<int4> levels;       // [nlev + 2]
     std::vector<int32_t> mrec;      // [masks][rec_ints]
-    std::vector<int32_t> special;   // level kernels' tables: special masks per level
+    std::vector<int2> special;      // level kernels' tables: special masks per level: copies of
+                                    // their records, from .x on, and their number .y
     std::vector<int32_t> items;     // and (mask, head) pairs per level
     std::vector<int32_t> script;    // small orders: the one-launch sweeps' table
     int nlev = 0;                   // levels (launches of a sweep)
@@ -187,7 +188,7 @@ void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
     P.slots = 1;
     P.nlev = 2 * nb;
     P.levels.assign(P.nlev + 2, make_int4(0, 0, 0, 0));
-    P.special.assign(P.nlev + 2, 0);
+    P.special.assign(P.nlev + 2, make_int2(0, 0));
     P.items.assign(P.nlev + 2, 0);
     if (nb == 0) {
         P.max_rows = 1;
@@ -216,14 +217,13 @@ void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
         int64_t r = 0;
         const int mask0 = (int)P.masks.size();
         for (int code : bylevel[l]) {
-            const uint32_t ones = P.minfo[code] & 0xffffu, twos = P.minfo[code] >> 16;
+            const uint32_t twos = P.minfo[code] >> 16;
             P.masks.push_back(code);
             // three rows per head, and the one row of head n - 1 once vertex 0 is full
             if (twos & 1u) {
                 P.rowbase[code] = (int32_t)(r + extra);
                 r += extra + (3 * (1 + __builtin_popcount(twos & ~1u)) + 1) * nb;
                 P.items[l] += 2 + __builtin_popcount(twos & ~1u);
-                if (!ones) ++P.special[l];
             } else {
                 P.rowbase[code] = (int32_t)r;
                 r += 3 * nb;
@@ -237,10 +237,18 @@ void build_host_plan_tiles(int n, bool multi, HostPlan &P) {
         P.max_masks = std::max(P.max_masks, nm);
     }
     P.levels[P.nlev + 1] = make_int4((int)P.total_rows, 0, (int)P.masks.size(), 0);
-    P.mrec.assign(P.masks.size() * kRecInts, 0);
+    // records: every mask's, then the special masks' once more, level by level
+    std::vector<int32_t> recs = P.masks;
+    for (int l = 1; l <= P.nlev; ++l) {
+        P.special[l].x = (int)recs.size();
+        for (int code : bylevel[l])
+            if ((P.minfo[code] & 0xffffu) == 0u) recs.push_back(code);
+        P.special[l].y = (int)recs.size() - P.special[l].x;
+    }
+    P.mrec.assign(recs.size() * kRecInts, 0);
     // (byte offsets: at most 0.86 GB per level and flavour, at n = 12)
-    for (size_t i = 0; i < P.masks.size(); ++i) {
-        const int code = P.masks[i];
+    for (size_t i = 0; i < recs.size(); ++i) {
+        const int code = recs[i];
         const uint32_t twos = P.minfo[code] >> 16;
         int32_t *r = &P.mrec[i * kRecInts];
         r[0] = (int32_t)P.minfo[code];
@@ -995,10 +1003,16 @@ static int det_per(const OrderGroup &o, int l, int parts, int64_t planes, int nc
 // vertex that the tiles keep out of the levels
 static int level_steps(const OrderGroup &o, int l) { return !o.sub && l == o.hp->nlev ? 3 : 1; }
 
-// one forward level of `cg` groups, its masks filled in here
-static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, int l, int cg, hipStream_t s) {
+// one forward level of `cg` groups, its masks filled in here: all, or the special
+// ones alone
+static cos_status forward_level(cos_batch_t b, const OrderGroup &o, LvlArgs a, int l, int cg, hipStream_t s,
+                                bool special = false) {
     a.level = l;
     level_masks(o, l, &a);
+    if (special) {
+        a.mask0 = o.hp->special[l].x;
+        a.nmasks = o.hp->special[l].y;
+    }
     int wpb = o.shape.fwd_wpb;
     if (o.sub) {
         // workgroups that a CU holds: by G in LDS, and by registers (75 to 128 from n =
@@ -1164,14 +1178,10 @@ cos_status cos_connected_sum_batched(cos_batch_t b, const double *d_G, const int
 
 // the split level h of a two-segment reverse sweep that minimises the larger
 // segment (levels 1..h, recomputed, or those above, stored by the first forward)
-// (a level with special masks cannot be h: the value with which the cycle of
-// head n - 1 opens there is stored when their own level is processed, and level
-// h is not processed again)
 static int best_split(const HostPlan &p) {
     int best = 0;
     int64_t bv = INT64_MAX;
     for (int h = 1; h < p.nlev; ++h) {
-        if (!p.special.empty() && p.special[h]) continue;
         const int64_t v = std::max(level_rows(p, 1, h), level_rows(p, h + 1, p.nlev));
         if (v < bv) bv = v, best = h;
     }
@@ -1426,6 +1436,22 @@ static cos_status adjoint_order(cos_batch_t b, const OrderGroup &o, const double
             // level 1 is the start state, which the kernels form themselves
             HIP_TRY(tmark(b, COS_PHASE_FORWARD, s));
             if (cos_status st = forward(1, h - 1, false)) return st;
+            // the value with which the cycle of head n - 1 opens in a special mask is
+            // stored when the mask's own level is processed: those of level h once
+            // more (what they write for level h + 1 goes to the window that the adjoints
+            // of level h will take)
+            if (!o.sub && o.hp->special[h].y) {
+                LvlArgs a = level_args(b, o, cycle_weight);
+                a.group0 = c0;
+                a.cur = Fs;
+                a.cur_gstride = fstride;
+                a.cur_frows = srows;
+                a.cur_row0 = (int32_t)srow(h, false);
+                a.nxt = (h & 1) ? B1 : B0;
+                a.nxt_gstride = bstride;
+                a.nxt_frows = mrows;
+                if (cos_status st = forward_level(b, o, a, h, cg, s, true)) return st;
+            }
             HIP_TRY(tmark(b, COS_PHASE_REVERSE, s));
             if (cos_status st = reverse(h, 1, false)) return st;
         }
